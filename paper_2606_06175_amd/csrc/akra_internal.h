@@ -22,6 +22,9 @@ namespace akra {
 // ------------------------------------------------------------------------------------------------
 // padding (in entries) after the coefficient table and the kernel-scaled alm buffers
 constexpr int ALM_PAD = 64;
+// the scalar functions of the transforms run to degree lmax + EXT_L (the stencil of sin^2 theta times a
+// spin-2 function reaches two degrees further)
+constexpr int EXT_L = 2;
 // unmasked-pixel compaction: threads per block, contiguous pixels per thread, pixels per tile
 constexpr int CMP_T = 256, CMP_PER = 16, CMP_TILE = CMP_T * CMP_PER;
 // spectra: degrees per block, orders per partial sum, pairs per launch
@@ -49,7 +52,7 @@ struct alignas(32) Coef64 {
 struct alignas(16) Coef32 {
     float a, b, g, pad;
 };
-// Scaled form of the same recurrence, run by the Legendre kernels away from the poles.  With
+// Scaled form of the same recurrence, run by the spin form of the Legendre kernels.  With
 // lambda_l = c_l mu_l, where c_{l0} = c_{l0+1} = 1 and c_{l+1} = g_l c_{l-1},
 //   mu_{l+1} = (a' x +- b') mu_l - mu_{l-1},   a' = a c_l / c_{l+1},  b' = b c_l / c_{l+1},
 // two FMAs per spin and step instead of three operations and a shared product.  Every g_l < 1 and
@@ -59,9 +62,17 @@ struct alignas(16) Coef32 {
 struct alignas(32) Coef64S {
     double a, b, c, ic;  // a', b', c_l, 1 / c_l
 };
-struct alignas(16) Coef32S {
-    float a, b, c, ic;
-};
+// Scalar functions l_lm = sqrt((2l+1)/4pi) d^l_{m0}: x l_l = A_{l+1} l_{l+1} + A_l l_{l-1} with
+// A_l = sqrt((l^2 - m^2) / (4 l^2 - 1)).  Scaled the same way, l_l = c_l mu_l with c_m = c_{m+1} = 1 and
+// c_{l+1} = (A_l / A_{l+1}) c_{l-1}: mu_{l+1} = a' x mu_l - mu_{l-1}, a' = c_l / (A_{l+1} c_{l+1}).
+// Stencil of sin^2(theta) W_lm and sin^2(theta) X_lm in them (W, X the half sum and half difference of the
+// spin +2 and -2 functions), with N = ((l-1) l (l+1) (l+2))^(-1/2):
+//   w_2  = N l (l-1) A_{l+1} A_{l+2},   w_-2 = N (l+1) (l+2) A_l A_{l-1},
+//   w_0  = N (m^2 - l (l+4) A_{l+1}^2 - (l+1) (l-3) A_l^2),
+//   x_1  = -2 m N (l-1) A_{l+1},        x_-1 = 2 m N (l+2) A_l.
+// They follow from sin^2 W = N ((sin d/dtheta)^2 - 2 cos sin d/dtheta + m^2) l, sin^2 X = -2 m N (sin
+// d/dtheta - cos) l and (sin d/dtheta) l_l = l A_{l+1} l_{l+1} - (l+1) A_l l_{l-1}.
+enum { ST_W2 = 0, ST_W0 = 1, ST_WM2 = 2, ST_X1 = 3, ST_XM1 = 4, STENCIL = 5 };
 // Near the poles FP32 kernels run the recurrence in difference form, with d_l = lambda_l - lambda_{l-1}
 // and y = 1 - x:
 //   d_{l+1} = (e - a y) lambda_l + g d_l,   lambda_{l+1} = lambda_l + d_{l+1},   e = a +- b - g - 1.
@@ -102,9 +113,10 @@ struct RingInfo {
 // counts as a north ring) or on south rings only (GCLS_SOUTH).  A one-ring class contracts with half
 // of the FMAs of the two-ring class.
 enum { GCLS_BOTH = 0, GCLS_NORTH = 1, GCLS_SOUTH = 2, GCLS_N = 3 };
-// 64-pair groups of one apply: per class an ascending list whose first npol entries are near-polar
-// groups of FP32 plans (difference form), then nmain others; list_any holds every listed group
-// (the union of the classes, for the batched kernels, which have no one-ring form).
+// 64-pair groups of one apply: per class an ascending list whose first npol entries are spin-form
+// groups (nearest the poles), then nmain others; list_any holds every listed group (the union of the
+// classes, for the batched kernels, which have no one-ring form), its first npol_any those the batched
+// kernels run in the difference form.
 struct GroupSet {
     const int *list[GCLS_N] = {nullptr, nullptr, nullptr};
     int npol[GCLS_N] = {0, 0, 0}, nmain[GCLS_N] = {0, 0, 0};
@@ -115,8 +127,8 @@ struct GroupSet {
 // Bluestein (RK_BF), two half-length Bluestein transforms (RK_BL), and the register engine's six
 // lists (RK_REG + q, q as in Plan::d_order_r)
 enum { RK_P2 = 0, RK_BF = 1, RK_BL = 2, RK_REG = 3, RING_KINDS = 9 };
-// ring blocks a class-split adjoint may write beyond the unsplit layout (each of up to two polar
-// and two further main parts rounds up by at most one block)
+// ring blocks a class-split adjoint may write beyond the unsplit layout (each of up to two further
+// spin and two further scalar parts rounds up by at most one block)
 constexpr int LIVE_NRB_EXTRA = 4;
 // values keying a recorded PCG iteration (see iter_key)
 constexpr int ITER_KEY_N = 18;
@@ -138,12 +150,16 @@ struct Plan {
     double *d_pair_z = nullptr;
     Coef64 *d_coef64 = nullptr;  // plain form: entry states (plan build)
     Coef32 *d_coef32 = nullptr;  // plain form: batched matrix-core synthesis
-    Coef64S *d_coef64s = nullptr;  // scaled form (Legendre kernels, FP64), and c_l for every form
-    Coef32S *d_coef32s = nullptr;  // scaled form (Legendre kernels, FP32)
+    Coef64S *d_coef64s = nullptr;  // scaled form of the spin kernels
     Coef32D *d_coef32d = nullptr;
-    double *d_seed2 = nullptr, *d_seedm2 = nullptr;  // [m][pair] seeds at l = max(m,2) (plan build only)
+    int64_t next = 0;              // (l, m) entries with l up to lmax + EXT_L: ext_base(m) + l
+    double *d_sa = nullptr, *d_sc = nullptr;  // [next] a' and c_l of the scalar functions
+    double *d_sten = nullptr;      // [STENCIL][nalm + ALM_PAD] stencil of the spin-2 functions, zero at l < 2
+    uint32_t *d_lm = nullptr;      // [next] m << 16 | l
+    double *d_seed2 = nullptr, *d_seedm2 = nullptr;  // [m][pair] seeds: spin groups at l = max(m,2) (both
+                                                     // spins), scalar groups at l = m (plan build only)
     int *d_seedk = nullptr;
-    Ent64 *d_ent = nullptr;     // [m][pair] entry states
+    Ent64 *d_ent = nullptr;     // [m][pair] entry states (scalar groups: mu_l, mu_{l-1} in c2, p2)
     int *d_entk = nullptr;      // [m][pair] their scale exponents
     int *d_entl = nullptr;      // [m][group] entry degree of each 64-pair group (ENT_SKIP: none)
     int ng64 = 0;               // 64-pair groups
@@ -180,7 +196,8 @@ struct Plan {
     int live_gen = 0;                // counts weight set-ups (recorded graphs hold the lists' sizes)
     bool skip_rings = true;          // weighted applies use the weighted sets (akra_plan_set_skip_unweighted)
     int n_live_rings = 0;            // rings that carry weight in the current weights
-    int nrb_cur = 1;                 // ring blocks the last single-right-hand-side adjoint wrote
+    int nrb_cur = 1;                 // ring blocks the last single-right-hand-side adjoint wrote,
+    int nrbs_cur = 0;                // the first nrbs_cur of them in the spin form
     int nrb_b_cur = 1;               // ring blocks the last batched adjoint wrote
     int64_t work_live[5] = {0, 0, 0, 0, 0};  // evaluated triples with the current weights: synthesis of
                                              // two-ring, one-ring groups, adjoint of two-ring, one-ring,
@@ -193,25 +210,22 @@ struct Plan {
     // contract with half the FMAs per loaded record or chunk
     int syn_R1 = 1, syn_V1 = 1, adj_R1 = 1, adj_W1 = 1, adj_L1 = 8;
     size_t part_rb_cap = 1;  // ring blocks the partial-sum buffer holds
-    // FP32 plans: the 64-pair groups nearest the poles run the Legendre stages in the difference
-    // form; the adjoint covers them with adj_nrb_polar single-wave ring blocks of at most adj_Rpol
-    // groups (spread evenly): 4, or 1 where blocks of four would leave the launch with too few waves
-    // for its long recurrences
-    int polar_groups = 0, adj_nrb_polar = 0, adj_Rpol = 4;
+    int spin_groups = 0;  // the first spin_groups 64-pair groups run the spin form
+    // batched FP32 kernels: the groups nearest the poles run in the difference form
+    int polar_groups = 0;
     // batched matrix-core kernels: waves (64-pair groups) per workgroup of the synthesis and the
     // adjoint; nrb_b adjoint ring blocks of bat_AW groups (the buffers hold those of bat_AW = 2)
     int bat_SW = 4, bat_AW = 4, nrb_b_cap = 0;
 
     // workspaces (sized for FP64; FP32 views reuse them)
     void *d_FG = nullptr;       // [nrhs][nrings][lmax+1][2] complex
-    void *d_part = nullptr;     // [nrb][nalm][4] adjoint partial sums
-    void *d_rec = nullptr;      // [nrhs][nalm + ALM_PAD] synthesis records (64 B in FP64), scaled form
-    float4 *d_recu = nullptr;   // FP32 plans with polar groups: [nrhs][nalm + ALM_PAD] unscaled alm for
-                                // the difference form
+    void *d_part = nullptr;     // [nrb][next][4] adjoint partial sums (spin blocks fill [nalm][4] of theirs)
+    double *d_rec = nullptr;    // [nrhs][next + ALM_PAD][5] synthesis records of the scalar form
+    void *d_rec_spin = nullptr; // [nrhs][nalm + ALM_PAD] synthesis records of the spin form (64 B)
     float *d_brec = nullptr;    // FP32 plans with nrhs > 1: [nalm + ALM_PAD][8 rhs][4] batched records
     int nrb_b = 0;              // FP32 plans with nrhs > 1: ring blocks of the batched adjoint
     int *d_wgstart_b = nullptr; // [m][nrb_b] first degree each batched adjoint block wrote
-    int64_t rec_stride = 0;     // records per right-hand side
+    int64_t rec_stride = 0;     // scalar records per right-hand side
     double *d_W = nullptr;      // [nrhs][npix] weights
     double *d_kern = nullptr;   // [lmax+1]
     double *d_kuser = nullptr;  // [lmax+1] caller-supplied kernel
@@ -336,8 +350,8 @@ akra_status hip_fail(hipError_t e, const char *what);
 // the weighted apply's Legendre and ring stages (single right-hand side, W of the plan's weights) as
 // one chain per class of ring groups on two streams (requires the side stream and both classes)
 void launch_weighted_chains(Plan &P, bool fp32, const double *W);
-// prologue: records {a, b, g, 0, K_l x_E, K_l x_B} per (l, m) in the transform precision (Im(a_l0) dropped)
-void launch_prologue(Plan &P, bool fp32, const double *xE, const double *xB, const double *kern, int nrhs);
+// prologue: the scalar form's records of K_l x (Im(a_l0) dropped) and, with spin, the spin form's
+void launch_prologue(Plan &P, const double *xE, const double *xB, const double *kern, int nrhs, bool spin);
 // entry states of the recurrence from the seeds (plan build)
 void launch_entry(Plan &P);
 // FP32 plans with nrhs > 1: kernel-scaled records and matrix-core synthesis of all right-hand sides
@@ -356,7 +370,8 @@ void launch_ring(Plan &P, bool fp32, int mode, const double *g1, const double *g
 // Legendre adjoint of d_FG into the partial sums d_part (live as for the synthesis; with live true,
 // rings without weight are read as G = 0); sets nrb_cur for the epilogue
 void launch_leg_adj(Plan &P, bool fp32, int rhs, bool live);
-// ring blocks an adjoint launch set writes
+// ring blocks an adjoint launch set writes: those of the spin form, and all
+int adj_blocks_spin_total(const Plan &P, bool live);
 int adj_blocks_total(const Plan &P, bool live);
 // per-ring flags (any weight nonzero on the ring, over the nrhs maps of W) into d_ring_live
 void launch_ring_live(Plan &P, int nrhs);
@@ -465,5 +480,8 @@ inline void adj_block(const AdjSplit &s, int n, int W, int b, int &first, int &c
         count = s.RA - 1;
     }
 }
+
+// spin-form groups per adjoint workgroup of W waves: two pairs per lane in a single wave, one otherwise
+constexpr int spin_gpb(int W) { return W == 1 ? 2 : W; }
 
 }  // namespace akra

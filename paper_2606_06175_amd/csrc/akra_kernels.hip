@@ -14,21 +14,22 @@ namespace akra {
 
 // ------------------------------------------------------------------------------------------------
 // Entry states (plan build).  One wave per (m, 64-pair group) runs the FP64 recurrence from the
-// seeds at l0 = max(m, 2) with the same steps and rescaling as the Legendre kernels' ramp (two
-// steps, then a rescale), and stops at the first degree where some pair of the group contributes:
-// it has left the scaled range and reaches `live`.  FP64 plans take live = 2^-100: the values are
-// of order one where they oscillate, so the terms of a group that is still below 2^-100 everywhere
-// change a sum by less than 2^-100 of its scale, far under FP64 rounding (2^-53), and skipping them
-// saves about 5% of the triples at lmax 4096.  FP32 plans take 2^-44, the bound below which the
-// FP32 kernels' scaled values are still masked.  The state at the last degree l0 + 8q
-// before it is stored with that degree; a group that never contributes up to lmax is marked
-// ENT_SKIP.
+// seeds at l0 (max(m, 2) for the first nspin groups, which run the spin form, m for the others) with
+// the rescaling of the Legendre kernels' ramp (two steps, then a rescale), and stops at the first
+// degree where some pair of the group contributes: it has left the scaled range and reaches the form's
+// bound.  FP64 plans take 2^-100 (spin) and 2^-105 (scalar, whose sums are divided by sin^2 theta): the
+// values are of order one where they oscillate, so the terms of a group that is still below that
+// everywhere change a sum by far less than FP64 rounding (2^-53), and skipping them saves about 5% of
+// the triples at lmax 4096.  FP32 plans take 2^-44 and 2^-49.  The state at the last degree l0 + 8q
+// before it is stored with that degree; a group that never contributes up to its last degree is
+// marked ENT_SKIP.
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_entry(const double *__restrict__ seed2, const double *__restrict__ seedm2,
                                                const int *__restrict__ seedk, const double *__restrict__ pair_z,
-                                               const Coef64 *__restrict__ coef, Ent64 *__restrict__ ent,
-                                               int *__restrict__ entk, int *__restrict__ entl, int lmax, int npairs,
-                                               int ng, int gpb, double live)
+                                               const Coef64 *__restrict__ coef, const double *__restrict__ sa,
+                                               Ent64 *__restrict__ ent, int *__restrict__ entk,
+                                               int *__restrict__ entl, int lmax, int npairs, int ng, int gpb,
+                                               int nspin, double live_spin, double live_scalar)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -36,63 +37,51 @@ __global__ __launch_bounds__(256) void k_entry(const double *__restrict__ seed2,
     const int g = (blockIdx.x - m * gpb) * 4 + wave;
     if (m > lmax || g >= ng) return;
     const int p = g * 64 + lane;
-    const bool valid = p < npairs;
+    const bool valid = p < npairs, spin = g < nspin;
     const int64_t idx = (int64_t)m * npairs + p;
     double x = 0, c2 = 0, p2 = 0, cm = 0, pm = 0;
     int k = 0;
     if (valid) {
         x = pair_z[p];
         c2 = seed2[idx];
-        cm = seedm2[idx];
+        cm = spin ? seedm2[idx] : 0.0;
         k = seedk[idx];
     }
-    const int l0 = m > 2 ? m : 2;
-    const Coef64 *cf = coef + (int64_t)m * (2 * lmax + 1 - m) / 2;
-    double s2 = c2, sp2 = p2, sm = cm, spm = pm;
+    const int l0 = spin && m < 2 ? 2 : m, lend = spin ? lmax : lmax + EXT_L;
+    const double live = spin ? live_spin : live_scalar;
+    const Coef64 *cf = coef + alm_base(m, lmax);
+    const double *sm = sa + ext_base(m, lmax);
+    Ent64 e = {c2, p2, cm, pm};
     int sk = k, sl = l0, res = ENT_SKIP;
-    for (int l = l0; l <= lmax;) {
+    for (int l = l0; l <= lend;) {
         if (wave_any(valid && k == 0 && fmax(fabs(c2), fabs(cm)) >= live)) {
             res = sl;
             break;
         }
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            const Coef64 c = cf[l + t];
-            const double u = c.a * x;
-            const double n2 = fma(u + c.b, c2, -(c.g * p2));
-            const double nm = fma(u - c.b, cm, -(c.g * pm));
-            p2 = c2;
-            c2 = n2;
-            pm = cm;
-            cm = nm;
-        }
-        l += 2;
-        if (k < 0) {
-            const double big = fmax(fabs(c2), fabs(cm));
-            if (big > scale_hi<double>()) {
-                const double d = scale_down<double>();
-                c2 *= d;
-                p2 *= d;
-                cm *= d;
-                pm *= d;
-                k += 1;
+            if (spin) {
+                const Coef64 c = cf[l + t];
+                const double u = c.a * x;
+                const double n2 = fma(u + c.b, c2, -(c.g * p2));
+                const double nm = fma(u - c.b, cm, -(c.g * pm));
+                p2 = c2;
+                c2 = n2;
+                pm = cm;
+                cm = nm;
+            } else {
+                rstep_0(sm[l + t], x, c2, p2);
             }
         }
+        l += 2;
+        if (k < 0) rescale_slot<FORM_SPIN>(c2, p2, cm, pm, k);
         if (((l - l0) & 7) == 0) {
-            s2 = c2;
-            sp2 = p2;
-            sm = cm;
-            spm = pm;
+            e = {c2, p2, cm, pm};
             sk = k;
             sl = l;
         }
     }
     if (valid) {
-        Ent64 e;
-        e.c2 = s2;
-        e.p2 = sp2;
-        e.cm = sm;
-        e.pm = spm;
         ent[idx] = e;
         entk[idx] = sk;
     }
@@ -102,49 +91,81 @@ __global__ __launch_bounds__(256) void k_entry(const double *__restrict__ seed2,
 // ================================================================================================
 // prologue / epilogue / weights
 // ================================================================================================
-// records of the scaled plain form (c_l times the u combinations of K_l alm, FP64 arithmetic; see
-// SynRec) and, when recu is given, the unscaled u combinations for the difference form
-template <typename T>
-__global__ void k_prologue(const double *__restrict__ xE, const double *__restrict__ xB, const double *__restrict__ kern,
-                           const int *__restrict__ lof, const typename CoefT<T, 0>::type *__restrict__ coef,
-                           const Coef64S *__restrict__ cs64, int lmax, int64_t nalm, int64_t rec_stride,
-                           SynRec<T> *__restrict__ rec, float4 *__restrict__ recu)
+// One thread per entry (l, m), l <= lmax + 2, of the scalar form's records: a' and c_l times
+//   q_l = w_2(l-2) E_{l-2} + w_0(l) E_l + w_-2(l+2) E_{l+2} + i (x_1(l-1) B_{l-1} + x_-1(l+1) B_{l+1}),
+//   u_l = w_2(l-2) B_{l-2} + w_0(l) B_l + w_-2(l+2) B_{l+2} - i (x_1(l-1) E_{l-1} + x_-1(l+1) E_{l+1})
+// of E, B = K_l (x_E, x_B) (the stencil is zero at degrees below 2; Im(a_l0) dropped), in FP64.  Bound
+// by HBM: x_E, x_B and the stencil read once (neighbours come from the caches), 40 bytes written.  With
+// rsp also the spin form's record.
+__global__ __launch_bounds__(256) void k_prologue(const double2 *__restrict__ xE, const double2 *__restrict__ xB,
+                                                  const double *__restrict__ kern, const uint32_t *__restrict__ lm,
+                                                  const double *__restrict__ sten, const double *__restrict__ sa,
+                                                  const double *__restrict__ sc, const Coef64S *__restrict__ cs64,
+                                                  int lmax, int64_t nalm, int64_t next, int64_t rec_stride,
+                                                  double *__restrict__ rec, SpinRec *__restrict__ rsp)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int rhs = blockIdx.y;
-    if (i >= nalm) return;
-    const int64_t o = rhs * nalm + i;
-    const double K = kern ? kern[lof[i]] : 1.0;
-    const bool m0 = i <= lmax;
-    const auto c = coef[i];
-    const double er = K * xE[2 * o], ei = m0 ? 0.0 : K * xE[2 * o + 1];
-    const double br = K * xB[2 * o], bi = m0 ? 0.0 : K * xB[2 * o + 1];
-    const double s = cs64[i].c;
-    const double u0 = er - bi, u1 = ei + br, u2 = er + bi, u3 = br - ei;
-    SynRec<T> r;
-    r.a = c.a;
-    r.b = c.b;
-    r.g = (T)0;
-    r.pad = (T)0;
-    r.u0 = (T)(s * u0);
-    r.u1 = (T)(s * u1);
-    r.u2 = (T)(s * u2);
-    r.u3 = (T)(s * u3);
-    rec[rhs * rec_stride + i] = r;
-    if (recu) recu[rhs * rec_stride + i] = make_float4((float)u0, (float)u1, (float)u2, (float)u3);
-}
-
-// m of the alm index i = m (2 lmax + 1 - m)/2 + l
-__device__ __forceinline__ int m_of(int64_t i, int l, int lmax)
-{
-    const int64_t b = i - l;
-    const double A = 2.0 * lmax + 1.0;
-    int m = (int)((A - sqrt(A * A - 8.0 * (double)b)) * 0.5);
-    if (m < 0) m = 0;
-    if (m > lmax) m = lmax;
-    while (m > 0 && (int64_t)m * (2 * lmax + 1 - m) / 2 > b) --m;
-    while (m < lmax && (int64_t)(m + 1) * (2 * lmax - m) / 2 <= b) ++m;
-    return m;
+    if (e >= next) return;
+    const int l = (int)(lm[e] & 0xffff), m = (int)(lm[e] >> 16);
+    const int64_t i = e - (int64_t)EXT_L * m, ns = nalm + ALM_PAD;
+    const double2 *pE = xE + rhs * nalm, *pB = xB + rhs * nalm;
+    double q0 = 0, q1 = 0, u0 = 0, u1 = 0;
+    auto at = [&](int d, double2 &E, double2 &B) {
+        const double K = kern ? kern[l + d] : 1.0;
+        E = pE[i + d];
+        B = pB[i + d];
+        E.x *= K;
+        B.x *= K;
+        E.y = m ? K * E.y : 0.0;
+        B.y = m ? K * B.y : 0.0;
+    };
+    auto even = [&](int d, int row) {
+        if (l + d < m || l + d > lmax) return;
+        const double w = sten[row * ns + i + d];
+        double2 E, B;
+        at(d, E, B);
+        q0 = fma(w, E.x, q0);
+        q1 = fma(w, E.y, q1);
+        u0 = fma(w, B.x, u0);
+        u1 = fma(w, B.y, u1);
+    };
+    auto odd = [&](int d, int row) {
+        if (l + d < m || l + d > lmax) return;
+        const double x = sten[row * ns + i + d];
+        double2 E, B;
+        at(d, E, B);
+        q0 = fma(-x, B.y, q0);
+        q1 = fma(x, B.x, q1);
+        u0 = fma(x, E.y, u0);
+        u1 = fma(-x, E.x, u1);
+    };
+    even(-2, ST_W2);
+    odd(-1, ST_X1);
+    even(0, ST_W0);
+    odd(1, ST_XM1);
+    even(2, ST_WM2);
+    const double s = sc[e];
+    double *r = rec + (rhs * rec_stride + e) * 5;
+    r[0] = sa[e];
+    r[1] = s * q0;
+    r[2] = s * q1;
+    r[3] = s * u0;
+    r[4] = s * u1;
+    if (rsp && l <= lmax) {
+        double2 E, B;
+        at(0, E, B);
+        const Coef64S c = cs64[i];
+        SpinRec o;
+        o.a = c.a;
+        o.b = c.b;
+        o.g = o.pad = 0.0;
+        o.u0 = c.c * (E.x - B.y);
+        o.u1 = c.c * (E.y + B.x);
+        o.u2 = c.c * (E.x + B.y);
+        o.u3 = c.c * (B.x - E.y);
+        rsp[rhs * ns + i] = o;
+    }
 }
 
 // Workgroup sum of 256 threads' values in a fixed order (deterministic); the result in thread 0.
@@ -159,74 +180,123 @@ __device__ __forceinline__ double block_sum256(double s, double *sh)
     return sh[0];
 }
 
-// One alm index of the epilogue; returns the full-m weighted Re<x, out> of the index (for the
-// fused inner product of a CG iteration).
-template <typename T>
-__device__ __forceinline__ double epilogue_one(int64_t i, const T *__restrict__ part, const int *__restrict__ wgstart,
-                                               int nrb, int64_t nalm, const int *__restrict__ lof, int lmax,
-                                               const double *__restrict__ kern, double lam,
-                                               const double *__restrict__ xE, const double *__restrict__ xB,
-                                               double *__restrict__ outE, double *__restrict__ outB, int proj)
-{
-    const int l = lof[i];
-    const bool m0 = i <= lmax;
-    double s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-    if (l >= 2) {
-        // ring blocks that started above l wrote nothing for it
-        const int *ws = wgstart + (int64_t)m_of(i, l, lmax) * nrb;
-        for (int rb = 0; rb < nrb; ++rb) {
-            if (l < ws[rb]) continue;
-            const T *q = part + ((int64_t)rb * nalm + i) * 4;
-            s0 += (double)q[0];
-            s1 += (double)q[1];
-            s2 += (double)q[2];
-            s3 += (double)q[3];
-        }
-    }
-    // cE = -(2h + -2h)/2,  cB = (i/2)(2h - -2h)
-    double eR = -0.5 * (s0 + s2), eI = -0.5 * (s1 + s3);
-    double bR = -0.5 * (s1 - s3), bI = 0.5 * (s0 - s2);
-    if (m0) eI = bI = 0.0;
-    const double K = kern ? kern[l] : 1.0;
-    eR *= K; eI *= K; bR *= K; bI *= K;
-    if (xE) {
-        eR += lam * xE[2 * i];
-        bR += lam * xB[2 * i];
-        if (!m0) {
-            eI += lam * xE[2 * i + 1];
-            bI += lam * xB[2 * i + 1];
-        }
-    }
-    // block systems: the output block of the unknowns held at zero is zero
-    if (proj == 1) bR = bI = 0.0;
-    if (proj == 2) eR = eI = 0.0;
-    outE[2 * i] = eR;
-    outE[2 * i + 1] = eI;
-    outB[2 * i] = bR;
-    outB[2 * i + 1] = bI;
-    if (!xE) return 0.0;
-    const double wgt = m0 ? 1.0 : 2.0;
-    return wgt * ((eR * xE[2 * i] + eI * xE[2 * i + 1]) + (bR * xB[2 * i] + bI * xB[2 * i + 1]));
-}
-
-// E/B combination of the adjoint's partial sums, harmonic diagonal and + lambda x (grid-stride over
-// the alm indices).  With dot_red, also the workgroup partials of the full-m inner product <x, out>
-// (one per workgroup, summed in a fixed order by the CG scalar kernel).
-template <typename T>
-__global__ __launch_bounds__(256) void k_epilogue(const T *__restrict__ part, const int *__restrict__ wgstart, int nrb,
-                                                  int64_t nalm, const int *__restrict__ lof, int lmax,
+// Sums of the adjoint's ring-block slabs, E/B combination, harmonic diagonal and + lambda x.  The first
+// nrbs slabs hold 2h, -2h (spin form): E = -(2h + -2h) / 2, B = (i / 2) (2h - -2h).  The others hold
+// the scalar sums T_1, T_2 in units of mu, and with T = c_l times the slab sums
+//   E_l = -(w_2 T_1(l+2) + w_0 T_1(l) + w_-2 T_1(l-2) + i (x_1 T_2(l+1) + x_-1 T_2(l-1))),
+//   B_l = -(w_2 T_2(l+2) + w_0 T_2(l) + w_-2 T_2(l-2) - i (x_1 T_1(l+1) + x_-1 T_1(l-1))).
+// A workgroup walks tiles of 256 entries (l, m) that overlap by two on each side: every thread sums
+// the slabs of its entry into LDS and the inner 252 apply the stencil from there, so the slabs, the
+// bulk of the traffic, are read once.  Ring blocks that started above l wrote nothing for it.
+// With dot_red, also the workgroup partials of the full-m inner product <x, out> (one per workgroup,
+// summed in a fixed order by the CG scalar kernel).
+constexpr int EPI_TILE = 256 - 2 * EXT_L;
+template <typename S>
+__global__ __launch_bounds__(256) void k_epilogue(const S *__restrict__ part, const int *__restrict__ wgstart,
+                                                  int nrbs, int nrb, int64_t nalm, int64_t next,
+                                                  const uint32_t *__restrict__ lm, const double *__restrict__ sten,
+                                                  const double *__restrict__ sc, int lmax,
                                                   const double *__restrict__ kern, double lam,
                                                   const double *__restrict__ xE, const double *__restrict__ xB,
                                                   double *__restrict__ outE, double *__restrict__ outB, int proj,
                                                   double *__restrict__ dot_red)
 {
     __shared__ double sh[256];
-    double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nalm; i += (int64_t)gridDim.x * blockDim.x)
-        s += epilogue_one<T>(i, part, wgstart, nrb, nalm, lof, lmax, kern, lam, xE, xB, outE, outB, proj);
+    __shared__ double T[4][256];
+    const int tid = threadIdx.x;
+    const int64_t ns = nalm + ALM_PAD;
+    double dot = 0.0;
+    for (int64_t e0 = (int64_t)blockIdx.x * EPI_TILE; e0 < next; e0 += (int64_t)gridDim.x * EPI_TILE) {
+        const int64_t e = e0 + tid - EXT_L;
+        const bool valid = e >= 0 && e < next;
+        const uint32_t v = valid ? lm[e] : 0;
+        const int l = (int)(v & 0xffff), m = (int)(v >> 16);
+        const int64_t i = e - (int64_t)EXT_L * m;
+        const int *ws = wgstart + (int64_t)m * nrb;
+        double t[4] = {0, 0, 0, 0};
+        if (valid) {
+            for (int rb = nrbs; rb < nrb; ++rb) {
+                if (l < ws[rb]) continue;
+                const S *q = part + ((int64_t)rb * next + e) * 4;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) t[c] += (double)q[c];
+            }
+            const double s = sc[e];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) t[c] *= s;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) T[c][tid] = t[c];
+        __syncthreads();
+        if (valid && tid >= EXT_L && tid < 256 - EXT_L && l <= lmax) {
+            double eR = 0, eI = 0, bR = 0, bI = 0;
+            if (l >= 2) {
+                auto even = [&](int d, int row) {
+                    if (l + d < m) return;
+                    const double w = sten[row * ns + i];
+                    eR = fma(-w, T[0][tid + d], eR);
+                    eI = fma(-w, T[1][tid + d], eI);
+                    bR = fma(-w, T[2][tid + d], bR);
+                    bI = fma(-w, T[3][tid + d], bI);
+                };
+                auto odd = [&](int d, int row) {
+                    if (l + d < m) return;
+                    const double x = sten[row * ns + i];
+                    eR = fma(x, T[3][tid + d], eR);
+                    eI = fma(-x, T[2][tid + d], eI);
+                    bR = fma(-x, T[1][tid + d], bR);
+                    bI = fma(x, T[0][tid + d], bI);
+                };
+                if (nrb > nrbs) {
+                    even(-2, ST_WM2);
+                    odd(-1, ST_XM1);
+                    even(0, ST_W0);
+                    odd(1, ST_X1);
+                    even(2, ST_W2);
+                }
+                double s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+                for (int rb = 0; rb < nrbs; ++rb) {
+                    if (l < ws[rb]) continue;
+                    const S *q = part + ((int64_t)rb * next + i) * 4;
+                    s0 += (double)q[0];
+                    s1 += (double)q[1];
+                    s2 += (double)q[2];
+                    s3 += (double)q[3];
+                }
+                if (nrbs) {
+                    eR -= 0.5 * (s0 + s2);
+                    eI -= 0.5 * (s1 + s3);
+                    bR -= 0.5 * (s1 - s3);
+                    bI += 0.5 * (s0 - s2);
+                }
+            }
+            if (m == 0) eI = bI = 0.0;
+            const double K = kern ? kern[l] : 1.0;
+            eR *= K; eI *= K; bR *= K; bI *= K;
+            if (xE) {
+                eR += lam * xE[2 * i];
+                bR += lam * xB[2 * i];
+                if (m) {
+                    eI += lam * xE[2 * i + 1];
+                    bI += lam * xB[2 * i + 1];
+                }
+            }
+            // block systems: the output block of the unknowns held at zero is zero
+            if (proj == 1) bR = bI = 0.0;
+            if (proj == 2) eR = eI = 0.0;
+            outE[2 * i] = eR;
+            outE[2 * i + 1] = eI;
+            outB[2 * i] = bR;
+            outB[2 * i + 1] = bI;
+            if (xE)
+                dot += (m ? 2.0 : 1.0) *
+                       ((eR * xE[2 * i] + eI * xE[2 * i + 1]) + (bR * xB[2 * i] + bI * xB[2 * i + 1]));
+        }
+        __syncthreads();
+    }
     if (dot_red) {
-        const double t = block_sum256(s, sh);
-        if (threadIdx.x == 0) dot_red[blockIdx.x] = t;
+        const double t = block_sum256(dot, sh);
+        if (tid == 0) dot_red[blockIdx.x] = t;
     }
 }
 
@@ -1543,13 +1613,13 @@ __global__ __launch_bounds__(64 * SW) __attribute__((amdgpu_waves_per_eu(2))) vo
     // a group that never enters still writes its (zero) F
     const int ls = __builtin_amdgcn_readfirstlane(uniform_ptr(entl + (int64_t)m * ng64)[w]);
 
-    typename PosT<float, F>::type x;
+    typename PosB<F>::type x;
     float c2 = 0.f, p2 = 0.f, cm = 0.f, pm = 0.f;
     int k = 0;
     setpos(x, 0.0);
     if (p < npairs && ls <= lmax) {
         setpos(x, pair_z[p]);
-        load_entry<float, F>(ent, entk, (int64_t)m * npairs + p, c2, p2, cm, pm, k);
+        load_entry_b<F>(ent, entk, (int64_t)m * npairs + p, c2, p2, cm, pm, k);
     }
     v16f D2e[2], D2o[2], Dme[2], Dmo[2];
 #pragma unroll
@@ -1669,7 +1739,7 @@ __global__ __launch_bounds__(64 * AW) __attribute__((amdgpu_waves_per_eu(2))) vo
                                                         int *__restrict__ wgstart, int64_t nalm, int lmax, int npairs,
                                                         int nrings, int nrhs, int q, const int *__restrict__ glist,
                                                         int ngl, const uint8_t *__restrict__ live, int rb0,
-                                                        int nrbl, int nrb)
+                                                        int nrbl, int nrb, int64_t slab)
 {
     __shared__ float lam[AW][2][64 * ABS];  // per wave: lambda+ and lambda- of its 64 pairs x 32 rows
     __shared__ float red[8 * AW * 64];      // the cross-wave sum, eight output registers at a time
@@ -1719,7 +1789,7 @@ __global__ __launch_bounds__(64 * AW) __attribute__((amdgpu_waves_per_eu(2))) vo
         }
     }
 
-    typename PosT<float, F>::type x;
+    typename PosB<F>::type x;
     setpos(x, valid ? pair_z[p] : 0.0);
     float c2 = 0.f, p2 = 0.f, cm = 0.f, pm = 0.f;
     int k = 0;
@@ -1736,7 +1806,7 @@ __global__ __launch_bounds__(64 * AW) __attribute__((amdgpu_waves_per_eu(2))) vo
     auto rows8 = [&](int lx, int t8, auto &&after) {
         const int lb = lx + t8;
         if (lb == e) {
-            if (valid) load_entry<float, F>(ent, entk, (int64_t)m * npairs + p, c2, p2, cm, pm, k);
+            if (valid) load_entry_b<F>(ent, entk, (int64_t)m * npairs + p, c2, p2, cm, pm, k);
             ramp = wave_any(k < 0);
         }
         if (lb < e || lb > lmax) {
@@ -1846,22 +1916,19 @@ __global__ __launch_bounds__(64 * AW) __attribute__((amdgpu_waves_per_eu(2))) vo
                 for (int w = 0; w < AW; ++w) sum += red[(w * 8 + r - h) * 64 + lane];
                 const int i = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), l = lc + i;
                 if (l <= lmax && rhs < nrhs)
-                    part[(((int64_t)(j >> 2) * nrb + rb) * nalm + base + l) * 4 + c] = sum;
+                    part[(((int64_t)(j >> 2) * nrb + rb) * slab + base + l) * 4 + c] = sum;
             }
         }
     }
 }
 
 
-void launch_prologue(Plan &P, bool fp32, const double *xE, const double *xB, const double *kern, int nrhs)
+void launch_prologue(Plan &P, const double *xE, const double *xB, const double *kern, int nrhs, bool spin)
 {
-    dim3 g((unsigned)cdiv(P.nalm, 256), nrhs);
-    if (fp32)
-        k_prologue<float><<<g, 256, 0, P.stream>>>(xE, xB, kern, P.d_lof, P.d_coef32s, P.d_coef64s, P.lmax, P.nalm,
-                                                   P.rec_stride, (SynRec<float> *)P.d_rec, P.d_recu);
-    else
-        k_prologue<double><<<g, 256, 0, P.stream>>>(xE, xB, kern, P.d_lof, P.d_coef64s, P.d_coef64s, P.lmax, P.nalm,
-                                                    P.rec_stride, (SynRec<double> *)P.d_rec, nullptr);
+    dim3 g((unsigned)cdiv(P.next, 256), nrhs);
+    k_prologue<<<g, 256, 0, P.stream>>>((const double2 *)xE, (const double2 *)xB, kern, P.d_lm, P.d_sten, P.d_sa,
+                                        P.d_sc, P.d_coef64s, P.lmax, P.nalm, P.next, P.rec_stride, P.d_rec,
+                                        spin ? (SpinRec *)P.d_rec_spin : nullptr);
 }
 
 // the near-polar groups list[0 .. npol) in the difference form and list[npol .. npol + nmain) in the
@@ -1893,12 +1960,12 @@ static void adj_b_launch(Plan &P, int q, int64_t fg_stride, int64_t lblocks, con
         k_leg_adj_b<1, AW><<<(unsigned)(8 * nbp * lblocks), 64 * AW, 0, P.stream>>>(
             (const float2 *)P.d_FG, fg_stride, P.d_coef32d, P.d_ent, P.d_entk, P.d_entl, P.ng64, P.d_pair_z,
             (float *)P.d_part, P.d_wgstart_b, P.nalm, P.lmax, P.npairs, P.nrings, P.nrhs, q, list, npol, live, 0, nbp,
-            nrb);
+            nrb, P.next);
     if (nbn > 0)
         k_leg_adj_b<0, AW><<<(unsigned)(8 * nbn * lblocks), 64 * AW, 0, P.stream>>>(
             (const float2 *)P.d_FG, fg_stride, P.d_coef32, P.d_ent, P.d_entk, P.d_entl, P.ng64, P.d_pair_z,
             (float *)P.d_part, P.d_wgstart_b, P.nalm, P.lmax, P.npairs, P.nrings, P.nrhs, q, list + npol, nmain, live,
-            nbp, nbn, nrb);
+            nbp, nbn, nrb, P.next);
 }
 
 // batched synthesis of FP32 plans: records and matrix-core sums per group of NBR right-hand sides, over
@@ -1942,18 +2009,21 @@ void launch_adj_batched(Plan &P, int q, bool live)
 void launch_epilogue_batched(Plan &P, int rhs, const double *kern, double lam, const double *xE, const double *xB,
                              double *outE, double *outB, double *dot_red)
 {
-    const float *part = (const float *)P.d_part + (int64_t)(rhs % NBR) * P.nrb_b_cur * P.nalm * 4;
-    const unsigned g = dot_red ? (unsigned)cg_red_blocks(P) : (unsigned)cdiv(P.nalm, 256);
-    k_epilogue<float><<<g, 256, 0, P.stream>>>(part, P.d_wgstart_b, P.nrb_b_cur, P.nalm, P.d_lof, P.lmax, kern, lam, xE,
-                                              xB, outE, outB, P.proj, dot_red);
+    // (the batched kernels run the spin form everywhere)
+    const float *part = (const float *)P.d_part + (int64_t)(rhs % NBR) * P.nrb_b_cur * P.next * 4;
+    const unsigned g = dot_red ? (unsigned)cg_red_blocks(P) : (unsigned)cdiv(P.next, EPI_TILE);
+    k_epilogue<float><<<g, 256, 0, P.stream>>>(part, P.d_wgstart_b, P.nrb_b_cur, P.nrb_b_cur, P.nalm, P.next, P.d_lm,
+                                              P.d_sten, P.d_sc, P.lmax, kern, lam, xE, xB, outE, outB, P.proj,
+                                              dot_red);
 }
 
 void launch_entry(Plan &P)
 {
     const int gpb = (int)cdiv(P.ng64, 4);
+    const bool f32 = P.prec == AKRA_FP32;
     k_entry<<<(unsigned)((int64_t)gpb * (P.lmax + 1)), 256, 0, P.stream>>>(
-        P.d_seed2, P.d_seedm2, P.d_seedk, P.d_pair_z, P.d_coef64, P.d_ent, P.d_entk, P.d_entl, P.lmax, P.npairs, P.ng64,
-        gpb, P.prec == AKRA_FP32 ? 0x1p-44 : 0x1p-100);
+        P.d_seed2, P.d_seedm2, P.d_seedk, P.d_pair_z, P.d_coef64, P.d_sa, P.d_ent, P.d_entk, P.d_entl, P.lmax,
+        P.npairs, P.ng64, gpb, P.spin_groups, f32 ? 0x1p-44 : 0x1p-100, f32 ? 0x1p-49 : 0x1p-105);
 }
 
 // Legendre synthesis of the prologue's records: every 64-pair group (live false), or the groups of
@@ -1988,39 +2058,57 @@ bool adj_shape_supported(int r, int w, int l)
     return false;
 }
 
-int adj_blocks_total(const Plan &P, bool live)
+int adj_blocks_spin_total(const Plan &P, bool live)
 {
     const GroupSet &G = live && P.skip_rings ? P.gs_live : P.gs_all;
     int n = 0;
-    for (int c = 0; c < GCLS_N; ++c) n += adj_blocks(P, c, G.npol[c], G.nmain[c]);
+    for (int c = 0; c < GCLS_N; ++c) n += adj_blocks_spin(P, c, G.npol[c]);
     return n;
+}
+
+int adj_blocks_total(const Plan &P, bool live)
+{
+    const GroupSet &G = live && P.skip_rings ? P.gs_live : P.gs_all;
+    int n = adj_blocks_spin_total(P, live);
+    for (int c = 0; c < GCLS_N; ++c) n += adj_blocks_main(P, c, G.nmain[c]);
+    return n;
+}
+
+// ring blocks of a class: the spin blocks of every class first (two-sided, north, south), then the
+// scalar ones in the same order (the slabs are disjoint)
+static void adj_first(const Plan &P, const GroupSet &G, int nspin, int cls, int &rbs, int &rbm)
+{
+    rbs = 0;
+    rbm = nspin;
+    for (int c = 0; c < cls; ++c) {
+        rbs += adj_blocks_spin(P, c, G.npol[c]);
+        rbm += adj_blocks_main(P, c, G.nmain[c]);
+    }
+}
+
+template <int CLS>
+static void adj_cls(Plan &P, bool fp32, int rhs, const GroupSet &G, const uint8_t *lv, int nspin, int nrb)
+{
+    if (G.npol[CLS] + G.nmain[CLS] <= 0) return;
+    int rbs, rbm;
+    adj_first(P, G, nspin, CLS, rbs, rbm);
+    leg_adj_cls<CLS>(P, fp32, rhs, G.list[CLS], G.npol[CLS], G.nmain[CLS], lv, rbs, rbm, nrb);
 }
 
 // Legendre adjoint of d_FG (right-hand side rhs) into the partial sums, over every 64-pair group
 // (live false) or the groups of the current weights by class, reading only rings that carry weight
-// (live true).  The near-polar groups of FP32 plans form their own blocks of at most adj_Rpol in
-// FP32 and in FP64 applies alike; the epilogue sums the nrb_cur blocks written.
+// (live true).  The epilogue sums the nrb_cur blocks written, the first nrbs_cur of them in the spin form.
 void launch_leg_adj(Plan &P, bool fp32, int rhs, bool live)
 {
     live = live && P.skip_rings;
     const GroupSet &G = live ? P.gs_live : P.gs_all;
     const uint8_t *lv = live ? P.d_ring_live : nullptr;
-    const int nrb = adj_blocks_total(P, live);
+    const int nspin = adj_blocks_spin_total(P, live), nrb = adj_blocks_total(P, live);
     auto n = [&](int c) { return G.npol[c] + G.nmain[c]; };
-    // ring blocks: the two-sided class first, then north, then south (the slabs are disjoint)
-    const int rb1 = adj_blocks(P, GCLS_BOTH, G.npol[GCLS_BOTH], G.nmain[GCLS_BOTH]);
-    const int rb2 = rb1 + adj_blocks(P, GCLS_NORTH, G.npol[GCLS_NORTH], G.nmain[GCLS_NORTH]);
-    auto two = [&]() {
-        if (n(GCLS_BOTH))
-            leg_adj_cls<GCLS_BOTH>(P, fp32, rhs, G.list[GCLS_BOTH], G.npol[GCLS_BOTH], G.nmain[GCLS_BOTH], lv, 0, nrb);
-    };
+    auto two = [&]() { adj_cls<GCLS_BOTH>(P, fp32, rhs, G, lv, nspin, nrb); };
     auto one = [&]() {
-        if (n(GCLS_NORTH))
-            leg_adj_cls<GCLS_NORTH>(P, fp32, rhs, G.list[GCLS_NORTH], G.npol[GCLS_NORTH], G.nmain[GCLS_NORTH], lv,
-                                    rb1, nrb);
-        if (n(GCLS_SOUTH))
-            leg_adj_cls<GCLS_SOUTH>(P, fp32, rhs, G.list[GCLS_SOUTH], G.npol[GCLS_SOUTH], G.nmain[GCLS_SOUTH], lv,
-                                    rb2, nrb);
+        adj_cls<GCLS_NORTH>(P, fp32, rhs, G, lv, nspin, nrb);
+        adj_cls<GCLS_SOUTH>(P, fp32, rhs, G, lv, nspin, nrb);
     };
     if (n(GCLS_BOTH) && n(GCLS_NORTH) + n(GCLS_SOUTH)) fork_join(P, two, one);
     else {
@@ -2028,6 +2116,7 @@ void launch_leg_adj(Plan &P, bool fp32, int rhs, bool live)
         one();
     }
     P.nrb_cur = nrb;
+    P.nrbs_cur = nspin;
 }
 
 int cg_red_blocks(const Plan &P) { return (int)std::min<int64_t>(CG_RED_BLOCKS, cdiv(P.nalm, 256)); }
@@ -2035,13 +2124,15 @@ int cg_red_blocks(const Plan &P) { return (int)std::min<int64_t>(CG_RED_BLOCKS, 
 void launch_epilogue(Plan &P, bool fp32, const double *kern, double lam, const double *xE, const double *xB,
                      double *outE, double *outB, double *dot_red)
 {
-    const dim3 g(dot_red ? (unsigned)cg_red_blocks(P) : (unsigned)cdiv(P.nalm, 256));
+    const dim3 g(dot_red ? (unsigned)cg_red_blocks(P) : (unsigned)cdiv(P.next, EPI_TILE));
     if (fp32)
-        k_epilogue<float><<<g, 256, 0, P.stream>>>((const float *)P.d_part, P.d_wgstart, P.nrb_cur, P.nalm, P.d_lof,
-                                                   P.lmax, kern, lam, xE, xB, outE, outB, P.proj, dot_red);
+        k_epilogue<float><<<g, 256, 0, P.stream>>>((const float *)P.d_part, P.d_wgstart, P.nrbs_cur, P.nrb_cur, P.nalm,
+                                                   P.next, P.d_lm, P.d_sten, P.d_sc, P.lmax, kern, lam, xE, xB, outE,
+                                                   outB, P.proj, dot_red);
     else
-        k_epilogue<double><<<g, 256, 0, P.stream>>>((const double *)P.d_part, P.d_wgstart, P.nrb_cur, P.nalm,
-                                                    P.d_lof, P.lmax, kern, lam, xE, xB, outE, outB, P.proj, dot_red);
+        k_epilogue<double><<<g, 256, 0, P.stream>>>((const double *)P.d_part, P.d_wgstart, P.nrbs_cur, P.nrb_cur,
+                                                    P.nalm, P.next, P.d_lm, P.d_sten, P.d_sc, P.lmax, kern, lam, xE,
+                                                    xB, outE, outB, P.proj, dot_red);
 }
 
 void launch_cg_alpha_sum(Plan &P, const double *red, double *scal, int *flag)
@@ -2215,9 +2306,7 @@ void launch_weighted_chains(Plan &P, bool fp32, const double *W)
 {
     const GroupSet &G = P.gs_live;
     const uint8_t *lv = P.d_ring_live;
-    const int nrb = adj_blocks_total(P, true);
-    const int rb1 = adj_blocks(P, GCLS_BOTH, G.npol[GCLS_BOTH], G.nmain[GCLS_BOTH]);
-    const int rb2 = rb1 + adj_blocks(P, GCLS_NORTH, G.npol[GCLS_NORTH], G.nmain[GCLS_NORTH]);
+    const int nspin = adj_blocks_spin_total(P, true), nrb = adj_blocks_total(P, true);
     auto n = [&](int c) { return G.npol[c] + G.nmain[c]; };
     auto ring = [&](const RingSet &RS) {
         if (fp32) ring_launch_t<float, 2>(P, RS, nullptr, nullptr, nullptr, nullptr, W, nullptr, nullptr, nullptr, 1, false);
@@ -2226,7 +2315,7 @@ void launch_weighted_chains(Plan &P, bool fp32, const double *W)
     auto two = [&]() {
         leg_synth_cls<GCLS_BOTH>(P, fp32, 1, G.list[GCLS_BOTH], G.npol[GCLS_BOTH], G.nmain[GCLS_BOTH]);
         ring(P.rs_cls[0]);
-        leg_adj_cls<GCLS_BOTH>(P, fp32, 0, G.list[GCLS_BOTH], G.npol[GCLS_BOTH], G.nmain[GCLS_BOTH], lv, 0, nrb);
+        adj_cls<GCLS_BOTH>(P, fp32, 0, G, lv, nspin, nrb);
     };
     auto one = [&]() {
         if (n(GCLS_NORTH))
@@ -2234,15 +2323,12 @@ void launch_weighted_chains(Plan &P, bool fp32, const double *W)
         if (n(GCLS_SOUTH))
             leg_synth_cls<GCLS_SOUTH>(P, fp32, 1, G.list[GCLS_SOUTH], G.npol[GCLS_SOUTH], G.nmain[GCLS_SOUTH]);
         ring(P.rs_cls[1]);
-        if (n(GCLS_NORTH))
-            leg_adj_cls<GCLS_NORTH>(P, fp32, 0, G.list[GCLS_NORTH], G.npol[GCLS_NORTH], G.nmain[GCLS_NORTH], lv,
-                                    rb1, nrb);
-        if (n(GCLS_SOUTH))
-            leg_adj_cls<GCLS_SOUTH>(P, fp32, 0, G.list[GCLS_SOUTH], G.npol[GCLS_SOUTH], G.nmain[GCLS_SOUTH], lv,
-                                    rb2, nrb);
+        adj_cls<GCLS_NORTH>(P, fp32, 0, G, lv, nspin, nrb);
+        adj_cls<GCLS_SOUTH>(P, fp32, 0, G, lv, nspin, nrb);
     };
     fork_join(P, two, one);
     P.nrb_cur = nrb;
+    P.nrbs_cur = nspin;
 }
 
 void launch_ring_grad(Plan &P, const double *g1, const double *g2, double *q1, double *q2, const double *W,

@@ -4,5 +4,5 @@
 
 namespace akra {
 template void leg_synth_cls<GCLS_NORTH>(Plan &, bool, int, const int *, int, int);
-template int leg_adj_cls<GCLS_NORTH>(Plan &, bool, int, const int *, int, int, const uint8_t *, int, int);
+template void leg_adj_cls<GCLS_NORTH>(Plan &, bool, int, const int *, int, int, const uint8_t *, int, int, int);
 }  // namespace akra

@@ -11,8 +11,17 @@
 
 #include "akra_internal.h"
 
-// FP32 plans run the spin-weighted recurrences of ring pairs within AKRA_DIFF_THETA radians of a pole
-// in the difference form.  Near a pole the per-step phase advance of the recurrence is of the order
+// The 64-pair groups that begin within AKRA_POLE_THETA radians of a pole run the spin form of the
+// Legendre kernels, the others the scalar form.  The scalar form divides its sums by sin^2(theta).  Its
+// terms share the phase error of one recurrence, so that error (about sqrt(l) eps / theta, the same in
+// both forms) is not amplified, but their own rounding is.  Synthesis error of both forms against 64
+// bits more, relative to the ring's rms, spin / scalar: lmax 4096: 4.1e-14 / 4.2e-14 at 0.2 rad,
+// 6.9e-14 / 7.4e-14 at 0.1; lmax 64: 1.6e-15 / 2.1e-15 at 0.45, 3.6e-15 / 5.2e-15 at 0.2,
+// 5.2e-15 / 1.1e-14 at 0.1, 1.6e-14 / 7.3e-13 at 0.02.  From 0.15 rad on the two are as good as equal
+// at the sizes whose second group begins that near a pole (Nside 350 and up).
+constexpr double AKRA_POLE_THETA = 0.15;
+// The batched FP32 kernels run the spin-weighted recurrences of ring pairs within AKRA_DIFF_THETA
+// radians of a pole in the difference form.  Near a pole the per-step phase advance of the recurrence is of the order
 // of theta; in the plain form the FP32 rounding of each step moves the phase by ~eps/theta, an
 // error that grows like sqrt(l) eps/theta.  The difference form keeps it at ~sqrt(l) eps there but
 // rounds more at large theta; the two errors cross near 0.45 rad.
@@ -101,14 +110,13 @@ static void build_rings(Plan &P)
 // The scaled form (Coef64S) divides out c_l with c_{l0} = c_{l0+1} = 1, c_{l+1} = g_l c_{l-1}: entries
 // below l0 and the padding carry c = 1, the entry at lmax its c with a' = b' = 0.
 static void build_coef(int lmax, std::vector<Coef64> &c64, std::vector<Coef32> &c32, std::vector<Coef32D> &c32d,
-                       std::vector<Coef64S> &c64s, std::vector<Coef32S> &c32s)
+                       std::vector<Coef64S> &c64s)
 {
     const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 2) / 2;
     c64.assign(nalm + ALM_PAD, Coef64{0, 0, 0, 0});
     c32.assign(nalm + ALM_PAD, Coef32{0, 0, 0, 0});
     c32d.assign(nalm + ALM_PAD, Coef32D{0, 0, 0, 0});
     c64s.assign(nalm + ALM_PAD, Coef64S{0, 0, 1, 1});
-    c32s.assign(nalm + ALM_PAD, Coef32S{0, 0, 1, 1});
     parallel_for(lmax + 1, [&](int m) {
         const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
         const int l0 = std::max(m, 2);
@@ -128,18 +136,52 @@ static void build_coef(int lmax, std::vector<Coef64> &c64, std::vector<Coef32> &
             if (l > l0) cs[l + 1] = g * cs[l - 1];
             const ld f = cs[l] / cs[l + 1];
             c64s[base + l] = Coef64S{(double)(a * f), (double)(b * f), (double)cs[l], (double)(1.0L / cs[l])};
-            c32s[base + l] = Coef32S{(float)(a * f), (float)(b * f), (float)cs[l], (float)(1.0L / cs[l])};
         }
         c64s[base + lmax] = Coef64S{0.0, 0.0, (double)cs[lmax], (double)(1.0L / cs[lmax])};
-        c32s[base + lmax] = Coef32S{0.0f, 0.0f, (float)cs[lmax], (float)(1.0L / cs[lmax])};
+    });
+}
+
+// Tables of the scalar functions (a', c_l over l = m .. lmax + EXT_L, and m << 16 | l of every entry) and
+// the stencil of the spin-2 functions in them (see akra_internal.h).
+static void build_scalar(int lmax, int64_t next, std::vector<double> &sa, std::vector<double> &sc,
+                         std::vector<double> &sten, std::vector<uint32_t> &lm)
+{
+    const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 2) / 2, ns = nalm + ALM_PAD;
+    sa.assign(next + ALM_PAD, 0.0);
+    sc.assign(next + ALM_PAD, 1.0);
+    sten.assign(STENCIL * ns, 0.0);
+    lm.assign(next, 0);
+    parallel_for(lmax + 1, [&](int m) {
+        typedef long double ld;
+        const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2, eb = base + (int64_t)EXT_L * m;
+        auto A = [&](int l) { return l <= m ? 0.0L : sqrtl(((ld)l * l - (ld)m * m) / (4.0L * l * l - 1.0L)); };
+        ld c0 = 1.0L, cm = 1.0L;  // c_l, c_{l-1}
+        for (int l = m; l <= lmax + EXT_L; ++l) {
+            const ld c1 = l == m ? 1.0L : A(l) / A(l + 1) * cm;
+            sa[eb + l] = (double)(c0 / (A(l + 1) * c1));
+            sc[eb + l] = (double)c0;
+            lm[eb + l] = (uint32_t)m << 16 | (uint32_t)l;
+            cm = c0;
+            c0 = c1;
+        }
+        for (int l = std::max(m, 2); l <= lmax; ++l) {
+            const ld L = l, M = m, N = 1.0L / sqrtl((L - 1) * L * (L + 1) * (L + 2));
+            const ld a0 = A(l), a1 = A(l + 1);
+            sten[ST_W2 * ns + base + l] = (double)(N * L * (L - 1) * a1 * A(l + 2));
+            sten[ST_W0 * ns + base + l] = (double)(N * (M * M - L * (L + 4) * a1 * a1 - (L + 1) * (L - 3) * a0 * a0));
+            sten[ST_WM2 * ns + base + l] = (double)(N * (L + 1) * (L + 2) * a0 * A(l - 1));
+            sten[ST_X1 * ns + base + l] = (double)(-2 * M * N * (L - 1) * a1);
+            sten[ST_XM1 * ns + base + l] = (double)(2 * M * N * (L + 2) * a0);
+        }
     });
 }
 
 // ---------------------------------------------------------------------------------------------
-// Seeds lambda_{l0,m}, l0 = max(m,2), for the north ring of every pair, by a recurrence in m:
+// Seeds for the north ring of every pair, by a recurrence in m.  Spin groups: lambda_{l0,m}, l0 = max(m,2):
 //   t_2 = d^2_{22} = c^4,  t_{m+1} = -t_m sqrt((2m+2)(2m+1)/((m+3)(m-1))) c s   (t_m = d^m_{m,2}),
 //   d^m_{m,-2} = t_m (s/c)^4;  for m < 2: d^2_{0,+-2} = sqrt6 c^2 s^2, d^2_{1,2} = 2 c^3 s, d^2_{1,-2} = -2 c s^3.
-// c = cos(theta/2), s = sin(theta/2).  Long double with explicit binary exponents; stored as
+// c = cos(theta/2), s = sin(theta/2).  Scalar groups: l_mm = sqrt((2m+1)/4pi) t_m, t_0 = 1,
+//   t_{m+1} = -t_m sqrt((2m+1)/(2m+2)) sin(theta).  Long double with explicit binary exponents; stored as
 // mant * 2^(512 k) (see Scale<double>).
 // ---------------------------------------------------------------------------------------------
 static void build_seeds(Plan &P, std::vector<double> &s2, std::vector<double> &sm, std::vector<int> &sk)
@@ -154,6 +196,24 @@ static void build_seeds(Plan &P, std::vector<double> &s2, std::vector<double> &s
     const ld inv4pi = 1.0L / (4.0L * 3.141592653589793238462643383279502884L);
     parallel_for(np, [&](int p) {
         const ld z = P.h_rings[p].z;
+        if (p >= 64 * P.spin_groups) {
+            const ld st = sqrtl((1 - z) * (1 + z));
+            int e = 0;
+            ld t = 1.0L;
+            for (int m = 0; m <= lmax; ++m) {
+                int ea;
+                const ld f = frexpl(t * sqrtl((2 * m + 1) * inv4pi), &ea);
+                ea += e;
+                const int k = ea < -400 ? (int)std::floor((ea + 300) / 512.0) : 0;
+                const size_t idx = (size_t)m * np + p;
+                s2[idx] = (double)ldexpl(f, ea - 512 * k);
+                sk[idx] = k;
+                int de;
+                t = frexpl(-t * sqrtl((ld)(2 * m + 1) / (2 * m + 2)) * st, &de);
+                e += de;
+            }
+            return;
+        }
         const ld c = sqrtl((1 + z) / 2), s = sqrtl((1 - z) / 2);
         const ld cs = c * s, t4 = (s / c) * (s / c) * (s / c) * (s / c);
         auto store = [&](int m, ld mant_m2, int e_m2, ld mant_2, int e_2) {
@@ -196,7 +256,8 @@ static void build_seeds(Plan &P, std::vector<double> &s2, std::vector<double> &s
 // at the earliest of its groups; every lane of a started wave or workgroup steps to lmax.
 static void compute_work(Plan &P)
 {
-    const int lmax = P.lmax, np = P.npairs, ng = P.ng64, gp = P.polar_groups;
+    const int lmax = P.lmax, np = P.npairs, ng = P.ng64, gp = P.spin_groups;
+    auto rows = [&](int ls) { return (int64_t)std::max(0, lmax - std::max(ls, 2) + 1); };  // of degrees 2 .. lmax
     auto pairs_in = [&](int g0, int g1) { return (int64_t)std::max(0, std::min(np, 64 * g1) - 64 * g0); };
     int64_t all = 0, syn = 0, adj = 0, bat = 0;
     // blocks of gs groups over [g0, g1): each starts at the earliest entry degree of its groups
@@ -205,7 +266,7 @@ static void compute_work(Plan &P)
         for (int b = g0; b < g1; b += gs) {
             int ls = ENT_SKIP;
             for (int g = b; g < std::min(g1, b + gs); ++g) ls = std::min(ls, e[g]);
-            if (ls <= lmax) w += pairs_in(b, std::min(g1, b + gs)) * (lmax - ls + 1);
+            w += pairs_in(b, std::min(g1, b + gs)) * rows(ls);
         }
         return w;
     };
@@ -219,7 +280,7 @@ static void compute_work(Plan &P)
             const int a0 = g0 + first, a1 = a0 + count;
             int ls = ENT_SKIP;
             for (int g = a0; g < a1; ++g) ls = std::min(ls, e[g]);
-            if (ls <= lmax) w += pairs_in(a0, a1) * (lmax - ls + 1);
+            w += pairs_in(a0, a1) * rows(ls);
         }
         return w;
     };
@@ -227,13 +288,20 @@ static void compute_work(Plan &P)
         all += (int64_t)np * (lmax - std::max(m, 2) + 1);
         const int *e = P.h_entl.data() + (size_t)m * ng;
         syn += seg(e, 0, gp, 1) + seg(e, gp, ng, P.syn_R);
-        adj += seg_adj(e, 0, gp, P.adj_Rpol, 1) + seg_adj(e, gp, ng, P.adj_R, P.adj_W);
+        adj += seg(e, 0, gp, spin_gpb(P.adj_W)) + seg_adj(e, gp, ng, P.adj_R, P.adj_W);
         bat += seg(e, 0, ng, 1);
     }
     P.work[0] = all;
     P.work[1] = syn;
     P.work[2] = adj;
     P.work_b = bat;
+}
+
+// ring blocks of the adjoint over every group
+static int adj_nrb_of(const Plan &P)
+{
+    return (P.spin_groups + spin_gpb(P.adj_W) - 1) / spin_gpb(P.adj_W) +
+           adj_split(P.ng64 - P.spin_groups, P.adj_R, P.adj_W).q;
 }
 
 static akra_status upload(void **dst, const void *src, size_t bytes, Plan &P)
@@ -273,6 +341,7 @@ static void compute_work_live(Plan &P)
 {
     const GroupSet &G = P.gs_live;
     const int lmax = P.lmax, ng = P.ng64, np = P.npairs;
+    auto rows = [&](int ls) { return (int64_t)std::max(0, lmax - std::max(ls, 2) + 1); };
     std::vector<int> hl[GCLS_N];
     const int *base = (const int *)(P.h_live + (P.nrings + 15) / 16 * 16) + (size_t)RING_KINDS * P.nrings;
     for (int c = 0; c < GCLS_N; ++c) hl[c].assign(base + (size_t)c * ng, base + (size_t)c * ng + G.npol[c] + G.nmain[c]);
@@ -285,7 +354,7 @@ static void compute_work_live(Plan &P)
                 ls = std::min(ls, e[gl[i]]);
                 pairs += std::min(64, np - 64 * gl[i]);
             }
-            if (ls <= lmax) w += pairs * (lmax - ls + 1);
+            w += pairs * rows(ls);
         }
         return w;
     };
@@ -301,7 +370,7 @@ static void compute_work_live(Plan &P)
                 ls = std::min(ls, e[gl[i]]);
                 pairs += std::min(64, np - 64 * gl[i]);
             }
-            if (ls <= lmax) w += pairs * (lmax - ls + 1);
+            w += pairs * rows(ls);
         }
         return w;
     };
@@ -316,7 +385,7 @@ static void compute_work_live(Plan &P)
             const int npol = G.npol[c], nmain = G.nmain[c];
             const bool two = c == GCLS_BOTH;
             const int64_t s = seg(e, gl, npol, 1) + seg(e, gl + npol, nmain, two ? P.syn_R : P.syn_R1);
-            const int64_t a = seg_adj(e, gl, npol, P.adj_Rpol, 1) + seg_adj(e, gl + npol, nmain, two ? P.adj_R : P.adj_R1,
+            const int64_t a = seg(e, gl, npol, spin_gpb(two ? P.adj_W : P.adj_W1)) + seg_adj(e, gl + npol, nmain, two ? P.adj_R : P.adj_R1,
                                                                  two ? P.adj_W : P.adj_W1);
             w[c == GCLS_BOTH ? 0 : 1] += s;
             w[c == GCLS_BOTH ? 2 : 3] += a;
@@ -374,7 +443,7 @@ static akra_status build_live_lists(Plan &P)
         const int c = gcls[g];
         for (int cc : {c, (int)GCLS_N}) {
             gbase[(size_t)cc * P.ng64 + cnt[cc]++] = g;
-            if (g < P.polar_groups) pol[cc]++;
+            if (g < (cc == GCLS_N ? P.polar_groups : P.spin_groups)) pol[cc]++;
         }
     }
     GroupSet &G = P.gs_live;
@@ -397,7 +466,7 @@ static akra_status build_live_lists(Plan &P)
 
 static void free_plan(Plan *P)
 {
-    void *ptrs[] = {P->d_rings, P->d_pair_z, P->d_coef64, P->d_coef32, P->d_coef64s, P->d_coef32s, P->d_recu,
+    void *ptrs[] = {P->d_rings, P->d_pair_z, P->d_coef64, P->d_coef32, P->d_coef64s, P->d_sa, P->d_sc, P->d_sten, P->d_lm, P->d_rec_spin,
                     P->d_seed2, P->d_seedm2, P->d_seedk,
                     P->d_ent, P->d_entk, P->d_entl, P->d_wgstart, P->d_wgstart_b, P->d_coef32d, P->d_brec,
                     P->d_tw64, P->d_tw32, P->d_bhat64, P->d_bhat32, P->d_bhatr64, P->d_bhatr32, P->d_order_r[0], P->d_order_r[1],
@@ -561,25 +630,17 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         int g = 0;
         while (g < P->ng64 && std::acos(P->h_rings[64 * g].z) < theta_c) ++g;
         P->polar_groups = std::min(P->ng64, (g + 3) / 4 * 4);
-        // blocks of four need some 8192 waves (8 per SIMD) to fill the device; fewer, and each wave's
-        // long difference-form recurrence leaves the launch latency-bound: then one group per block
-        P->adj_Rpol = (int64_t)((P->polar_groups + 3) / 4) * (lmax + 1) >= 8192 ? 4 : 1;
-        P->adj_nrb_polar = (P->polar_groups + P->adj_Rpol - 1) / P->adj_Rpol;
     }
+    while (P->spin_groups < P->ng64 && std::acos(P->h_rings[64 * P->spin_groups].z) < AKRA_POLE_THETA) ++P->spin_groups;
+    if (prec == AKRA_FP32 && nrhs > 1) P->spin_groups = P->ng64;  // the batched kernels run the spin form everywhere
+    P->next = P->nalm + (int64_t)EXT_L * (lmax + 1);
 
     // Legendre launch shapes
     P->syn_R = P->npairs >= 256 ? 2 : 1;
     P->syn_groups = (P->npairs + 64 * P->syn_R - 1) / (64 * P->syn_R);
-    const int caps[5][2] = {{1, 1}, {1, 2}, {1, 4}, {2, 4}, {4, 4}};
-    int ci = 4;
-    for (int i = 0; i < 5; ++i)
-        if (64 * caps[i][0] * caps[i][1] >= P->npairs) {
-            ci = i;
-            break;
-        }
-    P->adj_R = caps[ci][0];
-    P->adj_W = caps[ci][1];
-    P->adj_nrb = P->adj_nrb_polar + (P->ng64 - P->polar_groups + P->adj_R * P->adj_W - 1) / (P->adj_R * P->adj_W);
+    // pairs per lane of the adjoint: as many as leave two waves per SIMD (2048 waves), at most six
+    P->adj_R = (int)std::min<int64_t>(6, std::max<int64_t>(1, (int64_t)(P->ng64 - P->spin_groups) * (lmax + 1) / 2048));
+    P->adj_nrb = adj_nrb_of(*P);
     P->syn_V1 = P->syn_V;
     P->syn_R1 = P->syn_R;
     P->adj_R1 = P->adj_R;
@@ -602,13 +663,20 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         std::vector<Coef32> c32;
         std::vector<Coef32D> c32d;
         std::vector<Coef64S> c64s;
-        std::vector<Coef32S> c32s;
-        build_coef(lmax, c64, c32, c32d, c64s, c32s);
+        build_coef(lmax, c64, c32, c32d, c64s);
         AK_TRY(upload((void **)&P->d_coef64, c64.data(), c64.size() * sizeof(Coef64), *P));
         AK_TRY(upload((void **)&P->d_coef32, c32.data(), c32.size() * sizeof(Coef32), *P));
         AK_TRY(upload((void **)&P->d_coef64s, c64s.data(), c64s.size() * sizeof(Coef64S), *P));
-        AK_TRY(upload((void **)&P->d_coef32s, c32s.data(), c32s.size() * sizeof(Coef32S), *P));
         AK_TRY(upload((void **)&P->d_coef32d, c32d.data(), c32d.size() * sizeof(Coef32D), *P));
+    }
+    {
+        std::vector<double> sa, sc, sten;
+        std::vector<uint32_t> lm;
+        build_scalar(lmax, P->next, sa, sc, sten, lm);
+        AK_TRY(upload((void **)&P->d_sa, sa.data(), sa.size() * sizeof(double), *P));
+        AK_TRY(upload((void **)&P->d_sc, sc.data(), sc.size() * sizeof(double), *P));
+        AK_TRY(upload((void **)&P->d_sten, sten.data(), sten.size() * sizeof(double), *P));
+        AK_TRY(upload((void **)&P->d_lm, lm.data(), lm.size() * sizeof(uint32_t), *P));
     }
     {
         std::vector<double> s2, sm;
@@ -639,8 +707,10 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         AK_TRY(upload((void **)&P->d_gl_all, ids.data(), ids.size() * sizeof(int), *P));
         GroupSet &A = P->gs_all;
         A.list[GCLS_BOTH] = A.list_any = P->d_gl_all;
-        A.npol[GCLS_BOTH] = A.npol_any = P->polar_groups;
-        A.nmain[GCLS_BOTH] = A.nmain_any = P->ng64 - P->polar_groups;
+        A.npol[GCLS_BOTH] = P->spin_groups;
+        A.nmain[GCLS_BOTH] = P->ng64 - P->spin_groups;
+        A.npol_any = P->polar_groups;
+        A.nmain_any = P->ng64 - P->polar_groups;
         // until a weight set-up, the weighted sets are the full ones
         P->rs_live = P->rs_all;
         P->rs_cls[0] = P->rs_all;  // every group counts as two-sided
@@ -750,7 +820,7 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     AK_TRY(alloc(&P->d_FG, fg, *P));
     // the class lists of a weighted apply split the groups in up to three polar and three main parts,
     // each rounded up to whole blocks: at most LIVE_NRB_EXTRA blocks more than the unsplit layout
-    P->part_rb_cap = (size_t)std::max(P->adj_nrb, P->adj_nrb_polar + (P->npairs <= 1024 ? P->ng64 : (P->ng64 + 3) / 4)) +
+    P->part_rb_cap = (size_t)std::max(P->adj_nrb, (P->spin_groups + 1) / 2 + (P->npairs <= 1024 ? P->ng64 : (P->ng64 + 3) / 4)) +
                      LIVE_NRB_EXTRA;
     if (prec == AKRA_FP32 && nrhs > 1) {
         // batched adjoint: blocks of four groups (polar blocks apart), 8 right-hand sides of FP32 slabs
@@ -760,7 +830,7 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         P->part_rb_cap = std::max(P->part_rb_cap, (size_t)4 * P->nrb_b_cap);
         AK_TRY(alloc((void **)&P->d_wgstart_b, (size_t)P->nrb_b_cap * (lmax + 1) * sizeof(int), *P));
     }
-    AK_TRY(alloc(&P->d_part, P->part_rb_cap * P->nalm * 4 * sizeof(double), *P));
+    AK_TRY(alloc(&P->d_part, P->part_rb_cap * P->next * 4 * sizeof(double), *P));
     AK_TRY(alloc((void **)&P->d_wgstart, P->part_rb_cap * (lmax + 1) * sizeof(int), *P));
     compute_work(*P);
     // before any weight set-up every ring counts, in two-ring groups
@@ -768,18 +838,12 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     P->work_live[0] = P->work[1];
     P->work_live[2] = P->work[2];
     P->work_live[4] = P->work_b;
-    P->rec_stride = P->nalm + ALM_PAD;
-    AK_TRY(alloc(&P->d_rec, (size_t)nrhs * P->rec_stride * 64, *P));
-    if (prec == AKRA_FP32 && P->polar_groups > 0) {
-        AK_TRY(alloc((void **)&P->d_recu, (size_t)nrhs * P->rec_stride * sizeof(float4), *P));
-        if (hipMemset(P->d_recu, 0, (size_t)nrhs * P->rec_stride * sizeof(float4)) != hipSuccess) {
-            free_plan(P);
-            set_error("hipMemset failed");
-            return AKRA_ERR_HIP;
-        }
-    }
+    P->rec_stride = P->next + ALM_PAD;
+    const size_t rec_b = (size_t)nrhs * P->rec_stride * 5 * sizeof(double), recs_b = (size_t)nrhs * (P->nalm + ALM_PAD) * 64;
+    AK_TRY(alloc((void **)&P->d_rec, rec_b, *P));
+    if (P->spin_groups > 0) AK_TRY(alloc(&P->d_rec_spin, recs_b, *P));
     if (prec == AKRA_FP32 && nrhs > 1) AK_TRY(alloc((void **)&P->d_brec, (size_t)P->rec_stride * 8 * 4 * sizeof(float), *P));
-    if (hipMemset(P->d_rec, 0, (size_t)nrhs * P->rec_stride * 64) != hipSuccess) {
+    if (hipMemset(P->d_rec, 0, rec_b) != hipSuccess || (P->d_rec_spin && hipMemset(P->d_rec_spin, 0, recs_b) != hipSuccess)) {
         free_plan(P);
         set_error("hipMemset failed");
         return AKRA_ERR_HIP;
@@ -965,9 +1029,9 @@ static akra_status apply_H_timed(Plan &P, bool fp32, const double *kern_dev, dou
                                  const double *xB, double *yE, double *yB, int rhs, double *dot_red = nullptr)
 {
     stage_mark(P, 0, true);
-    launch_prologue(P, fp32, xE, xB, kern_dev, 1);
+    const GroupSet &G = P.skip_rings ? P.gs_live : P.gs_all;
+    launch_prologue(P, xE, xB, kern_dev, 1, G.npol[GCLS_BOTH] + G.npol[GCLS_NORTH] + G.npol[GCLS_SOUTH] > 0);
     stage_mark(P, 0, false);
-    const GroupSet &G = P.gs_live;
     const bool two = G.npol[GCLS_BOTH] + G.nmain[GCLS_BOTH] > 0,
                one = G.npol[GCLS_NORTH] + G.nmain[GCLS_NORTH] + G.npol[GCLS_SOUTH] + G.nmain[GCLS_SOUTH] > 0;
     if (!P.timing && P.skip_rings && P.side_stream && two && one) {
@@ -1372,7 +1436,7 @@ akra_status akra_synth2(akra_plan plan, const double *almE, const double *almB, 
     if (fp32 && P.nrhs > 1) {
         launch_synth_batched(P, almE, almB, P.nalm, nullptr, false);
     } else {
-        launch_prologue(P, fp32, almE, almB, nullptr, P.nrhs);
+        launch_prologue(P, almE, almB, nullptr, P.nrhs, P.spin_groups > 0);
         launch_leg_synth(P, fp32, P.nrhs, false);
     }
     launch_ring(P, fp32, 0, nullptr, nullptr, g1, g2, nullptr, P.nrhs, false);
@@ -1930,11 +1994,11 @@ akra_status akra_cg_solve_vjp(akra_plan plan, const double *g1, const double *g2
         launch_dot(P, P.d_x + 2 * na, xB + off, sc + 1, na);
         k_sum2_scaled<<<1, 1, 0, P.stream>>>(sc + 2, sc, sc + 1, ms[r] > 0 ? o.lambda / ms[r] : 0.0);
         // q = Y K u into the gradient maps
-        launch_prologue(P, false, P.d_x, P.d_x + 2 * na, kd, 1);
+        launch_prologue(P, P.d_x, P.d_x + 2 * na, kd, 1, P.spin_groups > 0);
         launch_leg_synth(P, false, 1, false);
         launch_ring(P, false, 0, nullptr, nullptr, dg1 + mo, dg2 + mo, nullptr, 1, false);
         // Y K x, consumed per pixel together with q, g, W and the mask
-        launch_prologue(P, false, xE + off, xB + off, kd, 1);
+        launch_prologue(P, xE + off, xB + off, kd, 1, P.spin_groups > 0);
         launch_leg_synth(P, false, 1, false);
         launch_ring_grad(P, g1 + mo, g2 + mo, dg1 + mo, dg2 + mo, P.d_W + mo, dninv + mo, mask, sc + 2);
         st = check_launch("solve_vjp");
@@ -2022,7 +2086,7 @@ akra_status akra_cg_state(akra_plan plan, double *rel_resid, int *iters, double 
 static int nrb_bound(const Plan &P, int gpw0, int gpw1)
 {
     const int gpw = std::min(gpw0, gpw1);
-    return P.adj_nrb_polar + (P.ng64 - P.polar_groups + gpw - 1) / gpw + LIVE_NRB_EXTRA;
+    return (P.spin_groups + 1) / 2 + (P.ng64 - P.spin_groups + gpw - 1) / gpw + LIVE_NRB_EXTRA;
 }
 
 static akra_status set_tuning_class(Plan &P, int one_sided, int syn_variant, int syn_rings, int adj_rings,
@@ -2052,7 +2116,7 @@ static akra_status set_tuning_class(Plan &P, int one_sided, int syn_variant, int
         P.adj_R = adj_rings;
         P.adj_W = adj_waves;
         P.adj_L = adj_chunk;
-        P.adj_nrb = P.adj_nrb_polar + (P.ng64 - P.polar_groups + gpw - 1) / gpw;
+        P.adj_nrb = adj_nrb_of(P);
     }
     compute_work(P);
     if (P.live_gen) compute_work_live(P);  // the staged lists of the last weight set-up
