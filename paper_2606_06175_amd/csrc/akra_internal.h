@@ -25,6 +25,8 @@ constexpr int ALM_PAD = 64;
 // the scalar functions of the transforms run to degree lmax + EXT_L (the stencil of sin^2 theta times a
 // spin-2 function reaches two degrees further)
 constexpr int EXT_L = 2;
+// right-hand sides per group of the batched kernels
+constexpr int NBR = 8;
 // unmasked-pixel compaction: threads per block, contiguous pixels per thread, pixels per tile
 constexpr int CMP_T = 256, CMP_PER = 16, CMP_TILE = CMP_T * CMP_PER;
 // spectra: degrees per block, orders per partial sum, pairs per launch
@@ -48,9 +50,6 @@ template <> struct Scale<float> {
 // stored at the alm index i(l, m) (entries at l = lmax are zero).
 struct alignas(32) Coef64 {
     double a, b, g, pad;
-};
-struct alignas(16) Coef32 {
-    float a, b, g, pad;
 };
 // Scaled form of the same recurrence, run by the spin form of the Legendre kernels.  With
 // lambda_l = c_l mu_l, where c_{l0} = c_{l0+1} = 1 and c_{l+1} = g_l c_{l-1},
@@ -115,8 +114,7 @@ struct RingInfo {
 enum { GCLS_BOTH = 0, GCLS_NORTH = 1, GCLS_SOUTH = 2, GCLS_N = 3 };
 // 64-pair groups of one apply: per class an ascending list whose first npol entries are spin-form
 // groups (nearest the poles), then nmain others; list_any holds every listed group (the union of the
-// classes, for the batched kernels, which have no one-ring form), its first npol_any those the batched
-// kernels run in the difference form.
+// classes, for the batched kernels, which have no one-ring form), spin-form groups first.
 struct GroupSet {
     const int *list[GCLS_N] = {nullptr, nullptr, nullptr};
     int npol[GCLS_N] = {0, 0, 0}, nmain[GCLS_N] = {0, 0, 0};
@@ -149,7 +147,6 @@ struct Plan {
     RingInfo *d_rings = nullptr;
     double *d_pair_z = nullptr;
     Coef64 *d_coef64 = nullptr;  // plain form: entry states (plan build)
-    Coef32 *d_coef32 = nullptr;  // plain form: batched matrix-core synthesis
     Coef64S *d_coef64s = nullptr;  // scaled form of the spin kernels
     Coef32D *d_coef32d = nullptr;
     int64_t next = 0;              // (l, m) entries with l up to lmax + EXT_L: ext_base(m) + l
@@ -198,7 +195,8 @@ struct Plan {
     int n_live_rings = 0;            // rings that carry weight in the current weights
     int nrb_cur = 1;                 // ring blocks the last single-right-hand-side adjoint wrote,
     int nrbs_cur = 0;                // the first nrbs_cur of them in the spin form
-    int nrb_b_cur = 1;               // ring blocks the last batched adjoint wrote
+    int nrb_b_cur = 1;               // ring blocks the last batched adjoint wrote,
+    int nrbs_b_cur = 0;              // the first nrbs_b_cur of them in the spin form
     int64_t work_live[5] = {0, 0, 0, 0, 0};  // evaluated triples with the current weights: synthesis of
                                              // two-ring, one-ring groups, adjoint of two-ring, one-ring,
                                              // batched kernels per right-hand side
@@ -211,8 +209,6 @@ struct Plan {
     int syn_R1 = 1, syn_V1 = 1, adj_R1 = 1, adj_W1 = 1, adj_L1 = 8;
     size_t part_rb_cap = 1;  // ring blocks the partial-sum buffer holds
     int spin_groups = 0;  // the first spin_groups 64-pair groups run the spin form
-    // batched FP32 kernels: the groups nearest the poles run in the difference form
-    int polar_groups = 0;
     // batched matrix-core kernels: waves (64-pair groups) per workgroup of the synthesis and the
     // adjoint; nrb_b adjoint ring blocks of bat_AW groups (the buffers hold those of bat_AW = 2)
     int bat_SW = 4, bat_AW = 4, nrb_b_cap = 0;
@@ -222,7 +218,8 @@ struct Plan {
     void *d_part = nullptr;     // [nrb][next][4] adjoint partial sums (spin blocks fill [nalm][4] of theirs)
     double *d_rec = nullptr;    // [nrhs][next + ALM_PAD][5] synthesis records of the scalar form
     void *d_rec_spin = nullptr; // [nrhs][nalm + ALM_PAD] synthesis records of the spin form (64 B)
-    float *d_brec = nullptr;    // FP32 plans with nrhs > 1: [nalm + ALM_PAD][8 rhs][4] batched records
+    float *d_brec = nullptr;    // FP32 plans with nrhs > 1: [next + ALM_PAD][8 rhs][4] batched records
+    float *d_brec_spin = nullptr;  // [nalm + ALM_PAD][8 rhs][4] those of the spin form
     int nrb_b = 0;              // FP32 plans with nrhs > 1: ring blocks of the batched adjoint
     int *d_wgstart_b = nullptr; // [m][nrb_b] first degree each batched adjoint block wrote
     int64_t rec_stride = 0;     // scalar records per right-hand side

@@ -91,12 +91,9 @@ __global__ __launch_bounds__(256) void k_entry(const double *__restrict__ seed2,
 // ================================================================================================
 // prologue / epilogue / weights
 // ================================================================================================
-// One thread per entry (l, m), l <= lmax + 2, of the scalar form's records: a' and c_l times
-//   q_l = w_2(l-2) E_{l-2} + w_0(l) E_l + w_-2(l+2) E_{l+2} + i (x_1(l-1) B_{l-1} + x_-1(l+1) B_{l+1}),
-//   u_l = w_2(l-2) B_{l-2} + w_0(l) B_l + w_-2(l+2) B_{l+2} - i (x_1(l-1) E_{l-1} + x_-1(l+1) E_{l+1})
-// of E, B = K_l (x_E, x_B) (the stencil is zero at degrees below 2; Im(a_l0) dropped), in FP64.  Bound
-// by HBM: x_E, x_B and the stencil read once (neighbours come from the caches), 40 bytes written.  With
-// rsp also the spin form's record.
+// One thread per entry (l, m), l <= lmax + 2, of the scalar form's records: a' and c_l times the stencil's
+// coefficients (stencil_in), in FP64.  Bound by HBM: x_E, x_B and the stencil read once (neighbours come
+// from the caches), 40 bytes written.  With rsp also the spin form's record.
 __global__ __launch_bounds__(256) void k_prologue(const double2 *__restrict__ xE, const double2 *__restrict__ xB,
                                                   const double *__restrict__ kern, const uint32_t *__restrict__ lm,
                                                   const double *__restrict__ sten, const double *__restrict__ sa,
@@ -110,51 +107,17 @@ __global__ __launch_bounds__(256) void k_prologue(const double2 *__restrict__ xE
     const int l = (int)(lm[e] & 0xffff), m = (int)(lm[e] >> 16);
     const int64_t i = e - (int64_t)EXT_L * m, ns = nalm + ALM_PAD;
     const double2 *pE = xE + rhs * nalm, *pB = xB + rhs * nalm;
-    double q0 = 0, q1 = 0, u0 = 0, u1 = 0;
-    auto at = [&](int d, double2 &E, double2 &B) {
-        const double K = kern ? kern[l + d] : 1.0;
-        E = pE[i + d];
-        B = pB[i + d];
-        E.x *= K;
-        B.x *= K;
-        E.y = m ? K * E.y : 0.0;
-        B.y = m ? K * B.y : 0.0;
-    };
-    auto even = [&](int d, int row) {
-        if (l + d < m || l + d > lmax) return;
-        const double w = sten[row * ns + i + d];
-        double2 E, B;
-        at(d, E, B);
-        q0 = fma(w, E.x, q0);
-        q1 = fma(w, E.y, q1);
-        u0 = fma(w, B.x, u0);
-        u1 = fma(w, B.y, u1);
-    };
-    auto odd = [&](int d, int row) {
-        if (l + d < m || l + d > lmax) return;
-        const double x = sten[row * ns + i + d];
-        double2 E, B;
-        at(d, E, B);
-        q0 = fma(-x, B.y, q0);
-        q1 = fma(x, B.x, q1);
-        u0 = fma(x, E.y, u0);
-        u1 = fma(-x, E.x, u1);
-    };
-    even(-2, ST_W2);
-    odd(-1, ST_X1);
-    even(0, ST_W0);
-    odd(1, ST_XM1);
-    even(2, ST_WM2);
+    double q[4];
+    stencil_in(pE, pB, kern, sten, l, m, lmax, nalm, i, q);
     const double s = sc[e];
     double *r = rec + (rhs * rec_stride + e) * 5;
     r[0] = sa[e];
-    r[1] = s * q0;
-    r[2] = s * q1;
-    r[3] = s * u0;
-    r[4] = s * u1;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) r[1 + t] = s * q[t];
     if (rsp && l <= lmax) {
-        double2 E, B;
-        at(0, E, B);
+        const double K = kern ? kern[l] : 1.0;
+        const double2 e2 = pE[i], b2 = pB[i];
+        const double2 E = make_double2(K * e2.x, m ? K * e2.y : 0.0), B = make_double2(K * b2.x, m ? K * b2.y : 0.0);
         const Coef64S c = cs64[i];
         SpinRec o;
         o.a = c.a;
@@ -1534,395 +1497,6 @@ __global__ void k_scalar_div(double *out, const double *num, const double *den) 
 // ================================================================================================
 bool pow2(int n) { return n > 0 && (n & (n - 1)) == 0; }
 
-// ================================================================================================
-// Batched synthesis (FP32 plans with several right-hand sides): for one m, a group of 64 ring pairs
-// (one per lane) and NBR = 8 right-hand sides, the sums over l of lambda(l, pair) a(l, rhs, c) are a
-// matrix product [pairs x l] x [l x (rhs, c)] with the lambda generated on the fly, accumulated on
-// the matrix cores (v_mfma_f32_32x32x2_f32: D[32 x 32] += A[32 x 2] B[2 x 32]), per half of the pairs.
-//   A[i][k]  lambda of pair i (of the half) at degree l + 2k (even offsets from the step l of four) or
-//            l + 1 + 2k (odd), held by lane i + 32k.  Every lane runs the recurrence of its own pair;
-//            one v_permlane32_swap per pair of degrees (l, l+2) moves the values into that layout:
-//            [low lanes at l | low lanes at l+2] for the first half, [high at l | high at l+2] for
-//            the second.
-//   B[k][j]  record value j = 4 rhs + c (c = Re/Im of aE, Re/Im of aB) at the same degree
-//   D        per half four accumulators: spin +2 / -2 times even / odd offsets from the start degree
-// Lane l, register r of D holds pair i = 8 (r/4) + 4 (l/32) + r%4 of the half and column j = l%32.
-// ================================================================================================
-typedef float v16f __attribute__((ext_vector_type(16)));
-constexpr int NBR = 8;  // right-hand sides per batched group
-
-// per (l, m): the NBR x 4 kernel-scaled alm values of one group (Im(a_l0) zeroed), zero past nrhs
-__global__ void k_prologue_b(const double *__restrict__ xE, const double *__restrict__ xB, int64_t rstride,
-                             const double *__restrict__ kern, const int *__restrict__ lof, int lmax, int64_t nalm,
-                             int nrhs, int q, float *__restrict__ brec)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // (alm, rhs-in-group)
-    if (t >= nalm * NBR) return;
-    const int64_t i = t / NBR;
-    const int rr = (int)(t - i * NBR), rhs = q * NBR + rr;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (rhs < nrhs) {
-        const int64_t o = (int64_t)rhs * rstride + i;  // rstride: complex elements between right-hand sides
-        const double K = kern ? kern[lof[i]] : 1.0;
-        const bool m0 = i <= lmax;
-        v.x = (float)(K * xE[2 * o]);
-        v.y = m0 ? 0.f : (float)(K * xE[2 * o + 1]);
-        v.z = (float)(K * xB[2 * o]);
-        v.w = m0 ? 0.f : (float)(K * xB[2 * o + 1]);
-    }
-    reinterpret_cast<float4 *>(brec)[t] = v;
-}
-
-// quad sum over the four lanes 4 rhs + (0..3) that hold c = 0..3 of one right-hand side
-__device__ __forceinline__ float quad_sum(float v)
-{
-    v += __shfl_xor(v, 1, 64);
-    v += __shfl_xor(v, 2, 64);
-    return v;
-}
-
-// exchange the upper half of a's lanes with the lower half of b's: a = [a_lo | b_lo], b = [a_hi | b_hi]
-__device__ __forceinline__ void swap_halves(float &a, float &b)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(a), __float_as_int(b), false, false);
-    a = __int_as_float(r[0]);
-    b = __int_as_float(r[1]);
-}
-
-// SW waves (64-pair groups) per workgroup, a launch shape of the autotuner
-template <int F, int SW>
-__global__ __launch_bounds__(64 * SW) __attribute__((amdgpu_waves_per_eu(2))) void k_leg_synth_b(const float *__restrict__ brec,
-                                                     const typename CoefB<F>::type *__restrict__ coef,
-                                                     float2 *__restrict__ FG, int64_t fg_stride,
-                                                     const Ent64 *__restrict__ ent, const int *__restrict__ entk,
-                                                     const int *__restrict__ entl, int ng64,
-                                                     const double *__restrict__ pair_z, int lmax, int npairs,
-                                                     int nrings, int nrhs, int q, const int *__restrict__ glist,
-                                                     int ngl, int nbm)
-{
-    const int lane = threadIdx.x & 63, h = lane >> 5, i = lane & 31;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    int m, blk;
-    xcd_map((int)blockIdx.x, nbm, m, blk);
-    const int wi = blk * SW + wave;  // list entry of the wave
-    if (m > lmax || wi >= ngl) return;
-    const int w = uniform_ptr(glist)[wi];  // 64-pair group: pairs 64 w .. 64 w + 63
-    const int l0 = m > 2 ? m : 2;
-    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
-    const int p = 64 * w + lane;
-    // a group that never enters still writes its (zero) F
-    const int ls = __builtin_amdgcn_readfirstlane(uniform_ptr(entl + (int64_t)m * ng64)[w]);
-
-    typename PosB<F>::type x;
-    float c2 = 0.f, p2 = 0.f, cm = 0.f, pm = 0.f;
-    int k = 0;
-    setpos(x, 0.0);
-    if (p < npairs && ls <= lmax) {
-        setpos(x, pair_z[p]);
-        load_entry_b<F>(ent, entk, (int64_t)m * npairs + p, c2, p2, cm, pm, k);
-    }
-    v16f D2e[2], D2o[2], Dme[2], Dmo[2];
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) D2e[s2][r] = D2o[s2][r] = Dme[s2][r] = Dmo[s2][r] = 0.f;
-    bool ramp = wave_any(k < 0);
-    using C = typename CoefB<F>::type;
-    const_as<C> *cp = uniform_ptr(coef + base);
-    const float *bl = brec + base * (NBR * 4) + i;  // column i of the group's records
-    // four degrees from l: records and recurrence values, then the eight products.  RAMP: some lane is
-    // still in the scaled range (its values count as zero until its exponent reaches zero, and the
-    // exponents are checked once per four steps); once no lane is, none returns to it, and the loop
-    // without the selects and the checks takes over.
-    auto four = [&](int l, auto ramp_tag) {
-        constexpr bool RAMP = decltype(ramp_tag)::value;
-        // B rows l + 2h (even offsets) and l + 1 + 2h (odd), zero past lmax
-        const int re = l + 2 * h, ro = re + 1;
-        const float be = re <= lmax ? bl[(int64_t)re * (NBR * 4)] : 0.f;
-        const float bo = ro <= lmax ? bl[(int64_t)ro * (NBR * 4)] : 0.f;
-        float v2[4], vm[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const bool live = !RAMP || k == 0;
-            v2[t] = live ? c2 : 0.f;
-            vm[t] = live ? cm : 0.f;
-            rstep(ld_coef(cp + l + t), x, c2, p2, cm, pm);
-        }
-        // degrees (l, l+2) and (l+1, l+3) of both halves of the pairs
-        swap_halves(v2[0], v2[2]);
-        swap_halves(v2[1], v2[3]);
-        swap_halves(vm[0], vm[2]);
-        swap_halves(vm[1], vm[3]);
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-            D2e[s2] = __builtin_amdgcn_mfma_f32_32x32x2f32(v2[2 * s2], be, D2e[s2], 0, 0, 0);
-            D2o[s2] = __builtin_amdgcn_mfma_f32_32x32x2f32(v2[2 * s2 + 1], bo, D2o[s2], 0, 0, 0);
-            Dme[s2] = __builtin_amdgcn_mfma_f32_32x32x2f32(vm[2 * s2], be, Dme[s2], 0, 0, 0);
-            Dmo[s2] = __builtin_amdgcn_mfma_f32_32x32x2f32(vm[2 * s2 + 1], bo, Dmo[s2], 0, 0, 0);
-        }
-        if constexpr (RAMP) {
-            // once per four steps (the growth over four steps stays far from overflow)
-            if (k < 0 && fmaxf(fabsf(c2), fabsf(cm)) > scale_hi<float>()) {
-                const float d = scale_down<float>();
-                c2 *= d;
-                p2 *= d;
-                cm *= d;
-                pm *= d;
-                k += 1;
-            }
-            ramp = wave_any(k < 0);
-        }
-    };
-    int l = ls;
-    for (; l <= lmax && ramp; l += 4) four(l, std::true_type{});
-    for (; l <= lmax; l += 4) four(l, std::false_type{});
-    // F of the north and south ring of every (pair, rhs): quad sums over c, written by lane c = 0
-    const bool odd0 = ((l0 + m) & 1) != 0;  // entries are l0 + 8 q: D2e holds degrees of parity l0 + m
-    const int c = i & 3, rl = i >> 2, rhs = q * NBR + rl;
-    const float s0r = c == 0 ? -1.f : (c == 3 ? 1.f : 0.f), s0i = (c == 1 || c == 2) ? -1.f : 0.f;
-    const float s1r = (c == 0 || c == 3) ? -1.f : 0.f, s1i = c == 2 ? -1.f : (c == 1 ? 1.f : 0.f);
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int pi = 64 * w + 32 * s2 + 8 * (r >> 2) + 4 * h + (r & 3);
-            const float E2 = odd0 ? D2o[s2][r] : D2e[s2][r], O2 = odd0 ? D2e[s2][r] : D2o[s2][r];
-            const float Em = odd0 ? Dmo[s2][r] : Dme[s2][r], Om = odd0 ? Dme[s2][r] : Dmo[s2][r];
-            // north: S2 = E2 + O2, Sm = Em + Om;  south: S2 = Em - Om, Sm = E2 - O2
-            const float S2n = E2 + O2, Smn = Em + Om, S2s = Em - Om, Sms = E2 - O2;
-            // f0 = -(S2[0] - S2[3], S2[1] + S2[2]),  f1 = -(Sm[0] + Sm[3], Sm[2] - Sm[1])
-            const float fn0r = quad_sum(s0r * S2n), fn0i = quad_sum(s0i * S2n);
-            const float fn1r = quad_sum(s1r * Smn), fn1i = quad_sum(s1i * Smn);
-            const float fs0r = quad_sum(s0r * S2s), fs0i = quad_sum(s0i * S2s);
-            const float fs1r = quad_sum(s1r * Sms), fs1i = quad_sum(s1i * Sms);
-            if (c == 0 && rhs < nrhs && pi < npairs) {
-                float2 *Fb = FG + (int64_t)rhs * fg_stride;
-                const int rn = pi, rs = nrings - 1 - pi;
-                float2 *f = Fb + ((int64_t)rn * (lmax + 1) + m) * 2;
-                f[0] = make_float2(fn0r, fn0i);
-                f[1] = make_float2(fn1r, fn1i);
-                if (rs != rn) {
-                    float2 *g = Fb + ((int64_t)rs * (lmax + 1) + m) * 2;
-                    g[0] = make_float2(fs0r, fs0i);
-                    g[1] = make_float2(fs1r, fs1i);
-                }
-            }
-        }
-    }
-}
-
-// ================================================================================================
-// Batched FP32 Legendre adjoint on the matrix cores.  For one m, a block of AW 64-pair groups (one per
-// wave) and the NBR right-hand sides of group q, the partial sums over the block's ring pairs
-//   out_rhs[l][c],  c = 0..3 as in k_leg_adj (2h_lm and -2h_lm, Re and Im).
-// Per chunk of ABL = 32 degrees each wave writes the recurrence values of its pairs to LDS (one row
-// per degree), then v_mfma_f32_32x32x2_f32 contracts over the pairs, two per instruction:
-//   D+ = Lambda+ [GN.x, GN.y, HS.x, HS.y],   D- = Lambda- [HN.x, HN.y, GS.x, GS.y]
-// (columns 4 rhs + c, G of the north ring GN, HN = conj of its second component, S the south ring),
-// and the south terms take the sign s = (-1)^(l+m) of their row:
-//   out_0,1 = D+[c] + s D-[c+2],   out_2,3 = D-[c-2] + s D+[c].
-// G is loaded once per wave into registers (it does not depend on l).  The waves of the block are
-// summed in LDS and one slab per (right-hand side of the group, block) is written,
-// [rhs - NBR q][nrb][nalm][4], rows from the chunk holding the block's first entry degree (recorded in
-// wgstart) to lmax.
-// ================================================================================================
-// AW waves (64-pair groups) per workgroup is a launch shape of the autotuner (2, 4 or 8)
-constexpr int ABL = 32;  // degrees per chunk: the rows of the MFMA
-constexpr int ABS = 33;  // LDS stride of one pair's 32 rows (bank-conflict-free writes)
-
-template <int F, int AW>
-__global__ __launch_bounds__(64 * AW) __attribute__((amdgpu_waves_per_eu(2))) void k_leg_adj_b(const float2 *__restrict__ FG, int64_t fg_stride,
-                                                        const typename CoefB<F>::type *__restrict__ coef,
-                                                        const Ent64 *__restrict__ ent, const int *__restrict__ entk,
-                                                        const int *__restrict__ entl, int ng64,
-                                                        const double *__restrict__ pair_z, float *__restrict__ part,
-                                                        int *__restrict__ wgstart, int64_t nalm, int lmax, int npairs,
-                                                        int nrings, int nrhs, int q, const int *__restrict__ glist,
-                                                        int ngl, const uint8_t *__restrict__ live, int rb0,
-                                                        int nrbl, int nrb, int64_t slab)
-{
-    __shared__ float lam[AW][2][64 * ABS];  // per wave: lambda+ and lambda- of its 64 pairs x 32 rows
-    __shared__ float red[8 * AW * 64];      // the cross-wave sum, eight output registers at a time
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    int m, rbl;
-    xcd_map((int)blockIdx.x, nrbl, m, rbl);
-    if (m > lmax) return;
-    const int rb = rb0 + rbl;
-    const int lb = rbl * AW;  // first list entry of the block
-    const int l0 = m > 2 ? m : 2;
-    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
-    const_as<int> *el = uniform_ptr(entl + (int64_t)m * ng64);
-    const_as<int> *gl = uniform_ptr(glist);
-    int ls = ENT_SKIP;
-    for (int li = lb; li < lb + AW && li < ngl; ++li) ls = el[gl[li]] < ls ? el[gl[li]] : ls;
-    if (threadIdx.x == 0) wgstart[(int64_t)m * nrb + rb] = ls;
-    if (ls > lmax) return;
-    const int g = lb + wave < ngl ? gl[lb + wave] : -1;  // this wave's group
-    const int e = g >= 0 ? el[g] : ENT_SKIP;             // and its entry degree
-    const int p = g * 64 + lane;
-    const bool valid = g >= 0 && p < npairs;
-
-    // B operands: lane l holds, for pair-pair kk, pair 64 g + 2 kk + l / 32 and column j = l % 32
-    const int j = lane & 31, c = j & 3, rhs = q * NBR + (j >> 2);
-    float Bp[32], Bm[32];
-#pragma unroll
-    for (int kk = 0; kk < 32; ++kk) {
-        Bp[kk] = Bm[kk] = 0.f;
-        const int pk = g * 64 + 2 * kk + (lane >> 5);
-        if (e > lmax || g < 0 || pk >= npairs || rhs >= nrhs) continue;
-        const float2 *Fb = FG + rhs * fg_stride;
-        if (c < 2) {
-            if (live && !live[pk]) continue;  // a ring without weight has G = 0
-            const float2 *fn = Fb + ((int64_t)pk * (lmax + 1) + m) * 2;
-            const float2 gn = fn[0], hn = fn[1];  // HN = conj(hn)
-            Bp[kk] = c ? gn.y : gn.x;
-            Bm[kk] = c ? -hn.y : hn.x;
-        } else {
-            const int rs = nrings - 1 - pk;
-            if (rs != pk && (!live || live[rs])) {
-                const float2 *fs = Fb + ((int64_t)rs * (lmax + 1) + m) * 2;
-                const float2 gs = fs[0], hs = fs[1];  // HS = conj(hs)
-                Bp[kk] = (c & 1) ? -hs.y : hs.x;
-                Bm[kk] = (c & 1) ? gs.y : gs.x;
-            }
-        }
-    }
-
-    typename PosB<F>::type x;
-    setpos(x, valid ? pair_z[p] : 0.0);
-    float c2 = 0.f, p2 = 0.f, cm = 0.f, pm = 0.f;
-    int k = 0;
-    bool ramp = false;
-    using C = typename CoefB<F>::type;
-    const_as<C> *cp = uniform_ptr(coef + base);
-    float *lp = &lam[wave][0][lane * ABS], *lmn = &lam[wave][1][lane * ABS];
-    const float *ap = &lam[wave][0][(lane >> 5) * ABS + (lane & 31)], *am = &lam[wave][1][(lane >> 5) * ABS + (lane & 31)];
-    // the wave's recurrence covers the chunk starting at lx (zero before the wave's entry, for lanes
-    // still in the scaled range and past lmax)
-    auto is_active = [&](int lx) { return lx <= lmax && e <= lx + ABL - 1 && e <= lmax; };
-    // rows t8 .. t8 + 7 of the chunk at lx into the wave's LDS rows (entry degrees are l0 + 8 q and
-    // chunks start at l0 + 32 j, so an entry falls on a block of 8)
-    auto rows8 = [&](int lx, int t8, auto &&after) {
-        const int lb = lx + t8;
-        if (lb == e) {
-            if (valid) load_entry_b<F>(ent, entk, (int64_t)m * npairs + p, c2, p2, cm, pm, k);
-            ramp = wave_any(k < 0);
-        }
-        if (lb < e || lb > lmax) {
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                lp[t8 + t] = lmn[t8 + t] = 0.f;
-                after(t);
-            }
-            return;
-        }
-        C cc[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) cc[t] = ld_coef(cp + lb + t);  // padded past lmax
-        if (!ramp && lb + 7 <= lmax) {
-            // every lane out of the scaled range and every row in range: no selects, no checks
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                lp[t8 + t] = c2;
-                lmn[t8 + t] = cm;
-                rstep(cc[t], x, c2, p2, cm, pm);
-                after(t);
-            }
-            return;
-        }
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const bool live = k == 0 && lb + t <= lmax;
-            lp[t8 + t] = live ? c2 : 0.f;
-            lmn[t8 + t] = live ? cm : 0.f;
-            rstep(cc[t], x, c2, p2, cm, pm);
-            after(t);
-            if (ramp && (t & 3) == 3) {
-                // every four steps (the growth over four steps stays far from overflow)
-                if (k < 0 && fmaxf(fabsf(c2), fabsf(cm)) > scale_hi<float>()) {
-                    const float d = scale_down<float>();
-                    c2 *= d;
-                    p2 *= d;
-                    cm *= d;
-                    pm *= d;
-                    k += 1;
-                }
-                ramp = wave_any(k < 0);
-            }
-        }
-    };
-    // Software pipeline over chunks: the A operands of chunk lc are read from LDS into registers, then
-    // the recurrence writes the rows of the next chunk into the same LDS rows while the matrix cores
-    // contract chunk lc (eight rows, then the sixteen products of eight pair-pairs).  A wave reads and
-    // writes only its own rows, and its LDS accesses run in program order, so the reads return the
-    // rows of chunk lc.
-    const int lstart = l0 + ((ls - l0) / ABL) * ABL;
-    if (is_active(lstart)) {
-#pragma unroll
-        for (int t8 = 0; t8 < ABL; t8 += 8) rows8(lstart, t8, [](int) {});
-    }
-    for (int lc = lstart; lc <= lmax; lc += ABL) {
-        const bool act = is_active(lc), actn = is_active(lc + ABL);
-        wg_lds_sync<1>();
-        float a[32], b[32];
-        if (act) {
-#pragma unroll
-            for (int kk = 0; kk < 32; ++kk) {
-                a[kk] = ap[2 * kk * ABS];
-                b[kk] = am[2 * kk * ABS];
-            }
-        }
-        wg_lds_sync<1>();
-        v16f Dp, Dm;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) Dp[r] = Dm[r] = 0.f;
-        // the products of pair-pair kk follow row kk % 8 of block kk / 8 of the next chunk
-        auto mm = [&](int kk) {
-            Dp = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kk], Bp[kk], Dp, 0, 0, 0);
-            Dm = __builtin_amdgcn_mfma_f32_32x32x2f32(b[kk], Bm[kk], Dm, 0, 0, 0);
-        };
-        if (act && actn) {
-#pragma unroll
-            for (int t8 = 0; t8 < ABL; t8 += 8) rows8(lc + ABL, t8, [&](int t) { mm(t8 + t); });
-        } else if (act) {
-#pragma unroll
-            for (int kk = 0; kk < 32; ++kk) mm(kk);
-        } else if (actn) {
-#pragma unroll
-            for (int t8 = 0; t8 < ABL; t8 += 8) rows8(lc + ABL, t8, [](int) {});
-        }
-        // D row of register r in lane l: 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
-        float o[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int i = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            const float s = ((lc + i + m) & 1) ? -1.f : 1.f;
-            const float t2 = dpp_mov<0x4E>(Dm[r]);  // D- of column j ^ 2
-            o[r] = c < 2 ? fmaf(s, t2, Dp[r]) : fmaf(s, Dp[r], t2);
-        }
-        // sum over the block's waves in LDS, eight registers at a time
-#pragma unroll
-        for (int h = 0; h < 16; h += 8) {
-            __syncthreads();
-#pragma unroll
-            for (int r8 = 0; r8 < 8; ++r8) red[(wave * 8 + r8) * 64 + lane] = o[h + r8];
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < 8 / AW; ++u) {
-                const int r = h + wave * (8 / AW) + u;  // this thread's register index, lane as it was
-                float sum = 0.f;
-#pragma unroll
-                for (int w = 0; w < AW; ++w) sum += red[(w * 8 + r - h) * 64 + lane];
-                const int i = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), l = lc + i;
-                if (l <= lmax && rhs < nrhs)
-                    part[(((int64_t)(j >> 2) * nrb + rb) * slab + base + l) * 4 + c] = sum;
-            }
-        }
-    }
-}
-
-
 void launch_prologue(Plan &P, const double *xE, const double *xB, const double *kern, int nrhs, bool spin)
 {
     dim3 g((unsigned)cdiv(P.next, 256), nrhs);
@@ -1931,88 +1505,12 @@ void launch_prologue(Plan &P, const double *xE, const double *xB, const double *
                                         spin ? (SpinRec *)P.d_rec_spin : nullptr);
 }
 
-// the near-polar groups list[0 .. npol) in the difference form and list[npol .. npol + nmain) in the
-// plain form, SW groups per workgroup
-template <int SW>
-static void synth_b_launch(Plan &P, int q, int64_t fg_stride, int64_t lblocks, const int *list, int npol, int nmain)
-{
-    if (npol > 0) {
-        const int nbm = (int)cdiv(npol, SW);
-        k_leg_synth_b<1, SW><<<(unsigned)(8 * nbm * lblocks), 64 * SW, 0, P.stream>>>(
-            P.d_brec, P.d_coef32d, (float2 *)P.d_FG, fg_stride, P.d_ent, P.d_entk, P.d_entl, P.ng64, P.d_pair_z,
-            P.lmax, P.npairs, P.nrings, P.nrhs, q, list, npol, nbm);
-    }
-    if (nmain > 0) {
-        const int nbm = (int)cdiv(nmain, SW);
-        k_leg_synth_b<0, SW><<<(unsigned)(8 * nbm * lblocks), 64 * SW, 0, P.stream>>>(
-            P.d_brec, P.d_coef32, (float2 *)P.d_FG, fg_stride, P.d_ent, P.d_entk, P.d_entl, P.ng64, P.d_pair_z,
-            P.lmax, P.npairs, P.nrings, P.nrhs, q, list + npol, nmain, nbm);
-    }
-}
-
-// ring blocks of AW groups: the near-polar groups first (difference form), then the others
-template <int AW>
-static void adj_b_launch(Plan &P, int q, int64_t fg_stride, int64_t lblocks, const int *list, int npol, int nmain,
-                         const uint8_t *live, int nrb)
-{
-    const int nbp = (int)cdiv(npol, AW), nbn = (int)cdiv(nmain, AW);
-    if (nbp > 0)
-        k_leg_adj_b<1, AW><<<(unsigned)(8 * nbp * lblocks), 64 * AW, 0, P.stream>>>(
-            (const float2 *)P.d_FG, fg_stride, P.d_coef32d, P.d_ent, P.d_entk, P.d_entl, P.ng64, P.d_pair_z,
-            (float *)P.d_part, P.d_wgstart_b, P.nalm, P.lmax, P.npairs, P.nrings, P.nrhs, q, list, npol, live, 0, nbp,
-            nrb, P.next);
-    if (nbn > 0)
-        k_leg_adj_b<0, AW><<<(unsigned)(8 * nbn * lblocks), 64 * AW, 0, P.stream>>>(
-            (const float2 *)P.d_FG, fg_stride, P.d_coef32, P.d_ent, P.d_entk, P.d_entl, P.ng64, P.d_pair_z,
-            (float *)P.d_part, P.d_wgstart_b, P.nalm, P.lmax, P.npairs, P.nrings, P.nrhs, q, list + npol, nmain, live,
-            nbp, nbn, nrb, P.next);
-}
-
-// batched synthesis of FP32 plans: records and matrix-core sums per group of NBR right-hand sides, over
-// every 64-pair group (live false) or those with a ring that carries weight (live true)
-void launch_synth_batched(Plan &P, const double *xE, const double *xB, int64_t rstride, const double *kern, bool live)
-{
-    const int64_t fg_stride = (int64_t)P.nrings * (P.lmax + 1) * 2;
-    const GroupSet &G = live && P.skip_rings ? P.gs_live : P.gs_all;
-    const int64_t lblocks = xcd_slots(P.lmax);
-    for (int q = 0; q * NBR < P.nrhs; ++q) {
-        k_prologue_b<<<(unsigned)cdiv(P.nalm * NBR, 256), 256, 0, P.stream>>>(xE, xB, rstride, kern, P.d_lof, P.lmax,
-                                                                             P.nalm, P.nrhs, q, P.d_brec);
-        switch (P.bat_SW) {
-        case 1: synth_b_launch<1>(P, q, fg_stride, lblocks, G.list_any, G.npol_any, G.nmain_any); break;
-        case 2: synth_b_launch<2>(P, q, fg_stride, lblocks, G.list_any, G.npol_any, G.nmain_any); break;
-        case 8: synth_b_launch<8>(P, q, fg_stride, lblocks, G.list_any, G.npol_any, G.nmain_any); break;
-        default: synth_b_launch<4>(P, q, fg_stride, lblocks, G.list_any, G.npol_any, G.nmain_any);
-        }
-    }
-}
-
-// batched adjoint of the right-hand-side group q into the [rhs - NBR q][nrb_cur_b][nalm][4] slabs of
-// d_part, over every 64-pair group (live false) or those with a ring that carries weight, reading
-// only such rings (live true)
-void launch_adj_batched(Plan &P, int q, bool live)
-{
-    live = live && P.skip_rings;
-    const int64_t fg_stride = (int64_t)P.nrings * (P.lmax + 1) * 2;
-    const GroupSet &G = live ? P.gs_live : P.gs_all;
-    const uint8_t *lv = live ? P.d_ring_live : nullptr;
-    const int64_t lblocks = xcd_slots(P.lmax);
-    const int nrb = (int)(cdiv(G.npol_any, P.bat_AW) + cdiv(G.nmain_any, P.bat_AW));
-    switch (P.bat_AW) {
-    case 2: adj_b_launch<2>(P, q, fg_stride, lblocks, G.list_any, G.npol_any, G.nmain_any, lv, nrb); break;
-    case 8: adj_b_launch<8>(P, q, fg_stride, lblocks, G.list_any, G.npol_any, G.nmain_any, lv, nrb); break;
-    default: adj_b_launch<4>(P, q, fg_stride, lblocks, G.list_any, G.npol_any, G.nmain_any, lv, nrb);
-    }
-    P.nrb_b_cur = nrb;
-}
-
 void launch_epilogue_batched(Plan &P, int rhs, const double *kern, double lam, const double *xE, const double *xB,
                              double *outE, double *outB, double *dot_red)
 {
-    // (the batched kernels run the spin form everywhere)
     const float *part = (const float *)P.d_part + (int64_t)(rhs % NBR) * P.nrb_b_cur * P.next * 4;
     const unsigned g = dot_red ? (unsigned)cg_red_blocks(P) : (unsigned)cdiv(P.next, EPI_TILE);
-    k_epilogue<float><<<g, 256, 0, P.stream>>>(part, P.d_wgstart_b, P.nrb_b_cur, P.nrb_b_cur, P.nalm, P.next, P.d_lm,
+    k_epilogue<float><<<g, 256, 0, P.stream>>>(part, P.d_wgstart_b, P.nrbs_b_cur, P.nrb_b_cur, P.nalm, P.next, P.d_lm,
                                               P.d_sten, P.d_sc, P.lmax, kern, lam, xE, xB, outE, outB, P.proj,
                                               dot_red);
 }

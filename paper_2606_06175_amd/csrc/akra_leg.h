@@ -27,12 +27,6 @@
 
 namespace akra {
 enum { FORM_SCALAR = 0, FORM_SPIN = 1 };
-// Recurrence forms of the batched FP32 kernels: 0 the plain three-term form, 1 the difference form
-// near the poles (see Coef32D).
-template <int F> struct CoefB;
-template <> struct CoefB<0> { using type = Coef32; };
-template <> struct CoefB<1> { using type = Coef32D; };
-
 // ------------------------------------------------------------------------------------------------
 // Entry states: stored in FP64 as mant * 2^(512 k).
 // ------------------------------------------------------------------------------------------------
@@ -60,15 +54,14 @@ __device__ __forceinline__ void load_entry_scalar(const Ent64 *__restrict__ ent,
     c = refl ? refl * e.c2 : e.c2;
     p = refl ? -refl * e.p2 : e.p2;
 }
-// the batched FP32 kernels re-express a spin entry state in their own unit (F = 1: the difference
-// form, p2 and pm carry lambda_l - lambda_{l-1})
-template <int F>
+// the batched FP32 kernels' near-polar groups: a spin entry state in their own unit, p2 and pm carrying
+// lambda_l - lambda_{l-1} (the difference form)
 __device__ __forceinline__ void load_entry_b(const Ent64 *__restrict__ ent, const int *__restrict__ entk, int64_t idx,
                                              float &c2, float &p2, float &cm, float &pm, int &k)
 {
     const Ent64 e = ent[idx];
     const int k64 = entk[idx];
-    const double d2 = F ? e.c2 - e.p2 : e.p2, dm = F ? e.cm - e.pm : e.pm;
+    const double d2 = e.c2 - e.p2, dm = e.cm - e.pm;
     const double big = fmax(fmax(fabs(e.c2), fabs(e.cm)), fmax(fabs(d2), fabs(dm)));
     if (big == 0.0) {
         c2 = p2 = cm = pm = 0.0f;
@@ -104,15 +97,6 @@ template <typename P> __device__ __forceinline__ const_as<P> *uniform_ptr(const 
     return (const_as<P> *)(((uint64_t)hi << 32) | lo);
 }
 
-__device__ __forceinline__ Coef32 ld_coef(const_as<Coef32> *p)
-{
-    Coef32 c;
-    c.a = p->a;
-    c.b = p->b;
-    c.g = p->g;
-    c.pad = 0;
-    return c;
-}
 __device__ __forceinline__ Coef32D ld_coef(const_as<Coef32D> *p)
 {
     Coef32D c;
@@ -123,46 +107,21 @@ __device__ __forceinline__ Coef32D ld_coef(const_as<Coef32D> *p)
     return c;
 }
 
-// The ring pair's position as the batched FP32 recurrences use it: an unevaluated sum hi + lo of two
-// floats, x = cos(theta) in the plain form and y = 1 - cos(theta) (exact in double for the ring's
-// defining z) in the difference form: rounding it to one float would move the ring by a fixed angle,
-// an error that grows linearly along l.
-struct XF {
-    float hi, lo;
-};
+// The ring pair's position as the difference form uses it: y = 1 - cos(theta) (exact in double for the
+// ring's defining z) as an unevaluated sum hi + lo of two floats.  Rounding it to one float would move
+// the ring by a fixed angle, an error that grows linearly along l.
 struct YF {
     float hi, lo;
 };
-template <int F> struct PosB;
-template <> struct PosB<0> { using type = XF; };
-template <> struct PosB<1> { using type = YF; };
-__device__ __forceinline__ void setpos(XF &x, double z)
-{
-    x.hi = (float)z;
-    x.lo = (float)(z - (double)x.hi);
-}
 __device__ __forceinline__ void setpos(YF &y, double z)
 {
     const double v = 1.0 - z;
     y.hi = (float)v;
     y.lo = (float)(v - (double)y.hi);
 }
-
-// One step l -> l+1 of the spin +2 and spin -2 recurrences of the batched kernels.  Plain form:
-// (c2, p2) = (lambda_l, lambda_{l-1}).  Difference form: (c2, p2) = (lambda_l, lambda_l - lambda_{l-1}).
-template <class C>
-__device__ __forceinline__ void rstep(const C &c, XF x, float &c2, float &p2, float &cm, float &pm)
-{
-    const float u = fmaf(c.a, x.hi, c.a * x.lo);
-    const float n2 = fmaf(u + c.b, c2, -(c.g * p2));
-    const float nm = fmaf(u - c.b, cm, -(c.g * pm));
-    p2 = c2;
-    c2 = n2;
-    pm = cm;
-    cm = nm;
-}
-template <class C>
-__device__ __forceinline__ void rstep(const C &c, YF y, float &c2, float &p2, float &cm, float &pm)
+// One step l -> l+1 of the spin +2 and spin -2 recurrences in the difference form: (c2, p2) = (lambda_l,
+// lambda_l - lambda_{l-1}).
+__device__ __forceinline__ void rstep(const Coef32D &c, YF y, float &c2, float &p2, float &cm, float &pm)
 {
     const float t = c.a * y.lo;
     const float kp = fmaf(-c.a, y.hi, c.ep - t), km = fmaf(-c.a, y.hi, c.em - t);
@@ -197,6 +156,51 @@ __device__ __forceinline__ bool wave_any(bool p) { return __ballot(p) != 0ull; }
 // of the scalar functions (EXT_L more than lmax)
 __device__ __forceinline__ int64_t alm_base(int m, int lmax) { return (int64_t)m * (2 * lmax + 1 - m) / 2; }
 __device__ __forceinline__ int64_t ext_base(int m, int lmax) { return alm_base(m, lmax) + (int64_t)EXT_L * m; }
+
+// The scalar form's coefficients q = (Re q_l, Im q_l, Re u_l, Im u_l) of entry (l, m), i its alm index (past
+// the stored ones when l > lmax), of E, B = K_l (x_E, x_B) with Im(a_l0) dropped:
+//   q_l = w_2(l-2) E_{l-2} + w_0(l) E_l + w_-2(l+2) E_{l+2} + i (x_1(l-1) B_{l-1} + x_-1(l+1) B_{l+1}),
+//   u_l = w_2(l-2) B_{l-2} + w_0(l) B_l + w_-2(l+2) B_{l+2} - i (x_1(l-1) E_{l-1} + x_-1(l+1) E_{l+1})
+// (the stencil is zero at degrees below 2).
+__device__ __forceinline__ void stencil_in(const double2 *__restrict__ xE, const double2 *__restrict__ xB,
+                                           const double *__restrict__ kern, const double *__restrict__ sten, int l,
+                                           int m, int lmax, int64_t nalm, int64_t i, double (&q)[4])
+{
+    const int64_t ns = nalm + ALM_PAD;
+    q[0] = q[1] = q[2] = q[3] = 0.0;
+    auto at = [&](int d, int row, double &w, double2 &E, double2 &B) {
+        if (l + d < m || l + d > lmax) return false;
+        w = sten[row * ns + i + d];
+        if (kern) w *= kern[l + d];
+        E = xE[i + d];
+        B = xB[i + d];
+        if (m == 0) E.y = B.y = 0.0;
+        return true;
+    };
+    auto even = [&](int d, int row) {
+        double w;
+        double2 E, B;
+        if (!at(d, row, w, E, B)) return;
+        q[0] = fma(w, E.x, q[0]);
+        q[1] = fma(w, E.y, q[1]);
+        q[2] = fma(w, B.x, q[2]);
+        q[3] = fma(w, B.y, q[3]);
+    };
+    auto odd = [&](int d, int row) {
+        double x;
+        double2 E, B;
+        if (!at(d, row, x, E, B)) return;
+        q[0] = fma(-x, B.y, q[0]);
+        q[1] = fma(x, B.x, q[1]);
+        q[2] = fma(x, E.y, q[2]);
+        q[3] = fma(-x, E.x, q[3]);
+    };
+    even(-2, ST_W2);
+    odd(-1, ST_X1);
+    even(0, ST_W0);
+    odd(1, ST_XM1);
+    even(2, ST_WM2);
+}
 
 // XCD-aware placement: workgroups are dealt to the 8 XCDs round-robin, so all blocks of one m
 // are mapped to blocks with the same index mod 8 (they share that XCD's L2 for the per-m data),

@@ -20,14 +20,9 @@
 // 5.2e-15 / 1.1e-14 at 0.1, 1.6e-14 / 7.3e-13 at 0.02.  From 0.15 rad on the two are as good as equal
 // at the sizes whose second group begins that near a pole (Nside 350 and up).
 constexpr double AKRA_POLE_THETA = 0.15;
-// The batched FP32 kernels run the spin-weighted recurrences of ring pairs within AKRA_DIFF_THETA
-// radians of a pole in the difference form.  Near a pole the per-step phase advance of the recurrence is of the order
-// of theta; in the plain form the FP32 rounding of each step moves the phase by ~eps/theta, an
-// error that grows like sqrt(l) eps/theta.  The difference form keeps it at ~sqrt(l) eps there but
-// rounds more at large theta; the two errors cross near 0.45 rad.
-#ifndef AKRA_DIFF_THETA
-#define AKRA_DIFF_THETA 0.45
-#endif
+// The batched kernels sum in FP32, whose rounding the division by sin^2(theta) does amplify: there the
+// spin form (in the FP32 difference form) covers the groups that begin within AKRA_POLE_THETA_B.
+constexpr double AKRA_POLE_THETA_B = 0.3;
 
 namespace akra {
 
@@ -109,12 +104,11 @@ static void build_rings(Plan &P)
 // Entries past the last column (ALM_PAD) keep the kernels' look-ahead loads in bounds.
 // The scaled form (Coef64S) divides out c_l with c_{l0} = c_{l0+1} = 1, c_{l+1} = g_l c_{l-1}: entries
 // below l0 and the padding carry c = 1, the entry at lmax its c with a' = b' = 0.
-static void build_coef(int lmax, std::vector<Coef64> &c64, std::vector<Coef32> &c32, std::vector<Coef32D> &c32d,
+static void build_coef(int lmax, std::vector<Coef64> &c64, std::vector<Coef32D> &c32d,
                        std::vector<Coef64S> &c64s)
 {
     const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 2) / 2;
     c64.assign(nalm + ALM_PAD, Coef64{0, 0, 0, 0});
-    c32.assign(nalm + ALM_PAD, Coef32{0, 0, 0, 0});
     c32d.assign(nalm + ALM_PAD, Coef32D{0, 0, 0, 0});
     c64s.assign(nalm + ALM_PAD, Coef64S{0, 0, 1, 1});
     parallel_for(lmax + 1, [&](int m) {
@@ -131,7 +125,6 @@ static void build_coef(int lmax, std::vector<Coef64> &c64, std::vector<Coef32> &
             const ld b = 2.0L * m * q / (L * r1);
             const ld g = (L + 1) * r0 * sqrtl((2 * L + 3) / (2 * L - 1)) / (L * r1);
             c64[base + l] = Coef64{(double)a, (double)b, (double)g, 0.0};
-            c32[base + l] = Coef32{(float)a, (float)b, (float)g, 0.0f};
             c32d[base + l] = Coef32D{(float)a, (float)(a + b - g - 1), (float)(a - b - g - 1), (float)g};
             if (l > l0) cs[l + 1] = g * cs[l - 1];
             const ld f = cs[l] / cs[l + 1];
@@ -443,7 +436,7 @@ static akra_status build_live_lists(Plan &P)
         const int c = gcls[g];
         for (int cc : {c, (int)GCLS_N}) {
             gbase[(size_t)cc * P.ng64 + cnt[cc]++] = g;
-            if (g < (cc == GCLS_N ? P.polar_groups : P.spin_groups)) pol[cc]++;
+            if (g < P.spin_groups) pol[cc]++;
         }
     }
     GroupSet &G = P.gs_live;
@@ -466,9 +459,9 @@ static akra_status build_live_lists(Plan &P)
 
 static void free_plan(Plan *P)
 {
-    void *ptrs[] = {P->d_rings, P->d_pair_z, P->d_coef64, P->d_coef32, P->d_coef64s, P->d_sa, P->d_sc, P->d_sten, P->d_lm, P->d_rec_spin,
+    void *ptrs[] = {P->d_rings, P->d_pair_z, P->d_coef64, P->d_coef64s, P->d_sa, P->d_sc, P->d_sten, P->d_lm, P->d_rec_spin,
                     P->d_seed2, P->d_seedm2, P->d_seedk,
-                    P->d_ent, P->d_entk, P->d_entl, P->d_wgstart, P->d_wgstart_b, P->d_coef32d, P->d_brec,
+                    P->d_ent, P->d_entk, P->d_entl, P->d_wgstart, P->d_wgstart_b, P->d_coef32d, P->d_brec, P->d_brec_spin,
                     P->d_tw64, P->d_tw32, P->d_bhat64, P->d_bhat32, P->d_bhatr64, P->d_bhatr32, P->d_order_r[0], P->d_order_r[1],
                     P->d_order_r[2], P->d_order_r[3], P->d_order_r[4], P->d_order_r[5], P->d_lof, P->d_order_p2, P->d_order_bl, P->d_order_bf, P->d_FG, P->d_part, P->d_rec, P->d_W, P->d_kern, P->d_kuser, P->d_red, P->d_red_cg, P->d_scal, P->d_flag, P->d_x, P->d_r,
                     P->d_p, P->d_w, P->d_b, P->d_xs, P->d_cmp, P->d_spec, P->d_gl_all, P->d_live_lists,
@@ -623,16 +616,9 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
             }
     }
 
-    // near-polar groups of FP32 plans: first pair of the group within theta_c of a pole
     P->ng64 = (P->npairs + 63) / 64;
-    if (prec == AKRA_FP32) {
-        const double theta_c = AKRA_DIFF_THETA;
-        int g = 0;
-        while (g < P->ng64 && std::acos(P->h_rings[64 * g].z) < theta_c) ++g;
-        P->polar_groups = std::min(P->ng64, (g + 3) / 4 * 4);
-    }
-    while (P->spin_groups < P->ng64 && std::acos(P->h_rings[64 * P->spin_groups].z) < AKRA_POLE_THETA) ++P->spin_groups;
-    if (prec == AKRA_FP32 && nrhs > 1) P->spin_groups = P->ng64;  // the batched kernels run the spin form everywhere
+    const double theta = prec == AKRA_FP32 && nrhs > 1 ? AKRA_POLE_THETA_B : AKRA_POLE_THETA;
+    while (P->spin_groups < P->ng64 && std::acos(P->h_rings[64 * P->spin_groups].z) < theta) ++P->spin_groups;
     P->next = P->nalm + (int64_t)EXT_L * (lmax + 1);
 
     // Legendre launch shapes
@@ -660,12 +646,10 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     // tables
     {
         std::vector<Coef64> c64;
-        std::vector<Coef32> c32;
         std::vector<Coef32D> c32d;
         std::vector<Coef64S> c64s;
-        build_coef(lmax, c64, c32, c32d, c64s);
+        build_coef(lmax, c64, c32d, c64s);
         AK_TRY(upload((void **)&P->d_coef64, c64.data(), c64.size() * sizeof(Coef64), *P));
-        AK_TRY(upload((void **)&P->d_coef32, c32.data(), c32.size() * sizeof(Coef32), *P));
         AK_TRY(upload((void **)&P->d_coef64s, c64s.data(), c64s.size() * sizeof(Coef64S), *P));
         AK_TRY(upload((void **)&P->d_coef32d, c32d.data(), c32d.size() * sizeof(Coef32D), *P));
     }
@@ -707,10 +691,8 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         AK_TRY(upload((void **)&P->d_gl_all, ids.data(), ids.size() * sizeof(int), *P));
         GroupSet &A = P->gs_all;
         A.list[GCLS_BOTH] = A.list_any = P->d_gl_all;
-        A.npol[GCLS_BOTH] = P->spin_groups;
-        A.nmain[GCLS_BOTH] = P->ng64 - P->spin_groups;
-        A.npol_any = P->polar_groups;
-        A.nmain_any = P->ng64 - P->polar_groups;
+        A.npol[GCLS_BOTH] = A.npol_any = P->spin_groups;
+        A.nmain[GCLS_BOTH] = A.nmain_any = P->ng64 - P->spin_groups;
         // until a weight set-up, the weighted sets are the full ones
         P->rs_live = P->rs_all;
         P->rs_cls[0] = P->rs_all;  // every group counts as two-sided
@@ -825,8 +807,8 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     if (prec == AKRA_FP32 && nrhs > 1) {
         // batched adjoint: blocks of four groups (polar blocks apart), 8 right-hand sides of FP32 slabs
         // ring blocks of bat_AW groups (polar blocks apart); room for the smallest supported bat_AW, 2
-        P->nrb_b = (P->polar_groups + P->bat_AW - 1) / P->bat_AW + (P->ng64 - P->polar_groups + P->bat_AW - 1) / P->bat_AW;
-        P->nrb_b_cap = (P->polar_groups + 1) / 2 + (P->ng64 - P->polar_groups + 1) / 2;
+        P->nrb_b = (P->spin_groups + P->bat_AW - 1) / P->bat_AW + (P->ng64 - P->spin_groups + P->bat_AW - 1) / P->bat_AW;
+        P->nrb_b_cap = (P->spin_groups + 1) / 2 + (P->ng64 - P->spin_groups + 1) / 2;
         P->part_rb_cap = std::max(P->part_rb_cap, (size_t)4 * P->nrb_b_cap);
         AK_TRY(alloc((void **)&P->d_wgstart_b, (size_t)P->nrb_b_cap * (lmax + 1) * sizeof(int), *P));
     }
@@ -842,7 +824,11 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     const size_t rec_b = (size_t)nrhs * P->rec_stride * 5 * sizeof(double), recs_b = (size_t)nrhs * (P->nalm + ALM_PAD) * 64;
     AK_TRY(alloc((void **)&P->d_rec, rec_b, *P));
     if (P->spin_groups > 0) AK_TRY(alloc(&P->d_rec_spin, recs_b, *P));
-    if (prec == AKRA_FP32 && nrhs > 1) AK_TRY(alloc((void **)&P->d_brec, (size_t)P->rec_stride * 8 * 4 * sizeof(float), *P));
+    if (prec == AKRA_FP32 && nrhs > 1) {
+        AK_TRY(alloc((void **)&P->d_brec, (size_t)P->rec_stride * NBR * 4 * sizeof(float), *P));
+        if (P->spin_groups > 0)
+            AK_TRY(alloc((void **)&P->d_brec_spin, (size_t)(P->nalm + ALM_PAD) * NBR * 4 * sizeof(float), *P));
+    }
     if (hipMemset(P->d_rec, 0, rec_b) != hipSuccess || (P->d_rec_spin && hipMemset(P->d_rec_spin, 0, recs_b) != hipSuccess)) {
         free_plan(P);
         set_error("hipMemset failed");
@@ -2168,7 +2154,7 @@ akra_status akra_plan_set_tuning_batched(akra_plan plan, int syn_waves, int adj_
     AK_HIP(hipStreamSynchronize(P.stream), "sync");
     P.bat_SW = syn_waves;
     P.bat_AW = adj_waves;
-    P.nrb_b = (P.polar_groups + adj_waves - 1) / adj_waves + (P.ng64 - P.polar_groups + adj_waves - 1) / adj_waves;
+    P.nrb_b = (P.spin_groups + adj_waves - 1) / adj_waves + (P.ng64 - P.spin_groups + adj_waves - 1) / adj_waves;
     drop_graph(P);  // recorded iterations hold the old launch shapes
     return AKRA_OK;
 }

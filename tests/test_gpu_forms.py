@@ -50,3 +50,36 @@ def test_forms_match_oracle(nside, lmax, prec, tol):
         ref = o.apply_H(np.stack(a), o.weights(ninv, mask), 0.02)
         check_alm(np.stack([v.cpu().numpy() for v in y]), ref, lmax, tol)
     p.close()
+
+
+# (nside, lmax, nrhs): groups of at most four right-hand sides (16-column products) and of eight (32
+# columns), full and padded, alone and one after the other; degrees just past a round (4 or 8) and past a
+# 64-degree chunk; one group, spin and scalar groups, many groups that never enter
+BATCHED = [(33, 2, 2), (33, 66, 4), (64, 61, 5), (70, 9, 8), (100, 130, 12), (128, 63, 3), (260, 12, 13)]
+
+
+@pytest.mark.parametrize("nside,lmax,nrhs", BATCHED)
+def test_batched_forms_match_oracle(nside, lmax, nrhs):
+    # FP32 products and sums of FP64 recurrence values: each coefficient and value is rounded once (6e-8),
+    # the division by sin^2 amplifies that by at most 11 (0.3 rad), so 1e-5 holds with room, per ring and
+    # per m; the spin groups within 0.3 rad keep the 1e-5 of the FP32 difference form
+    import torch
+    from paper_2606_06175_amd import Plan
+    print("nside %d lmax %d nrhs %d" % (nside, lmax, nrhs), flush=True)
+    dev = torch.device("cuda", 0)
+    rings = healpix_rings(nside)
+    o = Oracle(lmax, rings)
+    A, B = (np.stack([wl.random_alm(lmax, 10 * s + k, lmin=0) for k in range(nrhs)]) for s in (3, 9))
+    z = wl.pixel_vectors(nside)[2]
+    mask = ((z < 0.6) & (z > -0.9)).astype(np.uint8)
+    ninv = np.stack([np.random.default_rng(40 + k).uniform(5.0, 60.0, rings.npix) for k in range(nrhs)])
+    p = Plan(nside, lmax, nrhs=nrhs, precision="fp32", device=dev)
+    tA, tB = torch.from_numpy(A).to(dev), torch.from_numpy(B).to(dev)
+    g1, g2 = (v.cpu().numpy() for v in p.synth2(tA, tB))
+    yE, yB = (v.cpu().numpy() for v in p.apply_H(torch.from_numpy(ninv).to(dev), torch.from_numpy(mask).to(dev), tA,
+                                                 tB, 0.02))
+    for k in sorted({0, nrhs // 2, nrhs - 1}):
+        check_maps(g1[k], g2[k], *o.synth(A[k], B[k]), rings, 1e-5)
+        ref = o.apply_H(np.stack([A[k], B[k]]), o.weights(ninv[k], mask), 0.02)
+        check_alm(np.stack([yE[k], yB[k]]), ref, lmax, 1e-5)
+    p.close()
