@@ -339,6 +339,23 @@ template <class A, class B> void fork_join(Plan &P, A &&side, B &&main)
     P.in_fork = false;
 }
 
+// by-value kernel arguments: lambda of the right-hand sides of a batched group; the right-hand sides a PCG
+// update covers, with their preconditioners P
+struct EpiLam {
+    double lam[NBR];
+};
+constexpr int MAX_RHS = 64;
+struct CgList {
+    int n = 0;
+    int rhs[MAX_RHS] = {};
+    double pc[MAX_RHS] = {};
+    void add(int r, double p)
+    {
+        rhs[n] = r;
+        pc[n++] = p;
+    }
+};
+
 // error handling
 void set_error(const std::string &msg);
 akra_status hip_fail(hipError_t e, const char *what);
@@ -383,11 +400,12 @@ void launch_scale_scalar(Plan &P, double *out, const double *in, double f);
 // workgroup partials of the full-m <x, out> (cg_red_blocks(P) of them)
 void launch_epilogue(Plan &P, bool fp32, const double *kern, double lam, const double *xE, const double *xB,
                      double *outE, double *outB, double *dot_red = nullptr);
-// batched FP32 adjoint (matrix cores) of right-hand-side group q, and the epilogue of one right-hand
-// side from its slabs
+// batched FP32 adjoint (matrix cores) of right-hand-side group q, and the epilogue of its right-hand
+// sides (vectors v_stride doubles apart, lambda lam[r], partials of <x, y> 2 CG_RED_BLOCKS apart)
 void launch_adj_batched(Plan &P, int q, bool live);
-void launch_epilogue_batched(Plan &P, int rhs, const double *kern, double lam, const double *xE, const double *xB,
-                             double *outE, double *outB, double *dot_red = nullptr);
+void launch_epilogue_batched(Plan &P, int q, const double *kern, const double *lam, const double *xE,
+                             const double *xB, double *outE, double *outB, int64_t v_stride,
+                             double *dot_red = nullptr);
 // chirp spectra of the Bluestein sub lengths Ls (FFT lengths Ms, table offsets ofs; device arrays)
 void launch_bhat(Plan &P, const int *Ls, const int *Ms, const int64_t *ofs, int n, int maxM);
 void launch_bhat_reorder(Plan &P, int logm, const int64_t *src_ofs, const int64_t *dst_ofs, int n);
@@ -398,20 +416,16 @@ void launch_weights(Plan &P, const double *ninv, const uint8_t *mask, int nrhs, 
 // full-m dot products and CG vector updates on [2][nalm] complex FP64 vectors
 void launch_dot(Plan &P, const double *a, const double *b, double *out_dev, int64_t n_complex);
 void launch_cg_p(Plan &P, double *p, const double *r, const double *beta_dev, double precond, int64_t n_complex);
-// The PCG iteration's fused scalar path: at most CG_RED_BLOCKS workgroup partials per inner
-// product (the epilogue's <p, w>, the update's <r, r>), summed in a fixed order by the kernels that
-// form alpha and beta (scal[0] rz, [1] <p, w>, [2] alpha, [3] <r, r>, [4] beta)
+// The PCG iteration's fused scalar path: at most CG_RED_BLOCKS workgroup partials per inner product
+// (in d_red_cg, per right-hand side the epilogue's <p, w>, then the update's <r, r>), summed in a fixed
+// order by the kernels that form alpha and beta.  Per right-hand side 8 scalars (scal[0] rz, [1] <p, w>,
+// [2] alpha, [3] <r, r>, [4] beta, [7] rz between the two kernels) and a breakdown flag; vectors
+// n_complex apart.
 constexpr int CG_RED_BLOCKS = 1024;
 int cg_red_blocks(const Plan &P);
-void launch_cg_alpha_sum(Plan &P, const double *red, double *scal, int *flag);
-void launch_cg_xr_rr(Plan &P, double *x, double *r, const double *p, const double *w, const double *alpha_dev,
-                     int64_t n_complex, double *rr_red);
-void launch_cg_beta_sum(Plan &P, const double *red, double *scal, double precond);
-// the same iteration in two vector kernels for one right-hand side (scal[7] holds rz between them)
-void launch_cg_xr_alpha(Plan &P, double *x, double *r, const double *p, const double *w, const double *red_pw,
-                        double *scal, int *flag, int64_t n_complex, double *rr_red);
-void launch_cg_p_beta(Plan &P, double *p, const double *r, const double *red_rr, double *scal, double precond,
-                      int64_t n_complex);
+void launch_cg_xr_alpha(Plan &P, double *x, double *r, const double *p, const double *w, double *scal, int *flag,
+                        int64_t n_complex, const CgList &L);
+void launch_cg_p_beta(Plan &P, double *p, const double *r, double *scal, int64_t n_complex, const CgList &L);
 void launch_axpby(Plan &P, double *y, double a, const double *x, double b, int64_t n_complex);
 void launch_scalar_div(Plan &P, double *out, const double *num, const double *den);
 // shape-noise realisations and spectra (akra_spectra.hip)

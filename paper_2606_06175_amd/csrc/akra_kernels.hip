@@ -152,20 +152,32 @@ __device__ __forceinline__ double block_sum256(double s, double *sh)
 // the slabs of its entry into LDS and the inner 252 apply the stencil from there, so the slabs, the
 // bulk of the traffic, are read once.  Ring blocks that started above l wrote nothing for it.
 // With dot_red, also the workgroup partials of the full-m inner product <x, out> (one per workgroup,
-// summed in a fixed order by the CG scalar kernel).
+// summed in a fixed order by the CG scalar kernel).  blockIdx.y picks one of the right-hand sides of a
+// batched group (strides part_stride, v_stride and 2 CG_RED_BLOCKS, lambda la.lam).
 constexpr int EPI_TILE = 256 - 2 * EXT_L;
 template <typename S>
 __global__ __launch_bounds__(256) void k_epilogue(const S *__restrict__ part, const int *__restrict__ wgstart,
                                                   int nrbs, int nrb, int64_t nalm, int64_t next,
                                                   const uint32_t *__restrict__ lm, const double *__restrict__ sten,
                                                   const double *__restrict__ sc, int lmax,
-                                                  const double *__restrict__ kern, double lam,
+                                                  const double *__restrict__ kern, EpiLam la,
                                                   const double *__restrict__ xE, const double *__restrict__ xB,
                                                   double *__restrict__ outE, double *__restrict__ outB, int proj,
-                                                  double *__restrict__ dot_red)
+                                                  double *__restrict__ dot_red, int64_t part_stride,
+                                                  int64_t v_stride)
 {
     __shared__ double sh[256];
     __shared__ double T[4][256];
+    const int rhs = blockIdx.y;
+    const double lam = la.lam[rhs];
+    part += rhs * part_stride;
+    outE += rhs * v_stride;
+    outB += rhs * v_stride;
+    if (xE) {
+        xE += rhs * v_stride;
+        xB += rhs * v_stride;
+    }
+    if (dot_red) dot_red += (int64_t)rhs * 2 * CG_RED_BLOCKS;
     const int tid = threadIdx.x;
     const int64_t ns = nalm + ALM_PAD;
     double dot = 0.0;
@@ -1345,32 +1357,6 @@ __global__ __launch_bounds__(256) void k_sum_part(const double *__restrict__ red
     }
 }
 
-// x += alpha p, r -= alpha w on complex elements (re, im pairs), with the workgroup partials of the
-// full-m <r, r> of the updated r
-__global__ __launch_bounds__(256) void k_cg_xr_rr(double2 *__restrict__ x, double2 *__restrict__ r,
-                                                  const double2 *__restrict__ p, const double2 *__restrict__ w,
-                                                  const double *__restrict__ alpha, int64_t nc, int64_t nalm, int lmax,
-                                                  double *__restrict__ rr_red)
-{
-    __shared__ double sh[256];
-    const double a = *alpha;
-    double s = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nc; i += (int64_t)gridDim.x * blockDim.x) {
-        const double2 pi = p[i], wi = w[i];
-        double2 xi = x[i], ri = r[i];
-        xi.x = fma(a, pi.x, xi.x);
-        xi.y = fma(a, pi.y, xi.y);
-        ri.x = fma(-a, wi.x, ri.x);
-        ri.y = fma(-a, wi.y, ri.y);
-        x[i] = xi;
-        r[i] = ri;
-        const double wgt = ((i % nalm) <= lmax) ? 1.0 : 2.0;
-        s += wgt * (ri.x * ri.x + ri.y * ri.y);
-    }
-    const double t = block_sum256(s, sh);
-    if (threadIdx.x == 0) rr_red[blockIdx.x] = t;
-}
-
 // Fixed-order sum of n workgroup partials by one workgroup of 256 threads (thread t sums partials
 // t, t + 256, ... in order, then a tree), the total in thread 0
 __device__ __forceinline__ double sum_partials256(const double *__restrict__ red, int n, double *sh)
@@ -1380,35 +1366,27 @@ __device__ __forceinline__ double sum_partials256(const double *__restrict__ red
     return block_sum256(s, sh);
 }
 
-// scal[1] = <p, w> from the epilogue's partials, then alpha = rz / <p, w> into scal[2]; breakdown
-// (p^T H p <= 0 or non-finite) sets the flag, which is sticky: alpha = 0 until the host reads it
-__global__ __launch_bounds__(256) void k_cg_alpha_sum(const double *__restrict__ red, int n, double *__restrict__ scal,
-                                                      int *__restrict__ flag)
-{
-    __shared__ double sh[256];
-    const double pw = sum_partials256(red, n, sh);
-    if (threadIdx.x != 0) return;
-    scal[1] = pw;
-    if (flag[0] || !(pw > 0.0) || !isfinite(pw)) {
-        flag[0] = 1;
-        scal[2] = 0.0;
-    } else {
-        scal[2] = scal[0] / pw;
-    }
-}
-
-// Single-right-hand-side iteration with the scalar steps inside the vector kernels: every
-// workgroup sums the same partials in the same fixed order, so all hold the same alpha (beta), and
-// workgroup 0 records the scalars.  The x/r update reads rz at scal[0] and keeps it at scal[7] for
-// the p update, which then owns scal[0].
+// The vector half of a PCG iteration, one right-hand side of the list per blockIdx.y: x += alpha p,
+// r -= alpha w and the partials of <r, r>.  Every workgroup sums the <p, w> partials in the same fixed
+// order and forms alpha itself (0 on breakdown, which raises the flag); the first one leaves the
+// scalars.  Bound by HBM, 96 bytes per coefficient; at small sizes by the launch, which the right-hand
+// sides of a batch share.
 __global__ __launch_bounds__(256) void k_cg_xr_alpha(double2 *__restrict__ x, double2 *__restrict__ r,
                                                      const double2 *__restrict__ p, const double2 *__restrict__ w,
-                                                     const double *__restrict__ red_pw, int n_pw,
-                                                     double *__restrict__ scal, int *__restrict__ flag, int64_t nc,
-                                                     int64_t nalm, int lmax, double *__restrict__ rr_red)
+                                                     double *__restrict__ red, int n_red, double *__restrict__ scal,
+                                                     int *__restrict__ flag, int64_t nc, int64_t nalm, int lmax,
+                                                     CgList L)
 {
     __shared__ double sh[256];
-    const double pw = sum_partials256(red_pw, n_pw, sh);
+    const int q = L.rhs[blockIdx.y];
+    x += q * nc;
+    r += q * nc;
+    p += q * nc;
+    w += q * nc;
+    red += (int64_t)q * 2 * CG_RED_BLOCKS;
+    scal += 8 * q;
+    flag += q;
+    const double pw = sum_partials256(red, n_red, sh);
     __syncthreads();
     const double rz = scal[0];
     const bool bad = flag[0] != 0 || !(pw > 0.0) || !isfinite(pw);
@@ -1423,12 +1401,12 @@ __global__ __launch_bounds__(256) void k_cg_xr_alpha(double2 *__restrict__ x, do
         ri.y = fma(-a, wi.y, ri.y);
         x[i] = xi;
         r[i] = ri;
-        const double wgt = ((i % nalm) <= lmax) ? 1.0 : 2.0;
+        const double wgt = (i < nalm ? i : i - nalm) <= lmax ? 1.0 : 2.0;  // nc = 2 nalm
         s += wgt * (ri.x * ri.x + ri.y * ri.y);
     }
     const double t = block_sum256(s, sh);
     if (threadIdx.x == 0) {
-        rr_red[blockIdx.x] = t;
+        red[CG_RED_BLOCKS + blockIdx.x] = t;
         if (blockIdx.x == 0) {
             scal[1] = pw;
             scal[2] = a;
@@ -1438,14 +1416,18 @@ __global__ __launch_bounds__(256) void k_cg_xr_alpha(double2 *__restrict__ x, do
     }
 }
 
-// p = P r + beta p with beta = P <r, r> / rz (rz from scal[7]); workgroup 0 records <r, r> at scal[3],
-// beta at scal[4] and the new rz = P <r, r> at scal[0]
+// p = P r + beta p with beta = P <r, r> / rz formed the same way from the partials of <r, r>
 __global__ __launch_bounds__(256) void k_cg_p_beta(double2 *__restrict__ p, const double2 *__restrict__ r,
-                                                   const double *__restrict__ red_rr, int n_rr,
-                                                   double *__restrict__ scal, double pc, int64_t nc)
+                                                   const double *__restrict__ red, int n_red,
+                                                   double *__restrict__ scal, int64_t nc, CgList L)
 {
     __shared__ double sh[256];
-    const double rr = sum_partials256(red_rr, n_rr, sh);
+    const int q = L.rhs[blockIdx.y];
+    const double pc = L.pc[blockIdx.y];
+    p += q * nc;
+    r += q * nc;
+    scal += 8 * q;
+    const double rr = sum_partials256(red + (int64_t)q * 2 * CG_RED_BLOCKS + CG_RED_BLOCKS, n_red, sh);
     const double rz_old = scal[7];
     const double rz = pc * rr;
     const double bt = (rz_old > 0.0) ? rz / rz_old : 0.0;
@@ -1461,19 +1443,6 @@ __global__ __launch_bounds__(256) void k_cg_p_beta(double2 *__restrict__ p, cons
         scal[4] = bt;
         scal[0] = rz;
     }
-}
-
-// scal[3] = <r, r> from the update's partials, then beta = P <r, r> / rz into scal[4], rz <- P <r, r>
-__global__ __launch_bounds__(256) void k_cg_beta_sum(const double *__restrict__ red, int n, double *__restrict__ scal,
-                                                     double pc)
-{
-    __shared__ double sh[256];
-    const double rr = sum_partials256(red, n, sh);
-    if (threadIdx.x != 0) return;
-    scal[3] = rr;
-    const double rz = pc * rr;
-    scal[4] = (scal[0] > 0.0) ? rz / scal[0] : 0.0;
-    scal[0] = rz;
 }
 
 __global__ void k_cg_p(double *__restrict__ p, const double *__restrict__ r, const double *__restrict__ beta,
@@ -1505,14 +1474,17 @@ void launch_prologue(Plan &P, const double *xE, const double *xB, const double *
                                         spin ? (SpinRec *)P.d_rec_spin : nullptr);
 }
 
-void launch_epilogue_batched(Plan &P, int rhs, const double *kern, double lam, const double *xE, const double *xB,
-                             double *outE, double *outB, double *dot_red)
+void launch_epilogue_batched(Plan &P, int q, const double *kern, const double *lam, const double *xE,
+                             const double *xB, double *outE, double *outB, int64_t v_stride, double *dot_red)
 {
-    const float *part = (const float *)P.d_part + (int64_t)(rhs % NBR) * P.nrb_b_cur * P.next * 4;
-    const unsigned g = dot_red ? (unsigned)cg_red_blocks(P) : (unsigned)cdiv(P.next, EPI_TILE);
-    k_epilogue<float><<<g, 256, 0, P.stream>>>(part, P.d_wgstart_b, P.nrbs_b_cur, P.nrb_b_cur, P.nalm, P.next, P.d_lm,
-                                              P.d_sten, P.d_sc, P.lmax, kern, lam, xE, xB, outE, outB, P.proj,
-                                              dot_red);
+    const int n = std::min(NBR, P.nrhs - NBR * q);
+    EpiLam la = {};
+    for (int r = 0; r < n; ++r) la.lam[r] = lam[r];
+    const dim3 g(dot_red ? (unsigned)cg_red_blocks(P) : (unsigned)cdiv(P.next, EPI_TILE), n);
+    k_epilogue<float><<<g, 256, 0, P.stream>>>((const float *)P.d_part, P.d_wgstart_b, P.nrbs_b_cur, P.nrb_b_cur,
+                                              P.nalm, P.next, P.d_lm, P.d_sten, P.d_sc, P.lmax, kern, la, xE, xB,
+                                              outE, outB, P.proj, dot_red, (int64_t)P.nrb_b_cur * P.next * 4,
+                                              v_stride);
 }
 
 void launch_entry(Plan &P)
@@ -1623,47 +1595,32 @@ void launch_epilogue(Plan &P, bool fp32, const double *kern, double lam, const d
                      double *outE, double *outB, double *dot_red)
 {
     const dim3 g(dot_red ? (unsigned)cg_red_blocks(P) : (unsigned)cdiv(P.next, EPI_TILE));
+    EpiLam la = {};
+    la.lam[0] = lam;
     if (fp32)
         k_epilogue<float><<<g, 256, 0, P.stream>>>((const float *)P.d_part, P.d_wgstart, P.nrbs_cur, P.nrb_cur, P.nalm,
-                                                   P.next, P.d_lm, P.d_sten, P.d_sc, P.lmax, kern, lam, xE, xB, outE,
-                                                   outB, P.proj, dot_red);
+                                                   P.next, P.d_lm, P.d_sten, P.d_sc, P.lmax, kern, la, xE, xB, outE,
+                                                   outB, P.proj, dot_red, 0, 0);
     else
         k_epilogue<double><<<g, 256, 0, P.stream>>>((const double *)P.d_part, P.d_wgstart, P.nrbs_cur, P.nrb_cur,
-                                                    P.nalm, P.next, P.d_lm, P.d_sten, P.d_sc, P.lmax, kern, lam, xE,
-                                                    xB, outE, outB, P.proj, dot_red);
+                                                    P.nalm, P.next, P.d_lm, P.d_sten, P.d_sc, P.lmax, kern, la, xE,
+                                                    xB, outE, outB, P.proj, dot_red, 0, 0);
 }
 
-void launch_cg_alpha_sum(Plan &P, const double *red, double *scal, int *flag)
-{
-    k_cg_alpha_sum<<<1, 256, 0, P.stream>>>(red, cg_red_blocks(P), scal, flag);
-}
-
-void launch_cg_xr_rr(Plan &P, double *x, double *r, const double *p, const double *w, const double *alpha_dev,
-                     int64_t n_complex, double *rr_red)
-{
-    k_cg_xr_rr<<<cg_red_blocks(P), 256, 0, P.stream>>>((double2 *)x, (double2 *)r, (const double2 *)p,
-                                                       (const double2 *)w, alpha_dev, n_complex, P.nalm, P.lmax,
-                                                       rr_red);
-}
-
-void launch_cg_xr_alpha(Plan &P, double *x, double *r, const double *p, const double *w, const double *red_pw,
-                        double *scal, int *flag, int64_t n_complex, double *rr_red)
+void launch_cg_xr_alpha(Plan &P, double *x, double *r, const double *p, const double *w, double *scal, int *flag,
+                        int64_t n_complex, const CgList &L)
 {
     const int nb = cg_red_blocks(P);
-    k_cg_xr_alpha<<<nb, 256, 0, P.stream>>>((double2 *)x, (double2 *)r, (const double2 *)p, (const double2 *)w, red_pw,
-                                            nb, scal, flag, n_complex, P.nalm, P.lmax, rr_red);
+    k_cg_xr_alpha<<<dim3(nb, L.n), 256, 0, P.stream>>>((double2 *)x, (double2 *)r, (const double2 *)p,
+                                                       (const double2 *)w, P.d_red_cg, nb, scal, flag, n_complex,
+                                                       P.nalm, P.lmax, L);
 }
 
-void launch_cg_p_beta(Plan &P, double *p, const double *r, const double *red_rr, double *scal, double precond,
-                      int64_t n_complex)
+void launch_cg_p_beta(Plan &P, double *p, const double *r, double *scal, int64_t n_complex, const CgList &L)
 {
     const int nb = cg_red_blocks(P);
-    k_cg_p_beta<<<nb, 256, 0, P.stream>>>((double2 *)p, (const double2 *)r, red_rr, nb, scal, precond, n_complex);
-}
-
-void launch_cg_beta_sum(Plan &P, const double *red, double *scal, double precond)
-{
-    k_cg_beta_sum<<<1, 256, 0, P.stream>>>(red, cg_red_blocks(P), scal, precond);
+    k_cg_p_beta<<<dim3(nb, L.n), 256, 0, P.stream>>>((double2 *)p, (const double2 *)r, P.d_red_cg, nb, scal, n_complex,
+                                                     L);
 }
 
 // The ring kinds of a RingSet: RK_P2 whole power-of-two rings (LDS FFT), RK_BF whole-ring Bluestein,

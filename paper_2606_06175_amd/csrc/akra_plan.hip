@@ -493,7 +493,7 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         set_error("lmax must be in [2, 4 nside]");
         return AKRA_ERR_ARG;
     }
-    if (nrhs < 1 || nrhs > 64) {
+    if (nrhs < 1 || nrhs > MAX_RHS) {
         set_error("nrhs must be in [1, 64]");
         return AKRA_ERR_ARG;
     }
@@ -1056,17 +1056,17 @@ static akra_status apply_H_batched(Plan &P, const double *kern_dev, const double
     stage_mark(P, 2, true);
     launch_ring(P, true, 2, nullptr, nullptr, nullptr, nullptr, P.d_W, P.nrhs, true);
     stage_mark(P, 2, false);
-    for (int q = 0; q * 8 < P.nrhs; ++q) {
+    for (int q = 0; q * NBR < P.nrhs; ++q) {
         stage_mark(P, 3, true);
         launch_adj_batched(P, q, true);
         stage_mark(P, 3, false);
-        for (int r = 8 * q; r < P.nrhs && r < 8 * q + 8; ++r) {
-            const int64_t o = (int64_t)r * 2 * rstride;
-            stage_mark(P, 4, true);
-            launch_epilogue_batched(P, r, kern_dev, lam_host ? lam_host[r] : lam, xE + o, xB + o, yE + o, yB + o,
-                                    dot_red ? dot_red + (int64_t)r * 2 * CG_RED_BLOCKS : nullptr);
-            stage_mark(P, 4, false);
-        }
+        double lq[NBR];
+        for (int r = 0; r < NBR; ++r) lq[r] = lam_host && NBR * q + r < P.nrhs ? lam_host[NBR * q + r] : lam;
+        const int64_t o = (int64_t)NBR * q * 2 * rstride;
+        stage_mark(P, 4, true);
+        launch_epilogue_batched(P, q, kern_dev, lq, xE + o, xB + o, yE + o, yB + o, 2 * rstride,
+                                dot_red ? dot_red + (int64_t)NBR * q * 2 * CG_RED_BLOCKS : nullptr);
+        stage_mark(P, 4, false);
     }
     return check_launch("apply_H_batched");
 }
@@ -1132,13 +1132,14 @@ static akra_status cg_iterate(Plan &P, bool fp32)
 {
     const int64_t nc = 2 * P.nalm;
     double *x = P.d_x, *r = P.d_r, *p = P.d_p, *w = P.d_w;
-    double *red_pw = P.d_red_cg, *red_rr = P.d_red_cg + CG_RED_BLOCKS;
     akra_status st =
-        apply_H_timed(P, fp32, P.cg_kern, P.cg_lam, p, p + 2 * P.nalm, w, w + 2 * P.nalm, P.cg_rhs, red_pw);
+        apply_H_timed(P, fp32, P.cg_kern, P.cg_lam, p, p + 2 * P.nalm, w, w + 2 * P.nalm, P.cg_rhs, P.d_red_cg);
     if (st) return st;
     stage_mark(P, 5, true);
-    launch_cg_xr_alpha(P, x, r, p, w, red_pw, P.d_scal, P.d_flag, nc, red_rr);
-    launch_cg_p_beta(P, p, r, red_rr, P.d_scal, P.cg_pc, nc);
+    CgList L;
+    L.add(0, P.cg_pc);
+    launch_cg_xr_alpha(P, x, r, p, w, P.d_scal, P.d_flag, nc, L);
+    launch_cg_p_beta(P, p, r, P.d_scal, nc, L);
     stage_mark(P, 5, false);
     P.cg_iters++;
     return check_launch("cg_step");
@@ -1681,17 +1682,13 @@ static akra_status solve_batched(Plan &P, const double *g1, const double *g2, co
             akra_status s2 = apply_H_batched(P, kd, le.data(), 0.0, P.d_p, P.d_p + 2 * na, P.d_w, P.d_w + 2 * na,
                                              2 * na, P.d_red_cg);
             if (s2) return s2;
-            for (int r = 0; r < nr; ++r) {
-                if (!active[r]) continue;
-                // the epilogue left the partials of <p, w>; the update leaves those of <r, r>
-                double *red_pw = P.d_red_cg + (int64_t)r * 2 * CG_RED_BLOCKS, *red_rr = red_pw + CG_RED_BLOCKS;
-                stage_mark(P, 5, true);
-                launch_cg_alpha_sum(P, red_pw, S(r), P.d_flag + r);
-                launch_cg_xr_rr(P, V(P.d_x, r), V(P.d_r, r), V(P.d_p, r), V(P.d_w, r), S(r) + 2, nc, red_rr);
-                launch_cg_beta_sum(P, red_rr, S(r), pc[r]);
-                launch_cg_p(P, V(P.d_p, r), V(P.d_r, r), S(r) + 4, pc[r], nc);
-                stage_mark(P, 5, false);
-            }
+            CgList L;
+            for (int r = 0; r < nr; ++r)
+                if (active[r]) L.add(r, pc[r]);
+            stage_mark(P, 5, true);
+            launch_cg_xr_alpha(P, P.d_x, P.d_r, P.d_p, P.d_w, scb, P.d_flag, nc, L);
+            launch_cg_p_beta(P, P.d_p, P.d_r, scb, nc, L);
+            stage_mark(P, 5, false);
             return check_launch("cg_batched");
         };
         if (P.timing || !P.use_graph) {
