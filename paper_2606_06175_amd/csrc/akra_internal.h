@@ -122,9 +122,11 @@ struct GroupSet {
     int npol_any = 0, nmain_any = 0;
 };
 // rings of one ring-stage launch set, by kernel kind: whole power-of-two rings in LDS (RK_P2), whole-ring
-// Bluestein (RK_BF), two half-length Bluestein transforms (RK_BL), and the register engine's six
-// lists (RK_REG + q, q as in Plan::d_order_r)
-enum { RK_P2 = 0, RK_BF = 1, RK_BL = 2, RK_REG = 3, RING_KINDS = 9 };
+// Bluestein (RK_BF), two half-length Bluestein transforms (RK_BL), and the register engine's lists
+// (RK_REG + q): q = RG_DIRECT + j whole rings of M = 2^(8 + j) points, RG_BLUE + j whole-ring Bluestein of
+// M points (j = 0 .. 5), RG_SPLIT + j two half-length Bluestein transforms of 4096 and 8192 points (j = 0, 1)
+enum { RK_P2 = 0, RK_BF = 1, RK_BL = 2, RK_REG = 3, RING_KINDS = 17 };
+enum { RG_DIRECT = 0, RG_BLUE = 6, RG_SPLIT = 12, RG_N = 14 };
 // ring blocks a class-split adjoint may write beyond the unsplit layout (each of up to two further
 // spin and two further scalar parts rounds up by at most one block)
 constexpr int LIVE_NRB_EXTRA = 4;
@@ -170,10 +172,7 @@ struct Plan {
     int *d_lof = nullptr;  // l of every alm index
     int *d_order_p2 = nullptr, *d_order_bl = nullptr, *d_order_bf = nullptr;
     int n_p2 = 0, n_bl = 0, n_bf = 0, maxM_p2 = 1, maxM_bl = 1, maxM_bf = 1;
-    // rings of the register engine (transform length 4096 or 8192): [0] direct M = 4096, [1] direct
-    // 8192, [2] whole-ring Bluestein M = 4096, [3] 8192, [4] two-half Bluestein M = 4096, [5] 8192
-    int *d_order_r[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-    int n_r[6] = {0, 0, 0, 0, 0, 0};
+    int *d_order_r[RG_N] = {};  // rings of the register engine by list
     void *d_bhatr64 = nullptr, *d_bhatr32 = nullptr;  // their chirp spectra in register order
     std::vector<RingInfo> h_rings;
 
@@ -409,6 +408,8 @@ void launch_epilogue_batched(Plan &P, int q, const double *kern, const double *l
 // chirp spectra of the Bluestein sub lengths Ls (FFT lengths Ms, table offsets ofs; device arrays)
 void launch_bhat(Plan &P, const int *Ls, const int *Ms, const int64_t *ofs, int n, int maxM);
 void launch_bhat_reorder(Plan &P, int logm, const int64_t *src_ofs, const int64_t *dst_ofs, int n);
+void launch_bhat_reorder_f64(Plan &P, int logm, const int64_t *src_ofs, const int64_t *dst_ofs, int n);
+void launch_bhat_reorder_f32(Plan &P, int logm, const int64_t *src_ofs, const int64_t *dst_ofs, int n);
 // weights W = mask * ninv, plus the sums needed for lambda_eff / P and input validation; right-hand
 // side r reads the N^-1 map r mod ncount of ninv ([ncount][npix])
 void launch_weights(Plan &P, const double *ninv, const uint8_t *mask, int nrhs, int ncount);

@@ -462,11 +462,12 @@ static void free_plan(Plan *P)
     void *ptrs[] = {P->d_rings, P->d_pair_z, P->d_coef64, P->d_coef64s, P->d_sa, P->d_sc, P->d_sten, P->d_lm, P->d_rec_spin,
                     P->d_seed2, P->d_seedm2, P->d_seedk,
                     P->d_ent, P->d_entk, P->d_entl, P->d_wgstart, P->d_wgstart_b, P->d_coef32d, P->d_brec, P->d_brec_spin,
-                    P->d_tw64, P->d_tw32, P->d_bhat64, P->d_bhat32, P->d_bhatr64, P->d_bhatr32, P->d_order_r[0], P->d_order_r[1],
-                    P->d_order_r[2], P->d_order_r[3], P->d_order_r[4], P->d_order_r[5], P->d_lof, P->d_order_p2, P->d_order_bl, P->d_order_bf, P->d_FG, P->d_part, P->d_rec, P->d_W, P->d_kern, P->d_kuser, P->d_red, P->d_red_cg, P->d_scal, P->d_flag, P->d_x, P->d_r,
+                    P->d_tw64, P->d_tw32, P->d_bhat64, P->d_bhat32, P->d_bhatr64, P->d_bhatr32, P->d_lof, P->d_order_p2, P->d_order_bl, P->d_order_bf, P->d_FG, P->d_part, P->d_rec, P->d_W, P->d_kern, P->d_kuser, P->d_red, P->d_red_cg, P->d_scal, P->d_flag, P->d_x, P->d_r,
                     P->d_p, P->d_w, P->d_b, P->d_xs, P->d_cmp, P->d_spec, P->d_gl_all, P->d_live_lists,
                     P->d_ring_live};
     for (void *q : ptrs)
+        if (q) (void)hipFree(q);
+    for (int *q : P->d_order_r)
         if (q) (void)hipFree(q);
     if (P->h_pin) (void)hipHostFree(P->h_pin);
     if (P->h_live) (void)hipHostFree(P->h_live);
@@ -514,40 +515,53 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     // ring launch lists, largest first: power-of-two rings (whole-ring FFT), rings whose whole-ring
     // Bluestein convolution fits in LDS (M <= BF_MAXM), and the rest as two sub-transforms of length
     // N / 2, each by Bluestein (M <= 8192 since N <= 4 nside <= 8192)
-    // Rings whose transform length is 4096 or 8192 (a whole power-of-two ring, or a whole-ring
-    // Bluestein convolution) go to the register engine unless it is switched off.
+    // The register engine, unless it is switched off, takes the rings whose transform length M is 4096
+    // or 8192, and those of M = 256 to 2048 with at most about eight orders per bin (2 lmax + 1 <= 8 N:
+    // its threads fold a bin alone; the LDS kernels fold shorter rings with the whole workgroup.  Taking
+    // every ring, synthesis and adjoint of all rings at Nside 300, lmax 750 took 433 us, with this bound 375).
+    // Power-of-two rings below 256 pixels go through Bluestein there.
     const int BF_MAXM = g_ring_whole_maxm;
-    std::vector<int> p2, bl, bf, rl[6];
+    std::vector<int> p2, bl, bf, rl[RG_N];
     int maxp2 = 1, maxbl = 1, maxbf = 1, maxreg = 1;  // the LDS kernels' lists, and the register engine
+    auto log2i = [](int m) { return 31 - __builtin_clz((unsigned)m); };
     for (int r = 0; r < P->nrings; ++r) {
         RingInfo &ri = P->h_rings[r];
+        const int N = ri.nphi;
+        int MF = 256;  // whole-ring convolution length, at least the engine's smallest
+        while (MF < 2 * N - 1) MF <<= 1;
+        const bool few = g_ring_register && 2 * lmax + 1 <= 8 * N;
         if (!ri.M) {
-            if (g_ring_register && (ri.nphi == 4096 || ri.nphi == 8192)) {
-                rl[ri.nphi == 4096 ? 0 : 1].push_back(r);
-                maxreg = std::max(maxreg, ri.nphi);
+            if (N <= 8192 && ((few && N >= 256) || (g_ring_register && N >= 4096))) {
+                rl[RG_DIRECT + log2i(N) - 8].push_back(r);
+                maxreg = std::max(maxreg, N);
+            } else if (few && N < 256 && MF <= BF_MAXM) {
+                ri.M = MF;
+                rl[RG_BLUE + log2i(MF) - 8].push_back(r);
+                maxreg = std::max(maxreg, MF);
             } else {
                 p2.push_back(r);
                 maxp2 = std::max(maxp2, ri.sub);
             }
             continue;
         }
-        int MF = 1;
-        while (MF < 2 * ri.nphi - 1) MF <<= 1;
-        if (MF <= BF_MAXM) {
-            ri.M = MF;  // the whole ring's convolution length
-            if (g_ring_register && (MF == 4096 || MF == 8192)) {
-                rl[MF == 4096 ? 2 : 3].push_back(r);
+        int M1 = 1;
+        while (M1 < 2 * N - 1) M1 <<= 1;
+        if (M1 <= BF_MAXM) {
+            const bool reg = g_ring_register && MF <= BF_MAXM && MF <= 8192 && (few || M1 >= 4096);
+            ri.M = reg ? MF : M1;  // the whole ring's convolution length
+            if (reg) {
+                rl[RG_BLUE + log2i(MF) - 8].push_back(r);
                 maxreg = std::max(maxreg, MF);
             } else {
                 bf.push_back(r);
-                maxbf = std::max(maxbf, MF);
+                maxbf = std::max(maxbf, M1);
             }
         } else {
             int M2 = 1;
-            while (M2 < ri.nphi - 1) M2 <<= 1;  // 2 (N / 2) - 1
+            while (M2 < N - 1) M2 <<= 1;  // 2 (N / 2) - 1
             ri.M = M2;
             if (g_ring_register && (M2 == 4096 || M2 == 8192)) {
-                rl[M2 == 4096 ? 4 : 5].push_back(r);
+                rl[RG_SPLIT + (M2 == 4096 ? 0 : 1)].push_back(r);
                 maxreg = std::max(maxreg, M2);
             } else {
                 bl.push_back(r);
@@ -560,11 +574,10 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     std::stable_sort(bl.begin(), bl.end(), bysize);
     std::stable_sort(bf.begin(), bf.end(), bysize);
     for (auto &v : rl) std::stable_sort(v.begin(), v.end(), bysize);
-    for (int q = 0; q < 6; ++q) P->n_r[q] = (int)rl[q].size();
     P->h_order[RK_P2] = p2;
     P->h_order[RK_BF] = bf;
     P->h_order[RK_BL] = bl;
-    for (int q = 0; q < 6; ++q) P->h_order[RK_REG + q] = rl[q];
+    for (int q = 0; q < RG_N; ++q) P->h_order[RK_REG + q] = rl[q];
     P->n_p2 = (int)p2.size();
     P->n_bl = (int)bl.size();
     P->n_bf = (int)bf.size();
@@ -593,23 +606,23 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         };
         for (int r : bl) key(r, P->h_rings[r].nphi / 2);
         for (int r : bf) key(r, P->h_rings[r].nphi);
-        for (int q = 2; q < 6; ++q)
-            for (int r : rl[q]) key(r, q < 4 ? P->h_rings[r].nphi : P->h_rings[r].nphi / 2);
+        for (int q = RG_BLUE; q < RG_N; ++q)
+            for (int r : rl[q]) key(r, q < RG_SPLIT ? P->h_rings[r].nphi : P->h_rings[r].nphi / 2);
     }
-    // the register engine's chirp spectra in register order, one per distinct transformed length
-    // (lists 2 and 4 transform in 4096 points, 3 and 5 in 8192)
-    std::vector<int64_t> rsrc[2], rdst[2];
+    // the register engine's chirp spectra in register order, one per distinct transformed length, by
+    // the length of the convolution
+    std::vector<int64_t> rsrc[6], rdst[6];
     int64_t rtot = 0;
     {
         std::vector<int64_t> at(4 * (size_t)P->nside + 1, -1);
-        for (int q = 2; q < 6; ++q)
+        for (int q = RG_BLUE; q < RG_N; ++q)
             for (int r : rl[q]) {
                 RingInfo &ri = P->h_rings[r];
-                const int len = q < 4 ? ri.nphi : ri.nphi / 2;
+                const int len = q < RG_SPLIT ? ri.nphi : ri.nphi / 2;
                 if (at[len] < 0) {
                     at[len] = rtot;
-                    rsrc[(q & 1) ? 1 : 0].push_back(ri.bofs);
-                    rdst[(q & 1) ? 1 : 0].push_back(rtot);
+                    rsrc[log2i(ri.M) - 8].push_back(ri.bofs);
+                    rdst[log2i(ri.M) - 8].push_back(rtot);
                     rtot += ri.M;
                 }
                 ri.rofs = at[len];
@@ -678,12 +691,12 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         AK_TRY(upload((void **)&P->d_order_p2, p2.data(), p2.size() * sizeof(int), *P));
         AK_TRY(upload((void **)&P->d_order_bl, bl.data(), bl.size() * sizeof(int), *P));
         AK_TRY(upload((void **)&P->d_order_bf, bf.data(), bf.size() * sizeof(int), *P));
-        for (int q = 0; q < 6; ++q)
+        for (int q = 0; q < RG_N; ++q)
             if (!rl[q].empty()) AK_TRY(upload((void **)&P->d_order_r[q], rl[q].data(), rl[q].size() * sizeof(int), *P));
         P->rs_all.order[RK_P2] = P->d_order_p2;
         P->rs_all.order[RK_BF] = P->d_order_bf;
         P->rs_all.order[RK_BL] = P->d_order_bl;
-        for (int q = 0; q < 6; ++q) P->rs_all.order[RK_REG + q] = P->d_order_r[q];
+        for (int q = 0; q < RG_N; ++q) P->rs_all.order[RK_REG + q] = P->d_order_r[q];
         for (int k = 0; k < RING_KINDS; ++k) P->rs_all.n[k] = (int)P->h_order[k].size();
         // every group in one list (the transforms without weights), polar groups first
         std::vector<int> ids(P->ng64);
@@ -766,7 +779,7 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         AK_TRY(alloc(&P->d_bhatr64, (size_t)rtot * sizeof(double2), *P));
         AK_TRY(alloc(&P->d_bhatr32, (size_t)rtot * sizeof(float2), *P));
         bool ok = true;
-        for (int q = 0; q < 2 && ok; ++q) {
+        for (int q = 0; q < 6 && ok; ++q) {
             const size_t nb = rsrc[q].size();
             if (!nb) continue;
             int64_t *dS = nullptr, *dD = nullptr;
@@ -775,7 +788,7 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
                  hipMemcpy(dS, rsrc[q].data(), nb * sizeof(int64_t), hipMemcpyHostToDevice) == hipSuccess &&
                  hipMemcpy(dD, rdst[q].data(), nb * sizeof(int64_t), hipMemcpyHostToDevice) == hipSuccess;
             if (ok) {
-                launch_bhat_reorder(*P, q ? 13 : 12, dS, dD, (int)nb);
+                launch_bhat_reorder(*P, 8 + q, dS, dD, (int)nb);
                 ok = hipGetLastError() == hipSuccess && hipStreamSynchronize(P->stream) == hipSuccess;
             }
             for (void *d : {(void *)dS, (void *)dD})
