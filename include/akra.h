@@ -251,7 +251,7 @@ akra_status akra_plan_set_graph(akra_plan plan, int on);
 /*
  * Launch shapes of the Legendre kernels (chosen by the autotuner; results do not depend on them
  * beyond the rounding order of the adjoint's ring sums):
- *   syn_variant  0 two steps per trip, 1 four steps per trip with look-ahead loads
+ *   syn_variant  0 or 1: kept and reported, both run the same kernel
  *   syn_rings    ring pairs per lane of the synthesis (1, 2, 4)
  *   adj_rings, adj_waves, adj_chunk   ring pairs per lane, waves per workgroup and l-chunk of the
  *                adjoint: (R,1,8) and (R,1,4) for R = 1..8, and (1,2,8) (1,4,8) (2,2,8) (2,4,8)
@@ -263,8 +263,8 @@ akra_status akra_plan_set_graph(akra_plan plan, int on);
  * akra_plan_get_tuning writes the five current values to out5 (HOST).
  * These shapes apply to every group of an unweighted transform and to the ring groups weighted on
  * both sides in weighted applies (see akra_plan_set_skip_unweighted); akra_plan_set_tuning_one_sided
- * sets the same five values for the groups weighted on one side only (their contraction has half
- * the FMAs per loaded record or adjoint chunk, so another shape can pay), with the same rules, and
+ * sets the same five values for the groups weighted on one side only (they read half the values
+ * of the Fourier coefficients, so another shape can pay), with the same rules, and
  * akra_plan_get_tuning_one_sided reads them.  A new plan starts with both equal.
  */
 akra_status akra_plan_set_tuning(akra_plan plan, int syn_variant, int syn_rings, int adj_rings, int adj_waves,

@@ -201,10 +201,10 @@ struct Plan {
                                              // batched kernels per right-hand side
 
     // Legendre launch shapes
-    int syn_R = 1, syn_V = 1, syn_groups = 1;
+    int syn_R = 1, syn_V = 1, syn_groups = 1;  // syn_V: kept and reported, selects nothing
     int adj_R = 1, adj_W = 1, adj_L = 8, adj_nrb = 1;
     // the shapes of groups weighted on one side only (GCLS_NORTH, GCLS_SOUTH), tuned apart: they
-    // contract with half the FMAs per loaded record or chunk
+    // read half the values of F or G
     int syn_R1 = 1, syn_V1 = 1, adj_R1 = 1, adj_W1 = 1, adj_L1 = 8;
     size_t part_rb_cap = 1;  // ring blocks the partial-sum buffer holds
     int spin_groups = 0;  // the first spin_groups 64-pair groups run the spin form

@@ -109,9 +109,11 @@ __global__ __launch_bounds__(256) void k_prologue(const double2 *__restrict__ xE
     const double2 *pE = xE + rhs * nalm, *pB = xB + rhs * nalm;
     double q[4];
     stencil_in(pE, pB, kern, sten, l, m, lmax, nalm, i, q);
-    const double s = sc[e];
     double *r = rec + (rhs * rec_stride + e) * 5;
-    r[0] = sa[e];
+    // in the signs of the synthesis (see there)
+    const int j = (l - m) & 3;
+    const double s = (j & 2) ? -sc[e] : sc[e];
+    r[0] = (j & 1) ? -sa[e] : sa[e];
 #pragma unroll
     for (int t = 0; t < 4; ++t) r[1 + t] = s * q[t];
     if (rsp && l <= lmax) {

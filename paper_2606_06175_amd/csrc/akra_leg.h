@@ -252,43 +252,63 @@ template <int R> __device__ __forceinline__ bool pending(int l, int lmax, const 
 //   F(m) = -(S_q + i S_u) / sin^2,   F(-m) = -(conj S_q + i conj S_u) / sin^2.
 // The south ring of a pair takes the terms of odd l + m with the other sign: a two-sided class keeps
 // the sums of even and odd l + m apart, a one-sided class sums all in one.  One wave handles the 64 R
-// ring pairs of R list entries of one m: lane = pair, slot j = glist[w R + j] of wave w; the records are
-// wave-uniform, one scalar load of 40 bytes per degree that R pairs share.  V picks two (0) or four (1)
-// degrees per trip.  Bound by vector issue, six instructions per pair and degree: over all rings 5.5 ms
-// at Nside 2048, lmax 4096 (spin form: 11.1 ms), 0.80 of the FMA rate; 0.137 ms at Nside 512, lmax 1024
-// (0.22 ms).
+// ring pairs of R list entries of one m: lane = pair, slot j = glist[w R + j] of wave w.  The records are the
+// same for all lanes: lane n of every row of 16 loads that of degree l + n, 16 degrees ahead, and the FMAs
+// take theirs from lane n of the row (a DPP operand, which costs no issue slot).  As scalar loads, whose
+// wait covers all of them in flight, they could lead by two degrees only, and a wave waited for memory 64 to
+// 73 % of its time where few waves share a SIMD.  Signs: with s = (+ + - -) over (l - m) mod 4, c and p hold s_l mu_l
+// and s_l mu_{l-1}, and the records carry s_l and s_l s_{l+1}, so the recurrence is an accumulation,
+//   p <- p + a (x c), then c and p change places.
+// Bound by vector issue, six instructions per pair and degree: over all rings 5.6 ms at Nside 2048, lmax 4096,
+// 0.80 of the FMA rate (5.6 with scalar loads, 11.1 in the spin form); Nside 512, lmax 1024 0.133 ms (0.141;
+// 0.22), one ring of each pair 0.151 (0.198); northern footprint 75 || 57 us (115 || 109); Nside 256 0.054 (0.060).
 // ================================================================================================
 struct SRec {
     double a, q0, q1, u0, u1;  // a' of the scaled recurrence, c_l times Re q, Im q, Re u, Im u
 };
-struct SynSrc {
-    const_as<double> *r;
-    __device__ __forceinline__ explicit SynSrc(const double *p) : r(uniform_ptr(p)) {}
-    __device__ __forceinline__ SRec at(int i) const
-    {
-        SRec s;
-        s.a = r[5 * i];
-        s.q0 = r[5 * i + 1];
-        s.q1 = r[5 * i + 2];
-        s.u0 = r[5 * i + 3];
-        s.u1 = r[5 * i + 4];
-        return s;
-    }
-    __device__ __forceinline__ void adv(int n) { r += 5 * n; }
-};
 
-template <int R>
-__device__ __forceinline__ void syn_step(const SRec &in, const double (&x)[R], double (&c)[R], double (&p)[R],
+// acc += r[lane N of the row] * c: the DPP operand of the FMA broadcasts within each row of 16 lanes
+template <int N> __device__ __forceinline__ void fma_row(double &acc, double r, double c)
+{
+    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(r), "v"(c), "n"(N));
+}
+// r's last write to its registers is two wait states back (a DPP operand's hazard after a vector write)
+__device__ __forceinline__ void settle(SRec &r)
+{
+    asm volatile("s_nop 1" : "+v"(r.a), "+v"(r.q0), "+v"(r.q1), "+v"(r.u0), "+v"(r.u1));
+}
+
+// degree l + N of R pairs, r the records of l .. l + 15 in the lanes of each row
+template <int N, int R>
+__device__ __forceinline__ void syn_step(const SRec &r, const double (&x)[R], double (&c)[R], double (&p)[R],
                                          double (&acc)[4][R])
 {
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-        acc[0][j] = fma(c[j], in.q0, acc[0][j]);
-        acc[1][j] = fma(c[j], in.q1, acc[1][j]);
-        acc[2][j] = fma(c[j], in.u0, acc[2][j]);
-        acc[3][j] = fma(c[j], in.u1, acc[3][j]);
-        rstep_0(in.a, x[j], c[j], p[j]);
+        const double t = x[j] * c[j];
+        fma_row<N>(acc[0][j], r.q0, c[j]);
+        fma_row<N>(acc[1][j], r.q1, c[j]);
+        fma_row<N>(acc[2][j], r.u0, c[j]);
+        fma_row<N>(acc[3][j], r.u1, c[j]);
+        fma_row<N>(p[j], r.a, t);
+        const double n = p[j];
+        p[j] = c[j];
+        c[j] = n;
     }
+}
+// the eight degrees l + N .. l + N + 7
+template <int N, int R>
+__device__ __forceinline__ void syn_steps8(const SRec &r, const double (&x)[R], double (&c)[R], double (&p)[R],
+                                           double (&accA)[4][R], double (&accB)[4][R])
+{
+    syn_step<N, R>(r, x, c, p, accA);
+    syn_step<N + 1, R>(r, x, c, p, accB);
+    syn_step<N + 2, R>(r, x, c, p, accA);
+    syn_step<N + 3, R>(r, x, c, p, accB);
+    syn_step<N + 4, R>(r, x, c, p, accA);
+    syn_step<N + 5, R>(r, x, c, p, accB);
+    syn_step<N + 6, R>(r, x, c, p, accA);
+    syn_step<N + 7, R>(r, x, c, p, accB);
 }
 
 template <typename S> __device__ __forceinline__ void syn_store(cplx<S> *f, double s0, double s1, double s2, double s3)
@@ -297,7 +317,7 @@ template <typename S> __device__ __forceinline__ void syn_store(cplx<S> *f, doub
     f[1] = mk<S>((S)(-(s0 + s3)), (S)(s1 - s2));
 }
 
-template <typename S, int R, int V, int CLS>
+template <typename S, int R, int CLS>
 __device__ __forceinline__ void syn_body(const double *__restrict__ recs, int64_t rec_stride, cplx<S> *__restrict__ FG,
                                          int64_t fg_stride, const Ent64 *__restrict__ ent,
                                          const int *__restrict__ entk, const int *__restrict__ entl, int ng64,
@@ -329,7 +349,10 @@ __device__ __forceinline__ void syn_body(const double *__restrict__ recs, int64_
         const int refl = REFL ? (((l + m) & 1) ? -1 : 1) : 0;
 #pragma unroll
         for (int j = 0; j < R; ++j)
-            if (e[j] == l && pr[j] < npairs) load_entry_scalar(ent, entk, row + pr[j], refl, c[j], p[j], k[j]);
+            if (e[j] == l && pr[j] < npairs) {
+                load_entry_scalar(ent, entk, row + pr[j], refl, c[j], p[j], k[j]);
+                p[j] = -p[j];
+            }
     };
     auto scaled = [&]() {
         bool neg = false;
@@ -349,65 +372,57 @@ __device__ __forceinline__ void syn_body(const double *__restrict__ recs, int64_
     if (ls <= lend) enter(ls);
     // Lanes whose scale exponent is still negative ("ramp") run the same unmasked steps: their
     // scaled values accumulate garbage that is discarded when the lane's exponent reaches zero (its
-    // sums restart there) or at the end; the check runs once per trip of ST steps, which the growth
-    // of the recurrence over ST steps keeps far from overflow.
+    // sums restart there) or at the end; the check runs once per eight steps, which the growth
+    // of the recurrence keeps far from overflow.
     bool pend = R > 1 && pending<R>(ls, lend, e);
     bool ramp = scaled();
-    constexpr int ST = V == 0 ? 2 : 4;
-    int l = __builtin_amdgcn_readfirstlane(ls <= lend ? ls : lend + 1);
-    SynSrc rp(rec + (int64_t)5 * l);
-    // entries are m + 8 q, so l + m is even at the start of every trip
+    // entries are m + 8 q, so l + m is even at the start of every eight degrees
     double(&accB)[4][R] = TWO ? acc1 : acc0;
-    SRec a0 = rp.at(0), a1 = rp.at(1), b0 = a0, b1 = a1;
-    for (; l + ST - 1 <= lend; l += ST, rp.adv(ST)) {
-        if (pend) {
-            enter(l);
-            pend = pending<R>(l, lend, e);
-            ramp = ramp || scaled();
-        }
-        if constexpr (ST == 4) {
-            // Scalar loads return out of order, so the wait before a record's first use covers
-            // every load then in flight: each pair's loads are issued after the first step of the
-            // pair before it (the scheduling barriers keep them there) and have that pair's second
-            // step to arrive.
-            syn_step<R>(a0, x, c, p, acc0);
-            __builtin_amdgcn_sched_barrier(0);
-            b0 = rp.at(2);
-            b1 = rp.at(3);
-            __builtin_amdgcn_sched_barrier(0);
-            syn_step<R>(a1, x, c, p, accB);
-            __builtin_amdgcn_sched_barrier(0);
-            syn_step<R>(b0, x, c, p, acc0);
-            __builtin_amdgcn_sched_barrier(0);
-            a0 = rp.at(4);
-            a1 = rp.at(5);
-            __builtin_amdgcn_sched_barrier(0);
-            syn_step<R>(b1, x, c, p, accB);
-        } else {
-            syn_step<R>(a0, x, c, p, acc0);
-            syn_step<R>(a1, x, c, p, accB);
-            a0 = rp.at(2);
-            a1 = rp.at(3);
-        }
-        if (ramp) {
-            bool neg = false;
-            double no = 0.0;
+    auto load = [&](int l) {
+        const int i = l + (lane & 15);
+        const double *r = rec + (int64_t)5 * (i < lend ? i : lend);
+        SRec s;
+        s.a = r[0];
+        s.q0 = r[1];
+        s.q1 = r[2];
+        s.u0 = r[3];
+        s.u1 = r[4];
+        return s;
+    };
+    auto before = [&](int l) {
+        if (!pend) return;
+        enter(l);
+        pend = pending<R>(l, lend, e);
+        ramp = ramp || scaled();
+    };
+    auto after = [&]() {
+        if (!ramp) return;
+        bool neg = false;
+        double no = 0.0;
 #pragma unroll
-            for (int j = 0; j < R; ++j) {
-                if (k[j] < 0 && rescale_slot<FORM_SCALAR>(c[j], p[j], no, no, k[j])) {
+        for (int j = 0; j < R; ++j) {
+            if (k[j] < 0 && rescale_slot<FORM_SCALAR>(c[j], p[j], no, no, k[j])) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) acc0[q][j] = acc1[q][j] = 0.0;
-                }
-                neg |= (k[j] < 0);
+                for (int q = 0; q < 4; ++q) acc0[q][j] = acc1[q][j] = 0.0;
             }
-            ramp = wave_any(neg);
+            neg |= (k[j] < 0);
         }
-    }
-    // tail (fewer than ST steps)
-    for (int t = 0; l <= lend; ++l, ++t, rp.adv(1)) {
-        if (pend) enter(l);
-        if (t & 1) syn_step<R>(rp.at(0), x, c, p, accB);
-        else syn_step<R>(rp.at(0), x, c, p, acc0);
+        ramp = wave_any(neg);
+    };
+    int l = __builtin_amdgcn_readfirstlane(ls <= lend ? ls : lend + 1);
+    SRec r = load(l);
+    for (; l <= lend; l += 16) {
+        if (l + 15 > lend && l + (lane & 15) > lend) r.a = r.q0 = r.q1 = r.u0 = r.u1 = 0.0;
+        SRec n = load(l + 16);
+        settle(r);
+        before(l);
+        syn_steps8<0, R>(r, x, c, p, acc0, accB);
+        after();
+        if (l + 8 > lend) break;
+        before(l + 8);
+        syn_steps8<8, R>(r, x, c, p, acc0, accB);
+        after();
+        r = n;
     }
     cplx<S> *Fb = FG + rhs * fg_stride;
 #pragma unroll
@@ -553,7 +568,7 @@ __device__ __forceinline__ void spin_body(const SpinRec *__restrict__ recs, int6
 
 // Synthesis over a list of 64-pair groups: the first nspin waves of an m run one spin group each, the
 // others R of the ngl scalar groups that follow; four waves per workgroup, nbm workgroups per m.
-template <typename S, int R, int V, int CLS>
+template <typename S, int R, int CLS>
 __global__ __launch_bounds__(256) void k_leg_synth(const double *__restrict__ recs, int64_t rec_stride,
                                                    const SpinRec *__restrict__ srecs, int64_t srec_stride,
                                                    const Coef64S *__restrict__ cs64, cplx<S> *__restrict__ FG,
@@ -573,8 +588,8 @@ __global__ __launch_bounds__(256) void k_leg_synth(const double *__restrict__ re
                           uniform_ptr(glist)[w], blockIdx.y, m);
         return;
     }
-    syn_body<S, R, V, CLS>(recs, rec_stride, FG, fg_stride, ent, entk, entl, ng64, pair_z, lmax, npairs, nrings,
-                           glist + nspin, ngl, blockIdx.y, m, li0);
+    syn_body<S, R, CLS>(recs, rec_stride, FG, fg_stride, ent, entk, entl, ng64, pair_z, lmax, npairs, nrings,
+                        glist + nspin, ngl, blockIdx.y, m, li0);
 }
 
 // ================================================================================================
@@ -586,7 +601,9 @@ __global__ __launch_bounds__(256) void k_leg_synth(const double *__restrict__ re
 //   spin form    2h = sum_r 2lambda_lm(theta_r) G_r(m),  -2h = sum_r -2lambda_lm(theta_r) conj(G_r(-m))
 // (south rings through the reflection symmetry).  Each lane sums its R ring pairs in registers; each
 // degree's four sums are added over the four rows of the wave in registers (row_sum4: six lane swaps and
-// three adds), and every L steps of l the sixteen partials per output and wave go through LDS.  With
+// three adds), and every L steps of l the sixteen partials per output and wave go through LDS; a single-wave workgroup sums
+// them during the next L steps (waiting for them at once: 0.097 ms against 0.087 at Nside 256, lmax 512, and
+// 5 % of a 512 mixed solve).  With
 // every lane's partials through LDS instead (four writes and four reads per degree), the LDS time of a
 // degree was that of five to six ring pairs' FMAs and did not hide behind them.  Adjoint and epilogue
 // over all rings: Nside 2048, lmax 4096, 4 pairs per lane 10.7 -> 9.2 ms, 8 pairs 8.5 -> 7.9 ms (spin
@@ -838,6 +855,26 @@ __device__ __forceinline__ void adj_body(double *__restrict__ red, const cplx<S>
     };
 #pragma unroll
     for (int li = 0; li < L; ++li) ldc(li, cca[li], ccb[li]);
+    // sums over the 16 W partials of an output: thread (o, gi) reads the entries gi + G u of output o
+    // (wave / 16, partial % 16) at compile-time offsets, adds them in four independent partial
+    // sums, then sums over the G adjacent threads sharing the output with DPP lane moves
+    double rv[L], sc = 1.0;
+    auto read = [&]() {
+#pragma unroll
+        for (int u = 0; u < L; ++u) rv[u] = col[(G * u / 16) * 64 + (G * u) % 16];
+    };
+    auto finish = [&](int l, double c_l) {
+        double ps[4];
+#pragma unroll
+        for (int u = 0; u < L; ++u) {
+            if (u < 4) ps[u] = rv[u];
+            else ps[u & 3] += rv[u];
+        }
+        const double s = group_sum<G>((ps[0] + ps[1]) + (ps[2] + ps[3]));
+        if (gi == 0 && l >= ls && l + oli <= lend) pout[(int64_t)(l - ls) * 4] = (S)(SPIN ? s * c_l : s);
+    };
+#pragma unroll
+    for (int u = 0; u < L; ++u) rv[u] = 0.0;
     for (int lc = ls; lc <= lend; lc += L, cp += SPIN ? L : 0, sp += SPIN ? 0 : L) {
         if (pend) {
             enter(lc);
@@ -856,12 +893,20 @@ __device__ __forceinline__ void adj_body(double *__restrict__ red, const cplx<S>
 #pragma unroll
         for (int li = 0; li < L; ++li) ldc(L + li, nca[li], ncb[li]);
         // c_l of this thread's output row in the spin form (a vector load, used at the store)
-        double sc = 1.0;
+        const double scp = sc;
         if constexpr (SPIN) sc = cs64[base + (lc + oli < lmax ? lc + oli : lmax)].c;
         // all L steps unmasked: rows past lend (last chunk) are reduced but not stored, and the
         // coefficient table is padded past its last column
 #pragma unroll
         for (int li = 0; li < L; li += 2) {
+            // A single-wave workgroup reads a chunk's partials as soon as they are written and sums them
+            // in the middle of the next chunk's steps (its LDS accesses execute in order, so the next
+            // writes cannot pass the reads)
+            if (W == 1 && li == L / 2) {
+                __builtin_amdgcn_sched_barrier(0);
+                finish(lc - L, scp);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             double out[4];
             adj_step<FORM, R, false, CLS>(cca[li], ccb[li], x, c, p, cm, pm, ga, gb, out);
             rw[li * CS] = row_sum4(out);
@@ -869,19 +914,8 @@ __device__ __forceinline__ void adj_body(double *__restrict__ red, const cplx<S>
             rw[(li + 1) * CS] = row_sum4(out);
         }
         wg_lds_sync<W>();
-        // sums over the 16 W partials of an output: thread (o, gi) reads the entries gi + G u of output o
-        // (wave / 16, partial % 16) at compile-time offsets, adds them in four independent partial
-        // sums, then sums over the G adjacent threads sharing the output with DPP lane moves
-        double rv[L], ps[4];
-#pragma unroll
-        for (int u = 0; u < L; ++u) rv[u] = col[(G * u / 16) * 64 + (G * u) % 16];
-#pragma unroll
-        for (int u = 0; u < L; ++u) {
-            if (u < 4) ps[u] = rv[u];
-            else ps[u & 3] += rv[u];
-        }
-        const double s = group_sum<G>((ps[0] + ps[1]) + (ps[2] + ps[3]));
-        if (gi == 0 && lc + oli <= lend) pout[(int64_t)(lc - ls) * 4] = (S)(SPIN ? s * sc : s);
+        read();
+        if (W > 1) finish(lc, sc);
 #pragma unroll
         for (int li = 0; li < L; ++li) {
             cca[li] = nca[li];
@@ -900,6 +934,7 @@ __device__ __forceinline__ void adj_body(double *__restrict__ red, const cplx<S>
         }
         wg_lds_sync<W>();
     }
+    if (W == 1) finish(ls + (lend - ls) / L * L, sc);
 }
 
 // Adjoint over a list of 64-pair groups, the first nspin of them (nearest the poles) in the spin form.
@@ -948,20 +983,19 @@ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // orders per XCD of a launch placed by xcd_map: 8 of them cover 32 ceil((lmax + 1) / 32) >= lmax + 1
 inline int64_t xcd_slots(int lmax) { return 4 * cdiv(lmax + 1, 32); }
 
-template <typename S, int R, int V, int CLS>
+template <typename S, int R, int CLS>
 void syn_launch(Plan &P, int nrhs, const int *list, int nspin, int nmain)
 {
     const int64_t fg_stride = (int64_t)P.nrings * (P.lmax + 1) * 2;
     const int nbm = (int)cdiv(nspin + cdiv(nmain, R), 4);  // workgroups per m
     dim3 g((unsigned)(8 * nbm * xcd_slots(P.lmax)), nrhs);
-    k_leg_synth<S, R, V, CLS><<<g, 256, 0, P.stream>>>(
+    k_leg_synth<S, R, CLS><<<g, 256, 0, P.stream>>>(
         P.d_rec, P.rec_stride, (const SpinRec *)P.d_rec_spin, P.nalm + ALM_PAD, P.d_coef64s, (cplx<S> *)P.d_FG,
         fg_stride, P.d_ent, P.d_entk, P.d_entl, P.ng64, P.d_pair_z, P.lmax, P.npairs, P.nrings, list, nspin, nmain, nbm);
 }
 
-// launch shape of a class: the two-sided class takes (syn_V, syn_R, adj_R, adj_W, adj_L), the
-// one-sided classes (syn_V1, syn_R1, adj_R1, adj_W1, adj_L1)
-inline int syn_V_of(const Plan &P, int cls) { return cls == GCLS_BOTH ? P.syn_V : P.syn_V1; }
+// launch shape of a class: the two-sided class takes (syn_R, adj_R, adj_W, adj_L), the
+// one-sided classes (syn_R1, adj_R1, adj_W1, adj_L1)
 inline int syn_R_of(const Plan &P, int cls) { return cls == GCLS_BOTH ? P.syn_R : P.syn_R1; }
 inline void adj_shape_of(const Plan &P, int cls, int &R, int &W, int &L)
 {
@@ -973,13 +1007,10 @@ inline void adj_shape_of(const Plan &P, int cls, int &R, int &W, int &L)
 template <typename S, int CLS>
 void leg_synth_s(Plan &P, int nrhs, const int *list, int nspin, int nmain)
 {
-    const int V = syn_V_of(P, CLS), R = syn_R_of(P, CLS);
-    if (V == 0 && R == 1) syn_launch<S, 1, 0, CLS>(P, nrhs, list, nspin, nmain);
-    else if (V == 0 && R == 2) syn_launch<S, 2, 0, CLS>(P, nrhs, list, nspin, nmain);
-    else if (V == 0) syn_launch<S, 4, 0, CLS>(P, nrhs, list, nspin, nmain);
-    else if (R == 1) syn_launch<S, 1, 1, CLS>(P, nrhs, list, nspin, nmain);
-    else if (R == 2) syn_launch<S, 2, 1, CLS>(P, nrhs, list, nspin, nmain);
-    else syn_launch<S, 4, 1, CLS>(P, nrhs, list, nspin, nmain);
+    const int R = syn_R_of(P, CLS);
+    if (R == 1) syn_launch<S, 1, CLS>(P, nrhs, list, nspin, nmain);
+    else if (R == 2) syn_launch<S, 2, CLS>(P, nrhs, list, nspin, nmain);
+    else syn_launch<S, 4, CLS>(P, nrhs, list, nspin, nmain);
 }
 
 // Legendre synthesis of the groups list[0 .. nspin + nmain) of class CLS: the first nspin are the
