@@ -278,7 +278,7 @@ akra_status akra_plan_get_tuning_one_sided(akra_plan plan, int *out5);
  * 64-pair ring groups (one per wave) per workgroup of the batched synthesis, in {1, 2, 4, 8};
  * adj_waves groups per workgroup of the batched adjoint, in {2, 4, 8}, whose waves are summed in LDS
  * into one partial-sum slab per workgroup (fewer waves: more slabs for the epilogue to add).  The
- * default is (4, 4); results do not depend on the shapes beyond the rounding order of the adjoint's
+ * default is (4, 2); results do not depend on the shapes beyond the rounding order of the adjoint's
  * sums.  Synchronises the plan stream and drops a recorded iteration.  akra_plan_get_tuning_batched
  * writes the two current values to out2 (HOST).  Errors: AKRA_ERR_ARG (other values, or a plan that
  * is not FP32 with several right-hand sides), AKRA_ERR_HIP.

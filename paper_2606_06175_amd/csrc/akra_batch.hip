@@ -242,8 +242,21 @@ __global__ __launch_bounds__(64 * SW) void k_leg_synth_b(const float *__restrict
 // registers: they do not depend on l).  The waves of the block are summed in LDS and one slab per
 // (right-hand side of the group, block) is written, [rhs - rhs0][nrb][next][4], rows from the chunk
 // holding the block's first entry degree (recorded in wgstart) to lmax + 2.
-// AW is a launch shape of the autotuner (2, 4 or 8).
+// AW is a launch shape of the autotuner (2, 4 or 8): fewer waves in step with each other against more slabs for
+// the epilogue; with the epilogue 2 is the better or equal one throughout (all rings, ms: Nside 256, 16
+// right-hand sides 0.48 against 0.52 for 4; 512, 4: 0.52, 0.58; 1024, 16: 8.9, 9.0).  Bound by the chunk's serial
+// path (rows, operands, products, the sum of the waves): 0.38 of the FP32 matrix rate at Nside 512, 0.55 at 1024.
+// Footprint, AW = 4: Nside 256, 16 right-hand sides 170 -> 102 us a group of eight with G loaded in
+// batches and a' by vector loads (scalar loads without look-ahead before), Nside 512, four 373 -> 283 us.
 constexpr int BCH = 64;                // degrees per chunk
+template <int... I, typename F> __device__ __forceinline__ void static_for_(std::integer_sequence<int, I...>, F &&f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F> __device__ __forceinline__ void static_for(F &&f)
+{
+    static_for_(std::make_integer_sequence<int, N>{}, f);
+}
 constexpr int BST = BCH / 2 + 1;       // LDS stride of one pair's rows of one parity (conflict-free writes)
 
 template <int NB, int AW>
@@ -277,35 +290,64 @@ __global__ __launch_bounds__(64 * AW) __attribute__((amdgpu_waves_per_eu(2))) vo
     const int p = g * 64 + lane;
     const bool valid = g >= 0 && p < npairs;
 
-    // B operands: lane j + COLS k holds, for pairs K kk + k, column j of g_1, g_2 over sin^2
+    // B operands: lane j + COLS k holds, for pairs K kk + k, column j of g_1, g_2 over sin^2.  Every lane
+    // prepares 1 / 2 sin^2 and the weight flags of its own pair; the loads of G go out sixteen at a time,
+    // none behind a condition (one pair after the other, with its position, flags and G in turn, they took
+    // half of the kernel at Nside 256).
     const int kq = lane / M::COLS, j = lane % M::COLS, c4 = j & 3, rhs = rhs0 + j / 4;
     float Bp[NK], Bm[NK];
-#pragma unroll
-    for (int kk = 0; kk < NK; ++kk) {
-        Bp[kk] = Bm[kk] = 0.f;
-        const int pk = g * 64 + M::K * kk + kq;
-        if (e > lend || g < 0 || pk >= npairs || rhs >= nrhs) continue;
-        const double z = pair_z[pk], f = 0.5 / ((1.0 - z) * (1.0 + z));
+    double x = valid ? pair_z[p] : 0.0, c = 0, pv = 0;
+    if (g >= 0 && e <= lend) {
+        const double fz = 0.5 / ((1.0 - x) * (1.0 + x));
+        const int rs = nrings - 1 - p;
+        // a ring without weight has G = 0
+        const uint64_t on_n = __ballot(valid && (!live || live[p]));
+        const uint64_t on_s = __ballot(valid && rs != p && (!live || live[rs]));
+        const float2 *F = FG + (int64_t)(rhs < nrhs ? rhs : nrhs - 1) * fg_stride + 2 * m;
         // columns: Re g_1 = (G.x + H.x) / 2, Im g_1 = (G.y - H.y) / 2, Re g_2 = (G.y + H.y) / 2,
         // Im g_2 = (H.x - G.x) / 2 with G = G(m), H = G(-m)
-        auto comp = [&](int ring) {
-            const float2 *fr = FG + rhs * fg_stride + ((int64_t)ring * (lmax + 1) + m) * 2;
-            const float2 G = fr[0], H = fr[1];
-            const double a = (c4 == 0 || c4 == 3) ? H.x : G.y;
-            const double b = c4 == 0 ? G.x : c4 == 3 ? -G.x : c4 == 1 ? -H.y : H.y;
+        auto comp = [&](float4 v, double f) {
+            const double a = (c4 == 0 || c4 == 3) ? v.z : v.y;
+            const double b = c4 == 0 ? v.x : c4 == 3 ? -v.x : c4 == 1 ? -v.w : v.w;
             return f * (a + b);
         };
-        const int rs = nrings - 1 - pk;
-        const double n = !live || live[pk] ? comp(pk) : 0.0;  // a ring without weight has G = 0
-        const double s = rs != pk && (!live || live[rs]) ? comp(rs) : 0.0;
-        Bp[kk] = (float)(n + s);
-        Bm[kk] = (float)(n - s);
+#pragma unroll
+        for (int k0 = 0; k0 < NK; k0 += 8) {
+            float4 vn[8], vs[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int pk = g * 64 + M::K * (k0 + q) + kq, pc = pk < npairs ? pk : npairs - 1;
+                vn[q] = *(const float4 *)(F + (int64_t)pc * (lmax + 1) * 2);
+                vs[q] = *(const float4 *)(F + (int64_t)(nrings - 1 - pc) * (lmax + 1) * 2);
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int i = M::K * (k0 + q) + kq;
+                const double f = __shfl(fz, i, 64);
+                const double n = rhs < nrhs && ((on_n >> i) & 1) ? comp(vn[q], f) : 0.0;
+                const double s = rhs < nrhs && ((on_s >> i) & 1) ? comp(vs[q], f) : 0.0;
+                Bp[k0 + q] = (float)(n + s);
+                Bm[k0 + q] = (float)(n - s);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) Bp[kk] = Bm[kk] = 0.f;
     }
 
-    double x = valid ? pair_z[p] : 0.0, c = 0, pv = 0;
     int k = 0;
     bool ramp = false;
-    const_as<double> *cp = uniform_ptr(sa + base);
+    // a' of the chunk at l: lane n of every row of 16 lanes holds degrees l + 16 i + n, a chunk ahead of
+    // their use (DPP operands of the recurrence, in the signs of the single-vector synthesis)
+    const double *cp = sa + base;
+    auto loadc = [&](int l, double (&o)[4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int li = l + 16 * i + (lane & 15);
+            o[i] = cp[li < lend ? li : lend];
+        }
+    };
     float *le = &lam[wave][0][lane * BST], *lo = &lam[wave][1][lane * BST];
     const int arow = lane / M::ROWS * BST + lane % M::ROWS;
     const float *ae = &lam[wave][0][arow], *ao = &lam[wave][1][arow];
@@ -314,54 +356,65 @@ __global__ __launch_bounds__(64 * AW) __attribute__((amdgpu_waves_per_eu(2))) vo
     auto is_active = [&](int lx) { return lx <= lend && e <= lx + BCH - 1 && e <= lend; };
     // rows t8 .. t8 + 7 of the chunk at lx into the wave's LDS rows (entry degrees are m + 8 q and chunks
     // start at m + 64 j, so an entry falls on a block of 8)
-    auto rows8 = [&](int lx, int t8, auto &&after) {
+    auto rows8 = [&](int lx, auto tc, const double (&cc)[4], auto &&after) {
+        constexpr int t8 = decltype(tc)::value;
         const int l8 = lx + t8;
         if (l8 == e) {
             if (valid) load_entry_scalar(ent, entk, (int64_t)m * npairs + p, 0, c, pv, k);
+            pv = -pv;
             ramp = wave_any(k < 0);
         }
         if (l8 < e || l8 > lend) {
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
+            static_for<8>([&](auto t) {
                 ((t & 1) ? lo : le)[(t8 + t) >> 1] = 0.f;
-                after(t);
-            }
+                after(t8 + t);
+            });
             return;
         }
-        double cc[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) cc[t] = cp[l8 + t];  // padded past the last degree
+        auto step = [&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            const double xc = (t & 1) ? -x * c : x * c;
+            fma_row<(t8 + t) % 16>(pv, cc[(t8 + t) / 16], xc);
+            const double n = pv;
+            pv = c;
+            c = n;
+        };
         if (!ramp && l8 + 7 <= lend) {
             // every lane out of the scaled range and every row in range: no selects, no checks
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                ((t & 1) ? lo : le)[(t8 + t) >> 1] = (float)c;
-                rstep_0(cc[t], x, c, pv);
-                after(t);
-            }
+            static_for<8>([&](auto t) {
+                ((t & 1) ? lo : le)[(t8 + t) >> 1] = (float)((t & 2) ? -c : c);
+                step(t);
+                after(t8 + t);
+            });
             return;
         }
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            ((t & 1) ? lo : le)[(t8 + t) >> 1] = k == 0 && l8 + t <= lend ? (float)c : 0.f;
-            rstep_0(cc[t], x, c, pv);
-            after(t);
-        }
+        static_for<8>([&](auto t) {
+            ((t & 1) ? lo : le)[(t8 + t) >> 1] = k == 0 && l8 + t <= lend ? (float)((t & 2) ? -c : c) : 0.f;
+            step(t);
+            after(t8 + t);
+        });
         // every eight steps (the growth over eight steps stays far from overflow)
         double z = 0;
         if (k < 0) rescale_slot<FORM_SCALAR>(c, pv, z, z, k);
         ramp = wave_any(k < 0);
+    };
+    auto rows = [&](int lx, double (&cc)[4], auto &&after) {
+        settle(cc);
+        static_for<BCH / 8>([&](auto i) { rows8(lx, std::integral_constant<int, 8 * decltype(i)::value>{}, cc, after); });
     };
     // Software pipeline over chunks: the A operands of chunk lc are read from LDS into registers, then
     // the recurrence writes the rows of the next chunk into the same LDS rows while the matrix cores
     // contract chunk lc, one product per row.  A wave reads and writes only its own rows, and its LDS
     // accesses run in program order, so the reads return the rows of chunk lc.
     const int lstart = m + ((ls - m) / BCH) * BCH;
-    if (is_active(lstart)) {
-#pragma unroll
-        for (int t8 = 0; t8 < BCH; t8 += 8) rows8(lstart, t8, [](int) {});
-    }
+    double cc[4], cn[4];
+    loadc(lstart, cc);
+    loadc(lstart + BCH, cn);
+    if (is_active(lstart)) rows(lstart, cc, [](int) {});
     for (int lc = lstart; lc <= lend; lc += BCH) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) cc[i] = cn[i];
+        loadc(lc + 2 * BCH, cn);
         const bool act = is_active(lc), actn = is_active(lc + BCH);
         wg_lds_sync<1>();
         float a[2][RBK][NK];
@@ -389,14 +442,12 @@ __global__ __launch_bounds__(64 * AW) __attribute__((amdgpu_waves_per_eu(2))) vo
         };
         static_assert(2 * RBK * NK == BCH, "one product per row");
         if (act && actn) {
-#pragma unroll
-            for (int t8 = 0; t8 < BCH; t8 += 8) rows8(lc + BCH, t8, [&](int t) { mm(t8 + t); });
+            rows(lc + BCH, cc, [&](int i) { mm(i); });
         } else if (act) {
 #pragma unroll
             for (int i = 0; i < BCH; ++i) mm(i);
         } else if (actn) {
-#pragma unroll
-            for (int t8 = 0; t8 < BCH; t8 += 8) rows8(lc + BCH, t8, [](int) {});
+            rows(lc + BCH, cc, [](int) {});
         }
         // sum over the block's waves in LDS, eight registers at a time
         float o[NO];

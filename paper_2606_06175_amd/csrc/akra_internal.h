@@ -210,7 +210,7 @@ struct Plan {
     int spin_groups = 0;  // the first spin_groups 64-pair groups run the spin form
     // batched matrix-core kernels: waves (64-pair groups) per workgroup of the synthesis and the
     // adjoint; nrb_b adjoint ring blocks of bat_AW groups (the buffers hold those of bat_AW = 2)
-    int bat_SW = 4, bat_AW = 4, nrb_b_cap = 0;
+    int bat_SW = 4, bat_AW = 2, nrb_b_cap = 0;
 
     // workspaces (sized for FP64; FP32 views reuse them)
     void *d_FG = nullptr;       // [nrhs][nrings][lmax+1][2] complex

@@ -257,7 +257,7 @@ template <int R> __device__ __forceinline__ bool pending(int l, int lmax, const 
 // take theirs from lane n of the row (a DPP operand, which costs no issue slot).  As scalar loads, whose
 // wait covers all of them in flight, they could lead by two degrees only, and a wave waited for memory 64 to
 // 73 % of its time where few waves share a SIMD.  Signs: with s = (+ + - -) over (l - m) mod 4, c and p hold s_l mu_l
-// and s_l mu_{l-1}, and the records carry s_l and s_l s_{l+1}, so the recurrence is an accumulation,
+// and s_{l-1} mu_{l-1}, and the records carry s_l and s_l s_{l+1}, so the recurrence is an accumulation,
 //   p <- p + a (x c), then c and p change places.
 // Bound by vector issue, six instructions per pair and degree: over all rings 5.6 ms at Nside 2048, lmax 4096,
 // 0.80 of the FMA rate (5.6 with scalar loads, 11.1 in the spin form); Nside 512, lmax 1024 0.133 ms (0.141;
@@ -273,6 +273,10 @@ template <int N> __device__ __forceinline__ void fma_row(double &acc, double r, 
     asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(r), "v"(c), "n"(N));
 }
 // r's last write to its registers is two wait states back (a DPP operand's hazard after a vector write)
+__device__ __forceinline__ void settle(double (&r)[4])
+{
+    asm volatile("s_nop 1" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
+}
 __device__ __forceinline__ void settle(SRec &r)
 {
     asm volatile("s_nop 1" : "+v"(r.a), "+v"(r.q0), "+v"(r.q1), "+v"(r.u0), "+v"(r.u1));
