@@ -451,6 +451,10 @@ uint32_t *pixelize_keys(Plan &P, int64_t n, void *work, double4 **rec);
 void launch_ang2pix(Plan &P, const double *z, const double *phi, const double *e1, const double *e2, const double *w,
                     int64_t n, uint32_t *pix, double4 *rec);
 // sort by pixel, per-pixel sums in catalogue order and the pixel products (keys and records written)
+bool pixelize_in_buckets(const Plan &P);
+hipError_t launch_pixelize_buckets(Plan &P, const double *z, const double *phi, const double *e1, const double *e2,
+                                   const double *w, int64_t n, double R, double se2, double n_th, void *work,
+                                   double *g1, double *g2, double *ninv, double *neff, uint8_t *mask);
 hipError_t launch_pixelize(Plan &P, int64_t n, double R, double se2, double n_th, void *work, double *g1, double *g2,
                            double *ninv, double *neff, uint8_t *mask);
 bool pow2(int n);

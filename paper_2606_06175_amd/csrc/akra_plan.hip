@@ -2634,15 +2634,22 @@ akra_status akra_pixelize(akra_plan plan, const double *z, const double *phi, co
         return AKRA_ERR_ARG;
     }
     AK_HIP(hipMemsetAsync(P.d_cmp_flag, 0, 2 * sizeof(int), P.stream), "memset");
-    double4 *rec = nullptr;
-    uint32_t *keys = pixelize_keys(P, n_gal, work, &rec);
-    if (!keys) {
-        set_error("radix sort storage query failed");
-        return AKRA_ERR_HIP;
+    const bool buckets = pixelize_in_buckets(P);
+    if (buckets) {
+        AK_HIP(launch_pixelize_buckets(P, z, phi, e1, e2, w, n_gal, R, sigma_e * sigma_e, n_th, work, g1, g2, ninv, neff,
+                                       mask),
+               "pixelize");
+    } else {
+        double4 *rec = nullptr;
+        uint32_t *keys = pixelize_keys(P, n_gal, work, &rec);
+        if (!keys) {
+            set_error("radix sort storage query failed");
+            return AKRA_ERR_HIP;
+        }
+        launch_ang2pix(P, z, phi, e1, e2, w, n_gal, keys, rec);
+        st = check_launch("ang2pix");
+        if (st) return st;
     }
-    launch_ang2pix(P, z, phi, e1, e2, w, n_gal, keys, rec);
-    st = check_launch("ang2pix");
-    if (st) return st;
     int f[2];
     st = read_flags2(P, f);
     if (st) return st;
@@ -2651,6 +2658,7 @@ akra_status akra_pixelize(akra_plan plan, const double *z, const double *phi, co
                        : "a weight is negative or not finite, or an ellipticity is not finite");
         return AKRA_ERR_ARG;
     }
+    if (buckets) return AKRA_OK;  // read_flags2 has waited for the stream
     AK_HIP(launch_pixelize(P, n_gal, R, sigma_e * sigma_e, n_th, work, g1, g2, ninv, neff, mask), "pixelize");
     AK_HIP(hipStreamSynchronize(P.stream), "sync");
     return AKRA_OK;
