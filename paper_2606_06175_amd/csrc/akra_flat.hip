@@ -8,11 +8,12 @@
 // CG on x is CG on z (F is unitary), with two 2-D FFTs per apply instead of four.
 //
 // Layouts: maps are [ny][nx] float64 (i1 fast); the solver's Fourier vectors are stored transposed,
-// [nx][ny] complex (rows indexed by the x frequency n1), so each 2-D transform is one row pass, one
-// tiled transpose and one row pass, and the pixel-space weighting sits between an inverse and a
-// forward row transform of the same row in LDS:
-//   H x:  rows n1: x.D -> iFFT along n2 | transpose | rows i2: iFFT along n1, x W, FFT along i1 |
-//         transpose | rows n1: FFT along i2, x conj(D) / (nx ny), + lambda x.
+// [nx][ny] complex (rows indexed by the x frequency n1), so each 2-D transform is one row pass and
+// one column pass, and the pixel-space weighting sits between an inverse and a forward transform of the
+// same column:
+//   H x:  rows n1: x.D -> iFFT along n2 | columns i2: iFFT along n1, x W, FFT along i1 |
+//         rows n1: FFT along i2, x conj(D) / (nx ny), + lambda x.
+// Where the column pass does not reach (see col_ok) it is a tiled transpose, a row pass and a transpose.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -22,6 +23,7 @@
 
 #include "akra_fft.h"
 #include "akra_internal.h"
+#include "akra_ring16.h"
 
 #define FK_HIP(call, what)                                   \
     do {                                                     \
@@ -34,6 +36,12 @@ namespace akra {
 constexpr int FL_MAXN = 8192;  // longest row a workgroup transforms in LDS (FP64)
 constexpr int FL_RED = 1024;   // partial sums of the dot products
 
+constexpr int FCOL = 4;  // columns of a workgroup of the column pass
+static bool col_ok(int nx, int ny) { return nx >= 256 && nx <= 4096 && ny % FCOL == 0; }
+// row stride of the buffers between row and column passes: 256 bytes over ny, as the rows of one column, a power
+// of two apart, meet few memory channels (the column pass at 4096 x 4096 276 us against 317)
+static int64_t col_stride(int nx, int ny) { return col_ok(nx, ny) ? ny + 16 : ny; }
+
 struct FlatPlan {
     int nx = 0, ny = 0;
     int64_t n = 0;
@@ -42,7 +50,7 @@ struct FlatPlan {
     int twn = 1;
     double *d_W = nullptr;  // [ny][nx]
     double2 *d_x = nullptr, *d_r = nullptr, *d_p = nullptr, *d_w = nullptr, *d_b = nullptr;  // [nx][ny]
-    double2 *d_t1 = nullptr, *d_t2 = nullptr;  // transposition buffers
+    double2 *d_t1 = nullptr, *d_t2 = nullptr;  // between row and column passes, or transpositions
     double *d_red = nullptr, *d_scal = nullptr;
     int *d_flag = nullptr;
     double *h_pin = nullptr;
@@ -76,6 +84,7 @@ struct FRowArgs {
     double *dot_part;           // FR_FWD_OUT: per-row Re sum conj(xadd) out when non-null
     double lam, scale;
     int L;                      // row length (power of two)
+    int64_t is, os;             // row strides of in and out
     int dmode;                  // FR_INV_D / FR_FWD_OUT: 0 times D, 1 times conj(D), -1 none
     int nx, ny;                 // grid: in FR_INV_D / FR_FWD_OUT the row is n1, the position n2
     const double2 *tw;
@@ -95,11 +104,11 @@ __global__ __launch_bounds__(NT) void k_frow(FRowArgs a)
     extern __shared__ double2 buf[];
     const int r = blockIdx.x, L = a.L, tid = threadIdx.x;
     const int logL = 31 - __builtin_clz(L);
-    const int64_t base = (int64_t)r * L;
+    const int64_t base = (int64_t)r * L, bi = r * a.is, bo = r * a.os;
     if constexpr (MODE == FR_INV_D || MODE == FR_PIX_W || MODE == FR_INV_MAPS) {
         // natural order in, inverse transform (sign +1), bit-reversed out
         for (int k = tid; k < L; k += NT) {
-            double2 v = a.in[base + k];
+            double2 v = a.in[bi + k];
             if (MODE == FR_INV_D && a.dmode >= 0) v = cmul<double>(v, dfac(a.dmode, r, a.nx, k, a.ny));
             buf[pd(k)] = v;
         }
@@ -108,7 +117,7 @@ __global__ __launch_bounds__(NT) void k_frow(FRowArgs a)
         if constexpr (MODE == FR_INV_D) {
             for (int k = tid; k < L; k += NT) {
                 const double2 v = buf[pd(brev(k, logL))];
-                a.out[base + k] = make_double2(v.x * a.scale, v.y * a.scale);
+                a.out[bo + k] = make_double2(v.x * a.scale, v.y * a.scale);
             }
         } else if constexpr (MODE == FR_INV_MAPS) {
             for (int k = tid; k < L; k += NT) {
@@ -128,7 +137,7 @@ __global__ __launch_bounds__(NT) void k_frow(FRowArgs a)
             fft_dit<double, NT>(buf, L, a.tw, a.twn, -1);
             for (int k = tid; k < L; k += NT) {
                 const double2 v = buf[pd(k)];
-                a.out[base + k] = make_double2(v.x * a.scale, v.y * a.scale);
+                a.out[bo + k] = make_double2(v.x * a.scale, v.y * a.scale);
             }
         }
     } else {
@@ -142,7 +151,7 @@ __global__ __launch_bounds__(NT) void k_frow(FRowArgs a)
                     v = make_double2(v.x * w, v.y * w);
                 }
             } else {
-                v = a.in[base + k];
+                v = a.in[bi + k];
             }
             buf[pd(brev(k, logL))] = v;
         }
@@ -160,7 +169,7 @@ __global__ __launch_bounds__(NT) void k_frow(FRowArgs a)
                     dot += x.x * v.x + x.y * v.y;
                 }
             }
-            a.out[base + k] = v;
+            a.out[bo + k] = v;
         }
         if constexpr (MODE == FR_FWD_OUT) {
             if (a.dot_part) {
@@ -177,6 +186,92 @@ __global__ __launch_bounds__(NT) void k_frow(FRowArgs a)
                 }
             }
         }
+    }
+}
+
+// Column pass of the transposed layout [nx][ny]: the transforms along x of FCOL neighbouring columns i2 by
+// one workgroup, in place of a transposition, a row pass and (FC_PIX_W) a transposition back.  The register
+// engine of the ring stage (16 points per thread, nx / 16 threads a column) needs LDS for one component of
+// a point only, so four columns of 4096 points fit where the row kernel holds one; neighbouring lanes hold
+// neighbouring columns, and a row of the array is read and written 64 bytes at a time.
+//   FC_PIX_W: inverse transform, times W, forward transform back; FC_MAPS: inverse transform to two real
+//   maps [ny][nx]; FC_FROM_MAPS: two real maps, times W when given, forward transform.
+// Bound by memory: 4096 x 4096, FC_PIX_W 239 us, 0.60 of a copy's rate for its 670 MB
+// (215 + 2 x 106 us with row pass and transpositions; 276 with W read at the positions of the registers).
+// One workgroup of 1024 threads fills a compute unit, so its loads do not run beside its transforms.
+enum { FC_PIX_W = 0, FC_MAPS = 1, FC_FROM_MAPS = 2 };
+template <int LOGM> struct FColShape {
+    static constexpr int NT = R16<LOGM>::NT;
+    // LDS doubles of a column: an odd multiple of 8 apart, so that four columns of eight lanes each spread
+    // over the banks
+    static constexpr int LS = R16<LOGM>::M + R16<LOGM>::M / 32 + (40 - (R16<LOGM>::M + R16<LOGM>::M / 32) % 32) % 32;
+};
+template <int LOGM, int MODE>
+__global__ __launch_bounds__(FCOL *FColShape<LOGM>::NT) void k_fcol(FRowArgs a)
+{
+    using G = R16<LOGM>;
+    constexpr int NT = G::NT, WV = FCOL * NT <= 64 ? 1 : 2;
+    extern __shared__ double cbuf[];
+    // neighbouring workgroups, which share the 128-byte lines, on one XCD
+    const int nb = gridDim.x, b = nb % 8 ? (int)blockIdx.x : (int)((blockIdx.x & 7) * (nb / 8) + (blockIdx.x >> 3));
+    const int c = threadIdx.x % FCOL, t = threadIdx.x / FCOL, col = b * FCOL + c;
+    double *lds = cbuf + c * FColShape<LOGM>::LS;
+    // The columns' rows of the real arrays go through the LDS, natural order on the memory side (element
+    // e = threadIdx.x + i * threads of the FCOL rows), positions brev(pos) on the side of the registers: at those
+    // positions every lane of a load from memory would meet a line of its own.
+    constexpr int TH = FCOL * NT;
+    const int64_t mb = (int64_t)b * FCOL * G::M;
+    auto slot = [&](int i) {
+        const int e = threadIdx.x + i * TH;
+        return e / G::M * FColShape<LOGM>::LS + pd(e % G::M);
+    };
+    const int tp = opaque(t);
+    auto mine = [&](int k) { return pd(brevm<LOGM>(lpos<G::S2>(tp, k))); };
+    auto fetch = [&](const double *p, double *o) {
+        wg_lds_sync<WV>();
+#pragma unroll
+        for (int i = 0; i < 16; ++i) cbuf[slot(i)] = p[mb + threadIdx.x + i * TH];
+        wg_lds_sync<WV>();
+#pragma unroll
+        for (int k = 0; k < 16; ++k) o[k] = lds[mine(k)];
+    };
+    auto store = [&](double *p, auto &&val) {
+        wg_lds_sync<WV>();
+#pragma unroll
+        for (int k = 0; k < 16; ++k) lds[mine(k)] = val(k);
+        wg_lds_sync<WV>();
+#pragma unroll
+        for (int i = 0; i < 16; ++i) p[mb + threadIdx.x + i * TH] = cbuf[slot(i)];
+    };
+    double2 v[16];
+    if constexpr (MODE != FC_FROM_MAPS) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = a.in[(t + NT * k) * a.is + col];
+        fft16_dif<double, LOGM, true, WV>(v, lds, a.tw, a.twn, t, +1);
+    }
+    if constexpr (MODE == FC_MAPS) {
+        store(a.out1, [&](int k) { return v[k].x * a.scale; });
+        store(a.out2, [&](int k) { return v[k].y * a.scale; });
+    } else {
+        double q[16];
+        if constexpr (MODE == FC_FROM_MAPS) {
+            fetch(a.in1, q);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) v[k].x = q[k];
+            fetch(a.in2, q);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) v[k].y = q[k];
+        }
+        if (MODE == FC_PIX_W || a.W) {
+            fetch(a.W, q);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) v[k] = cscale<double>(v[k], q[k]);
+        }
+    }
+    if constexpr (MODE != FC_MAPS) {
+        fft16_dit<double, LOGM, true, WV>(v, lds, a.tw, a.twn, t, -1);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) a.out[(t + NT * k) * a.os + col] = v[k];
     }
 }
 
@@ -376,7 +471,7 @@ template <int MODE> static hipError_t allow_lds()
 static FRowArgs row_args(FlatPlan &F, int L)
 {
     FRowArgs a{};
-    a.L = L;
+    a.L = a.is = a.os = L;
     a.scale = 1.0;
     a.dmode = -1;
     a.nx = F.nx;
@@ -391,6 +486,37 @@ static void transpose(FlatPlan &F, const double2 *in, double2 *out, int R, int C
     k_ftranspose<<<dim3((C + 31) / 32, (R + 31) / 32), 256, 0, F.stream>>>(in, out, R, C);
 }
 
+// The column pass takes nx = 256 to 4096 (the engine's one-column lengths; 8192 points of four columns exceed a
+// workgroup) and ny a multiple of its columns; other grids are transposed, and col_pass returns false.
+template <int MODE> static bool col_pass(FlatPlan &F, FRowArgs a)
+{
+    if (!col_ok(F.nx, F.ny)) return false;
+    a.is = a.os = col_stride(F.nx, F.ny);
+    auto go = [&](auto logm) {
+        constexpr int LOGM = decltype(logm)::value;
+        k_fcol<LOGM, MODE><<<F.ny / FCOL, FCOL * FColShape<LOGM>::NT, FCOL * FColShape<LOGM>::LS * sizeof(double),
+                             F.stream>>>(a);
+        return true;
+    };
+    using std::integral_constant;
+    switch (F.nx) {
+    case 256: return go(integral_constant<int, 8>{});
+    case 512: return go(integral_constant<int, 9>{});
+    case 1024: return go(integral_constant<int, 10>{});
+    case 2048: return go(integral_constant<int, 11>{});
+    default: return go(integral_constant<int, 12>{});
+    }
+}
+template <int MODE> static hipError_t allow_lds_col()
+{
+    hipError_t e = hipFuncSetAttribute((const void *)k_fcol<12, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       FCOL * FColShape<12>::LS * (int)sizeof(double));
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void *)k_fcol<11, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                FCOL * FColShape<11>::LS * (int)sizeof(double));
+    return e;
+}
+
 // x = F (m1 + i m2) [x W] [x conj(D) or D] (unitary), into the transposed layout [nx][ny]
 static void to_fourier(FlatPlan &F, const double *m1, const double *m2, const double *W, int dmode, double2 *x)
 {
@@ -398,11 +524,15 @@ static void to_fourier(FlatPlan &F, const double *m1, const double *m2, const do
     a.in1 = m1;
     a.in2 = m2;
     a.W = W;
-    a.out = F.d_t1;
-    row_pass_nt<FR_FWD_MAPS>(F, a, F.ny);
-    transpose(F, F.d_t1, F.d_t2, F.ny, F.nx);
+    a.out = F.d_t2;
+    if (!col_pass<FC_FROM_MAPS>(F, a)) {
+        a.out = F.d_t1;
+        row_pass_nt<FR_FWD_MAPS>(F, a, F.ny);
+        transpose(F, F.d_t1, F.d_t2, F.ny, F.nx);
+    }
     FRowArgs b = row_args(F, F.ny);
     b.in = F.d_t2;
+    b.is = col_stride(F.nx, F.ny);
     b.out = x;
     b.dmode = dmode;
     b.scale = 1.0 / std::sqrt((double)F.n);
@@ -415,14 +545,17 @@ static void to_maps(FlatPlan &F, const double2 *x, int dmode, double *o1, double
     FRowArgs a = row_args(F, F.ny);
     a.in = x;
     a.out = F.d_t1;
+    a.os = col_stride(F.nx, F.ny);
     a.dmode = dmode;
     row_pass_nt<FR_INV_D>(F, a, F.nx);
-    transpose(F, F.d_t1, F.d_t2, F.nx, F.ny);
     FRowArgs b = row_args(F, F.nx);
-    b.in = F.d_t2;
+    b.in = F.d_t1;
     b.out1 = o1;
     b.out2 = o2;
     b.scale = 1.0 / std::sqrt((double)F.n);
+    if (col_pass<FC_MAPS>(F, b)) return;
+    transpose(F, F.d_t1, F.d_t2, F.nx, F.ny);
+    b.in = F.d_t2;
     row_pass_nt<FR_INV_MAPS>(F, b, F.ny);
 }
 
@@ -432,17 +565,23 @@ static void apply_H(FlatPlan &F, const double2 *x, double2 *y, double lam, doubl
     FRowArgs a = row_args(F, F.ny);
     a.in = x;
     a.out = F.d_t1;
+    a.os = col_stride(F.nx, F.ny);
     a.dmode = 0;
     row_pass_nt<FR_INV_D>(F, a, F.nx);
-    transpose(F, F.d_t1, F.d_t2, F.nx, F.ny);
     FRowArgs b = row_args(F, F.nx);
-    b.in = F.d_t2;
-    b.out = F.d_t1;
+    b.in = F.d_t1;
+    b.out = F.d_t2;
     b.W = F.d_W;
-    row_pass_nt<FR_PIX_W>(F, b, F.ny);
-    transpose(F, F.d_t1, F.d_t2, F.ny, F.nx);
+    if (!col_pass<FC_PIX_W>(F, b)) {
+        transpose(F, F.d_t1, F.d_t2, F.nx, F.ny);
+        b.in = F.d_t2;
+        b.out = F.d_t1;
+        row_pass_nt<FR_PIX_W>(F, b, F.ny);
+        transpose(F, F.d_t1, F.d_t2, F.ny, F.nx);
+    }
     FRowArgs c = row_args(F, F.ny);
     c.in = F.d_t2;
+    c.is = col_stride(F.nx, F.ny);
     c.out = y;
     c.dmode = 1;
     c.scale = 1.0 / (double)F.n;
@@ -551,11 +690,11 @@ akra_status akra_flat_plan_create(int nx, int ny, void *hip_stream, akra_flat_pl
         F->device_bytes += (int64_t)b;
         return true;
     };
-    const size_t cb = (size_t)F->n * sizeof(double2);
+    const size_t cb = (size_t)F->n * sizeof(double2), tb = (size_t)(F->nx * col_stride(F->nx, F->ny)) * sizeof(double2);
     bool ok = al((void **)&F->d_tw, sizeof(double2) * (F->twn / 2)) && al((void **)&F->d_W, sizeof(double) * F->n) &&
               al((void **)&F->d_x, cb) && al((void **)&F->d_r, cb) && al((void **)&F->d_p, cb) &&
-              al((void **)&F->d_w, cb) && al((void **)&F->d_b, cb) && al((void **)&F->d_t1, cb) &&
-              al((void **)&F->d_t2, cb) && al((void **)&F->d_red, sizeof(double) * std::max(FL_RED * 4, nx)) &&
+              al((void **)&F->d_w, cb) && al((void **)&F->d_b, cb) && al((void **)&F->d_t1, tb) &&
+              al((void **)&F->d_t2, tb) && al((void **)&F->d_red, sizeof(double) * std::max(FL_RED * 4, nx)) &&
               al((void **)&F->d_scal, sizeof(double) * 64) && al((void **)&F->d_flag, sizeof(int) * 4);
     if (ok && hipHostMalloc((void **)&F->h_pin, 64 * sizeof(double)) != hipSuccess) {
         F->h_pin = nullptr;
@@ -574,7 +713,9 @@ akra_status akra_flat_plan_create(int nx, int ny, void *hip_stream, akra_flat_pl
     if (hipMemcpy(F->d_tw, tw.data(), sizeof(double2) * tw.size(), hipMemcpyHostToDevice) != hipSuccess ||
         allow_lds<FR_INV_D>() != hipSuccess || allow_lds<FR_PIX_W>() != hipSuccess ||
         allow_lds<FR_FWD_MAPS>() != hipSuccess || allow_lds<FR_FWD_OUT>() != hipSuccess ||
-        allow_lds<FR_INV_MAPS>() != hipSuccess || hipMemset(F->d_flag, 0, sizeof(int) * 4) != hipSuccess) {
+        allow_lds<FR_INV_MAPS>() != hipSuccess || allow_lds_col<FC_PIX_W>() != hipSuccess ||
+        allow_lds_col<FC_MAPS>() != hipSuccess || allow_lds_col<FC_FROM_MAPS>() != hipSuccess ||
+        hipMemset(F->d_flag, 0, sizeof(int) * 4) != hipSuccess) {
         free_flat(F);
         set_error("plan set-up failed");
         return AKRA_ERR_HIP;

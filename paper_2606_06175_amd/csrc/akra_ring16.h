@@ -174,12 +174,11 @@ template <typename T> __device__ __forceinline__ void lane_stage(cplx<T> (&v)[16
 }
 
 // full DIF from layout S0 (natural) to the bit-reversed positions of layout S2, all stages done
-template <typename T, int LOGM, bool SPLIT>
+template <typename T, int LOGM, bool SPLIT, int WV = R16<LOGM>::NT <= 64 ? 1 : 2>
 __device__ __forceinline__ void fft16_dif(cplx<T> (&v)[16], T *lds, const cplx<T> *__restrict__ tw, int twn, int t,
                                           int sign)
 {
     using G = R16<LOGM>;
-    constexpr int WV = G::NT <= 64 ? 1 : 2;
     dif_pass<T, G::S0>(v, tw, twn, t, sign);
     exchange16<T, SPLIT, G::S0, G::S1, WV>(v, lds, t);
     dif_pass<T, G::S1>(v, tw, twn, t, sign);
@@ -191,12 +190,11 @@ __device__ __forceinline__ void fft16_dif(cplx<T> (&v)[16], T *lds, const cplx<T
 }
 
 // full DIT from the bit-reversed positions of layout S2 to the natural layout S0
-template <typename T, int LOGM, bool SPLIT>
+template <typename T, int LOGM, bool SPLIT, int WV = R16<LOGM>::NT <= 64 ? 1 : 2>
 __device__ __forceinline__ void fft16_dit(cplx<T> (&v)[16], T *lds, const cplx<T> *__restrict__ tw, int twn, int t,
                                           int sign)
 {
     using G = R16<LOGM>;
-    constexpr int WV = G::NT <= 64 ? 1 : 2;
     if constexpr (LOGM == 13) lane_stage<T>(v, t & 1);
     if constexpr (G::N2 > 0) {
         dit_pass<T, G::S2, G::N2>(v, tw, twn, t, sign);
