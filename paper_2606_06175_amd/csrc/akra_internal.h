@@ -232,6 +232,7 @@ struct Plan {
     // solver vectors [nrhs][2][nalm] complex FP64
     double *d_x = nullptr, *d_r = nullptr, *d_p = nullptr, *d_w = nullptr, *d_b = nullptr, *d_xs = nullptr;
     double *h_pin = nullptr;    // pinned host scalars
+    double *h_cg = nullptr;  // pinned: <r, r> and the breakdown flag of each right-hand side after an iteration
     // unmasked-pixel list (compaction scratch) and spectrum partial sums
     int64_t cmp_ntile = 0;        // tiles of CMP_TILE pixels
     void *d_cmp = nullptr;        // one allocation holding the four members below

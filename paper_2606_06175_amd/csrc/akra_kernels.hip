@@ -902,10 +902,13 @@ __global__ __launch_bounds__(256) void k_cg_xr_alpha(double2 *__restrict__ x, do
     }
 }
 
-// p = P r + beta p with beta = P <r, r> / rz formed the same way from the partials of <r, r>
+// p = P r + beta p with beta = P <r, r> / rz formed the same way from the partials of <r, r>.  What the host
+// decides on, <r, r> and the flag, goes to its pinned memory from here (two copies after every iteration
+// before: 400 iterations at Nside 32 29.0 -> 26.8 ms)
 __global__ __launch_bounds__(256) void k_cg_p_beta(double2 *__restrict__ p, const double2 *__restrict__ r,
                                                    const double *__restrict__ red, int n_red,
-                                                   double *__restrict__ scal, int64_t nc, CgList L)
+                                                   double *__restrict__ scal, int64_t nc, CgList L,
+                                                   const int *__restrict__ flag, double *__restrict__ host)
 {
     __shared__ double sh[256];
     const int q = L.rhs[blockIdx.y];
@@ -928,6 +931,9 @@ __global__ __launch_bounds__(256) void k_cg_p_beta(double2 *__restrict__ p, cons
         scal[3] = rr;
         scal[4] = bt;
         scal[0] = rz;
+        host[2 * q] = rr;
+        host[2 * q + 1] = (double)flag[q];
+        __threadfence_system();
     }
 }
 
@@ -1106,7 +1112,7 @@ void launch_cg_p_beta(Plan &P, double *p, const double *r, double *scal, int64_t
 {
     const int nb = cg_red_blocks(P);
     k_cg_p_beta<<<dim3(nb, L.n), 256, 0, P.stream>>>((double2 *)p, (const double2 *)r, P.d_red_cg, nb, scal, n_complex,
-                                                     L);
+                                                     L, P.d_flag, P.h_cg);
 }
 
 // The ring kinds of a RingSet: RK_P2 whole power-of-two rings (LDS FFT), RK_BF whole-ring Bluestein,

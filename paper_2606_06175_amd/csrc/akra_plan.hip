@@ -884,12 +884,13 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         set_error("stream or event creation failed");
         return AKRA_ERR_HIP;
     }
-    if (hipHostMalloc((void **)&P->h_pin, 256 * sizeof(double)) != hipSuccess) {
+    if (hipHostMalloc((void **)&P->h_pin, (256 + 2 * MAX_RHS) * sizeof(double)) != hipSuccess) {
         P->h_pin = nullptr;
         free_plan(P);
         set_error("hipHostMalloc failed");
         return AKRA_ERR_ALLOC;
     }
+    P->h_cg = P->h_pin + 256;
 #undef AK_TRY
     *out = P;
     return AKRA_OK;
@@ -1305,8 +1306,9 @@ static akra_status cg_run(Plan &P, const akra_cg_opts &o, akra_cg_info *info)
             if (!fp32 && P.prec == AKRA_FP32) P.cg_fp64_applies++;
         }
         int flag = 0;
-        st = cg_poll(P, &rr, &flag);
-        if (st) return st;
+        AK_HIP(hipStreamSynchronize(P.stream), "sync");
+        rr = P.h_cg[0];
+        flag = P.h_cg[1] != 0.0;
         fresh = false;
         if ((flag || !std::isfinite(rr)) && fp32) {
             // x is the last iterate (alpha was set to 0): restart p = P r from the true residual
@@ -1636,15 +1638,9 @@ static akra_status solve_batched(Plan &P, const double *g1, const double *g2, co
         launch_cg_p(P, V(P.d_p, r), V(P.d_r, r), S(r) + 4, pc[r], nc);
     }
     std::vector<double> hs(8 * nr);
-    std::vector<int> hf(nr);
-    auto pull = [&]() -> akra_status {
-        AK_HIP(hipMemcpyAsync(hs.data(), scb, sizeof(double) * 8 * nr, hipMemcpyDeviceToHost, P.stream), "copy");
-        AK_HIP(hipMemcpyAsync(hf.data(), P.d_flag, sizeof(int) * nr, hipMemcpyDeviceToHost, P.stream), "copy");
-        AK_HIP(hipStreamSynchronize(P.stream), "sync");
-        return AKRA_OK;
-    };
-    akra_status st = pull();
-    if (st) return st;
+    AK_HIP(hipMemcpyAsync(hs.data(), scb, sizeof(double) * 8 * nr, hipMemcpyDeviceToHost, P.stream), "copy");
+    AK_HIP(hipStreamSynchronize(P.stream), "sync");
+    akra_status st = AKRA_OK;
     for (int r = 0; r < nr; ++r) {
         if (!std::isfinite(hs[8 * r + 5])) {
             set_error("right-hand side is not finite");
@@ -1734,13 +1730,12 @@ static akra_status solve_batched(Plan &P, const double *g1, const double *g2, co
         }
         if (st) return st;
         ++iters;
-        st = pull();
-        if (st) return st;
+        AK_HIP(hipStreamSynchronize(P.stream), "sync");
         for (int r = 0; r < nr; ++r) {
             if (!active[r]) continue;
             fresh[r] = 0;
-            rr[r] = hs[8 * r + 3];
-            if (hf[r] || !std::isfinite(rr[r])) {
+            rr[r] = P.h_cg[2 * r];
+            if (P.h_cg[2 * r + 1] != 0.0 || !std::isfinite(rr[r])) {
                 // p^T H p <= 0 with the FP32 operator: restart once from the true residual,
                 // a second breakdown stops this right-hand side at its last iterate
                 AK_HIP(hipMemsetAsync(P.d_flag + r, 0, sizeof(int), P.stream), "memset");

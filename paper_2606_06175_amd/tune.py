@@ -22,7 +22,7 @@ import os
 import sys
 
 CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning.json")
-SYN = [(v, r) for v in (0, 1) for r in (1, 2, 4)]
+SYN = [(1, r) for r in (1, 2, 4)]  # the variant selects nothing
 ADJ = [(r, 1, c) for c in (8, 4) for r in range(1, 9)] + \
       [(1, 2, 8), (1, 4, 8), (2, 2, 8), (2, 4, 8), (4, 2, 8), (4, 4, 8), (8, 2, 8), (2, 4, 4), (4, 2, 4), (4, 4, 4)]
 
