@@ -26,14 +26,16 @@ sys.path.insert(0, ROOT)
 METRIC = "H·v applies/s + CG time-to-1e-8 at Nside 2048 ℓmax 4096, mixed/batched vs FP64"
 PEAK_FP64 = 78.6e12      # MI355X FP64 vector FMA, FLOP/s
 PEAK_FP32 = 157.3e12     # MI355X FP32 vector (packed) FMA, FLOP/s
-FLOP_PER_TRIPLE = 26     # per (l, m, ring pair) and direction: 2 recurrences (10) + 8 contraction FMAs (16)
-FLOP_PER_TRIPLE_ONE = 18  # the same with one ring of the pair weighted: 2 recurrences + 4 contraction FMAs
+# per (l, m, ring pair) and direction, for both rings of the pair or one: a scalar recurrence step (a
+# multiply and an FMA) and 4 contraction FMAs.  The groups within 0.15 rad of a pole run two spin-weighted
+# recurrences and 8 (4) FMAs; they are counted at the same 11, which understates the rates a little.
+FLOP_PER_TRIPLE = 11
 
 
 def weighted_flops(ww):
     """Algorithmic flop of the weighted synthesis and adjoint launches (akra_plan_work_weighted)."""
-    return {"leg_synth": FLOP_PER_TRIPLE * ww["synth_two"] + FLOP_PER_TRIPLE_ONE * ww["synth_one"],
-            "leg_adj": FLOP_PER_TRIPLE * ww["adjoint_two"] + FLOP_PER_TRIPLE_ONE * ww["adjoint_one"]}
+    return {"leg_synth": FLOP_PER_TRIPLE * (ww["synth_two"] + ww["synth_one"]),
+            "leg_adj": FLOP_PER_TRIPLE * (ww["adjoint_two"] + ww["adjoint_one"])}
 
 
 def live_ring_bytes(nside, lmax, w, fg_bytes):
@@ -57,7 +59,7 @@ TRAFFIC = {
     "leg_adj": {"bytes": 4.344e9, "workload": (2048, 4096), "shapes": ((0, 1, 5, 1, 8), (0, 2, 8, 1, 8)),
                 "sources_sha256": "dad28f34f7f07a6d8186e7387dbe4b6f9f9c1495755f63a184261ce44d0388b1"},
 }
-LEG_SOURCES = ("akra_leg.h", "akra_leg_both.hip", "akra_leg_north.hip", "akra_leg_south.hip", "akra_kernels.hip")
+LEG_SOURCES = ("akra_internal.h", "akra_leg.h", "akra_leg_both.hip", "akra_leg_north.hip", "akra_leg_south.hip", "akra_kernels.hip")
 
 
 def legendre_sources_sha256():
@@ -122,11 +124,10 @@ def make_inputs(name, nside, lmax, dev):
 
 
 def fp32_roofline(plan32, g1, g2, ninv, mask, nside, lmax, steps=3):
-    """The FP32 operator's Legendre kernels (the mixed solve's iterations) against the FP32 peaks:
-    157.3 TFLOP/s is the packed-FP32 figure; the kernels issue plain FP32 VALU instructions, whose
-    rate is that of FP64 (78.6 TFLOP/s).  Stage times are HIP events over `steps` PCG steps; the
-    flop count is 26 per (l, m, ring-pair) triple the FP32 plan evaluates in ring groups weighted on
-    both sides and 18 per triple of groups weighted on one side."""
+    """The FP32 plan's Legendre kernels (the mixed solve's iterations) against the peaks: their arithmetic is
+    FP64 (78.6 TFLOP/s, the rate of plain FP32 instructions too; 157.3 is the packed-FP32 figure), F and
+    G are stored as floats.  Stage times are HIP events over `steps` PCG steps; the flop count is 11 per
+    (l, m, ring-pair) triple the plan evaluates."""
     import torch
     plan32.cg_start(g1, g2, ninv, mask)
     plan32.cg_step(1)
@@ -253,11 +254,11 @@ def batched_leg(name, tol, maxiter, solves=True, napply=20):
     pb.set_timing(False)
     t_apply = float(np.median(ts)) * 1e-3
     per_apply = {k: v[0] / napply for k, v in st.items() if v[1]}
-    # matrix-core Legendre stages against the FP32 MFMA peak: (10 + 16 K) flop per evaluated
-    # (l, m, ring-pair) triple and direction for K right-hand sides (two recurrence steps shared by the
-    # right-hand sides, eight multiply-adds per right-hand side)
+    # matrix-core Legendre stages against the FP32 MFMA peak: (3 + 8 K) flop per evaluated
+    # (l, m, ring-pair) triple and direction for K right-hand sides (a scalar recurrence step shared by the
+    # right-hand sides, four multiply-adds per right-hand side)
     tb_eval = pb.work_weighted()["batched"]  # ring groups with weight in some right-hand side
-    flop = (10 + 16 * nr) * tb_eval
+    flop = (3 + 8 * nr) * tb_eval
     mfma = {"unit": "TFLOP/s", "peak": PEAK_FP32 / 1e12, "evaluated_triples": tb_eval,
             "flop_per_launch_set": flop, "note": "per batched apply; the right-hand sides run in groups of 8"}
     for stage in ("leg_synth", "leg_adj"):
@@ -689,8 +690,8 @@ def main():
                 "frac": achieved / peak,
                 "traffic": (traffic(dom, nside, lmax, (plan.get_tuning(), plan.get_tuning_one_sided()))
                             if args.precision == "fp64" else None),
-                "algorithmic": "26 flop x %d triples of ring groups weighted on both sides + 18 flop x %d of groups "
-                               "weighted on one side = %.4g flop per launch (all (l, m, ring-pair) triples T = %d; "
+                "algorithmic": "11 flop x (%d triples of ring groups weighted on both sides + %d of groups "
+                               "weighted on one side) = %.4g flop per launch (all (l, m, ring-pair) triples T = %d; "
                                "groups without a weighted ring and the terms below each group's entry degree, where "
                                "its recurrence values first reach 2^-100, are skipped)"
                                % (ww[key + "_two"], ww[key + "_one"], fl[dom], T)}

@@ -298,8 +298,9 @@ akra_status akra_plan_work(akra_plan plan, int64_t *out3);
  * Work of the batched matrix-core Legendre kernels (FP32 plans with nrhs > 1), written to out1 (HOST):
  * the (l, m, ring pair) triples evaluated per right-hand side when every 64-pair ring group starts
  * at its own entry degree, as those kernels do.  One batched synthesis or adjoint of K right-hand
- * sides performs (10 + 16 K) flop per such triple: two recurrence steps shared by the right-hand
- * sides and eight multiply-adds per right-hand side (the transform of eq. shear_SH and its adjoint).
+ * sides performs (3 + 8 K) flop per such triple: a scalar recurrence step shared by the right-hand
+ * sides and four multiply-adds per right-hand side (the transform of eq. shear_SH and its adjoint; groups
+ * near a pole run the two spin-weighted recurrences and eight, 10 + 16 K).
  */
 akra_status akra_plan_work_batched(akra_plan plan, int64_t *out1);
 /*
@@ -322,9 +323,9 @@ akra_status akra_plan_work_batched(akra_plan plan, int64_t *out1);
  * evaluate with the current shapes: [1] synthesis in groups weighted on both sides, [2] synthesis in
  * groups weighted on one side, [3] adjoint on both sides, [4] adjoint on one side, [5] the batched
  * kernels per right-hand side (FP32 plans with nrhs > 1; they contract both sides of every weighted
- * group).  A two-sided triple costs 26 flop per direction (two recurrence steps and eight
- * multiply-adds), a one-sided one 18 (the same recurrence and four multiply-adds).  Errors:
- * AKRA_ERR_ARG.
+ * group).  A triple costs 11 flop per direction (a scalar recurrence step, 3, and four
+ * multiply-adds that serve both rings of a pair or the one); in the groups near a pole, which run the
+ * spin-weighted recurrences, 26 on both sides and 18 on one.  Errors: AKRA_ERR_ARG.
  */
 akra_status akra_plan_set_skip_unweighted(akra_plan plan, int on);
 akra_status akra_plan_work_weighted(akra_plan plan, int64_t *out6);

@@ -632,7 +632,7 @@ class Plan:
     def work_weighted(self):
         """Rings that carry weight in the last weight set-up, and the (l, m, ring-pair) triples the
         weighted Legendre launches evaluate: synthesis and adjoint, in groups weighted on both sides
-        (26 flop each) and on one side (18 flop each), and per right-hand side of the batched kernels."""
+        and on one side (11 flop each), and per right-hand side of the batched kernels."""
         v = (ctypes.c_int64 * 6)()
         _check(lib().akra_plan_work_weighted(self._h, v))
         return {"live_rings": v[0], "synth_two": v[1], "synth_one": v[2], "adjoint_two": v[3],
