@@ -53,13 +53,14 @@ def live_ring_bytes(nside, lmax, w, fg_bytes):
 # the kernel sources and launch shapes they were taken with (the SHA-256 of the Legendre sources and
 # the plan's two- and one-sided shapes are checked at run time).
 TRAFFIC = {
-    # profiles/k_leg_adj_nside2048_lmax4096_fp64.md: two-sided k_leg_adj<double, 4, 1, 8, 0, 0>
-    # FETCH 6.1001e5 KiB x 2.0 + WRITE 8.3224e5 KiB, one-sided k_leg_adj<double, 7, 1, 8, 0, 2>
-    # FETCH 6.0235e5 KiB x 2.0 + WRITE 9.8547e5 KiB (means of the two dispatches of each run)
-    "leg_adj": {"bytes": 4.344e9, "workload": (2048, 4096), "shapes": ((0, 1, 5, 1, 8), (0, 2, 8, 1, 8)),
-                "sources_sha256": "dad28f34f7f07a6d8186e7387dbe4b6f9f9c1495755f63a184261ce44d0388b1"},
+    # profiles/cases_kernels.md: two-sided k_leg_adj<double, 6, 1, 8, 0> FETCH 3.3631e5 KiB x 2.0 + WRITE
+    # 6.8352e5 KiB, one-sided k_leg_adj<double, 7, 1, 8, 2> FETCH 4.7525e5 KiB x 2.0 + WRITE 1.15272e6 KiB (means
+    # of the two dispatches of each run)
+    "leg_adj": {"bytes": 3.542e9, "workload": (2048, 4096), "shapes": ((1, 2, 8, 1, 8), (1, 1, 8, 1, 8)),
+                "sources_sha256": "ba03893510901459958e9dc33239de142283ab94712495b215364b3b463f4225"},
 }
-LEG_SOURCES = ("akra_internal.h", "akra_leg.h", "akra_leg_both.hip", "akra_leg_north.hip", "akra_leg_south.hip", "akra_kernels.hip")
+LEG_SOURCES = ("akra_internal.h", "akra_leg.h", "akra_leg_both.hip", "akra_leg_north.hip", "akra_leg_south.hip",
+               "akra_kernels.hip")
 
 
 def legendre_sources_sha256():

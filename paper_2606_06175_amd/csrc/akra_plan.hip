@@ -664,7 +664,8 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         build_coef(lmax, c64, c32d, c64s);
         AK_TRY(upload((void **)&P->d_coef64, c64.data(), c64.size() * sizeof(Coef64), *P));
         AK_TRY(upload((void **)&P->d_coef64s, c64s.data(), c64s.size() * sizeof(Coef64S), *P));
-        AK_TRY(upload((void **)&P->d_coef32d, c32d.data(), c32d.size() * sizeof(Coef32D), *P));
+        if (prec == AKRA_FP32 && nrhs > 1)  // the batched near-polar groups
+            AK_TRY(upload((void **)&P->d_coef32d, c32d.data(), c32d.size() * sizeof(Coef32D), *P));
     }
     {
         std::vector<double> sa, sc, sten;
@@ -778,22 +779,21 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     if (rtot > 0) {
         AK_TRY(alloc(&P->d_bhatr64, (size_t)rtot * sizeof(double2), *P));
         AK_TRY(alloc(&P->d_bhatr32, (size_t)rtot * sizeof(float2), *P));
-        bool ok = true;
-        for (int q = 0; q < 6 && ok; ++q) {
-            const size_t nb = rsrc[q].size();
-            if (!nb) continue;
-            int64_t *dS = nullptr, *dD = nullptr;
-            ok = hipMalloc((void **)&dS, nb * sizeof(int64_t)) == hipSuccess &&
-                 hipMalloc((void **)&dD, nb * sizeof(int64_t)) == hipSuccess &&
-                 hipMemcpy(dS, rsrc[q].data(), nb * sizeof(int64_t), hipMemcpyHostToDevice) == hipSuccess &&
-                 hipMemcpy(dD, rdst[q].data(), nb * sizeof(int64_t), hipMemcpyHostToDevice) == hipSuccess;
-            if (ok) {
-                launch_bhat_reorder(*P, 8 + q, dS, dD, (int)nb);
-                ok = hipGetLastError() == hipSuccess && hipStreamSynchronize(P->stream) == hipSuccess;
-            }
-            for (void *d : {(void *)dS, (void *)dD})
-                if (d) (void)hipFree(d);
+        // sources, then destinations, of all lengths in one buffer
+        std::vector<int64_t> sd;
+        for (auto *v : {rsrc, rdst})
+            for (int q = 0; q < 6; ++q) sd.insert(sd.end(), v[q].begin(), v[q].end());
+        int64_t *dS = nullptr;
+        bool ok = hipMalloc((void **)&dS, sd.size() * sizeof(int64_t)) == hipSuccess &&
+                  hipMemcpy(dS, sd.data(), sd.size() * sizeof(int64_t), hipMemcpyHostToDevice) == hipSuccess;
+        if (ok) {
+            size_t at0 = 0;
+            for (int q = 0; q < 6; at0 += rsrc[q++].size())
+                if (!rsrc[q].empty())
+                    launch_bhat_reorder(*P, 8 + q, dS + at0, dS + sd.size() / 2 + at0, (int)rsrc[q].size());
+            ok = hipGetLastError() == hipSuccess && hipStreamSynchronize(P->stream) == hipSuccess;
         }
+        if (dS) (void)hipFree(dS);
         if (!ok) {
             free_plan(P);
             set_error("chirp-spectrum reordering kernel failed");
