@@ -57,7 +57,7 @@ TRAFFIC = {
     # 6.8352e5 KiB, one-sided k_leg_adj<double, 7, 1, 8, 2> FETCH 4.7525e5 KiB x 2.0 + WRITE 1.15272e6 KiB (means
     # of the two dispatches of each run)
     "leg_adj": {"bytes": 3.542e9, "workload": (2048, 4096), "shapes": ((1, 2, 8, 1, 8), (1, 1, 8, 1, 8)),
-                "sources_sha256": "ba03893510901459958e9dc33239de142283ab94712495b215364b3b463f4225"},
+                "sources_sha256": "685f7189abf0d907a006e1ec5e190985f0d620e2a9d76c91e9ffb5f78fb92575"},
 }
 LEG_SOURCES = ("akra_internal.h", "akra_leg.h", "akra_leg_both.hip", "akra_leg_north.hip", "akra_leg_south.hip",
                "akra_kernels.hip")

@@ -169,7 +169,8 @@ __device__ __forceinline__ void stencil_in(const double2 *__restrict__ xE, const
     const int64_t ns = nalm + ALM_PAD;
     q[0] = q[1] = q[2] = q[3] = 0.0;
     auto at = [&](int d, int row, double &w, double2 &E, double2 &B) {
-        if (l + d < m || l + d > lmax) return false;
+        // (degrees below 2 take no part, whatever they hold)
+        if (l + d < m || l + d < 2 || l + d > lmax) return false;
         w = sten[row * ns + i + d];
         if (kern) w *= kern[l + d];
         E = xE[i + d];

@@ -83,3 +83,24 @@ def test_batched_forms_match_oracle(nside, lmax, nrhs):
         ref = o.apply_H(np.stack([A[k], B[k]]), o.weights(ninv[k], mask), 0.02)
         check_alm(np.stack([yE[k], yB[k]]), ref, lmax, 1e-5)
     p.close()
+
+
+@pytest.mark.parametrize("prec,nrhs", [("fp64", 1), ("fp32", 1), ("fp32", 3)])
+def test_degrees_below_two_take_no_part(prec, nrhs):
+    # spin-2 transforms start at l = 2: whatever l = 0 and 1 hold, also NaN or infinity, changes nothing
+    import torch
+    from paper_2606_06175_amd import Plan
+    nside, lmax = 33, 20
+    dev = torch.device("cuda", 0)
+    low = [0, 1, lmax + 1]  # (l, m) = (0, 0), (1, 0), (1, 1)
+    p = Plan(nside, lmax, nrhs=nrhs, precision=prec, device=dev)
+    x = np.stack([[wl.random_alm(lmax, 5 * c + k, lmin=0) for k in range(nrhs)] for c in (0, 1)])
+    out = []
+    for bad in (0.0, np.nan, np.inf):
+        y = x.copy()
+        y[..., low] = bad
+        t = [torch.from_numpy(v[0] if nrhs == 1 else v).to(dev).contiguous() for v in y]
+        out.append([v.cpu().numpy() for v in p.synth2(*t)])
+    p.close()
+    for o in out[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(o, out[0]))
