@@ -37,6 +37,10 @@ constexpr int FL_MAXN = 8192;  // longest row a workgroup transforms in LDS (FP6
 constexpr int FL_RED = 1024;   // partial sums of the dot products
 
 constexpr int FCOL = 4;  // columns of a workgroup of the column pass
+// From FCOL_MIN_NY columns on four to a workgroup; fewer leave compute units idle, and one column each fills more
+// of them (CG step, us, one / four / transposed: 4096 x 16 39 / 57 / 46, 4096 x 256 78 / 92 / 92, 1024 x 64 29 / 32 / 36,
+// 4096 x 512 120 / 127 / 144, 4096 x 1024 229 / 224 / 268)
+constexpr int FCOL_MIN_NY = 512;
 static bool col_ok(int nx, int ny) { return nx >= 256 && nx <= 4096 && ny % FCOL == 0; }
 // row stride of the buffers between row and column passes: 256 bytes over ny, as the rows of one column, a power
 // of two apart, meet few memory channels (the column pass at 4096 x 4096 276 us against 317)
@@ -189,8 +193,8 @@ __global__ __launch_bounds__(NT) void k_frow(FRowArgs a)
     }
 }
 
-// Column pass of the transposed layout [nx][ny]: the transforms along x of FCOL neighbouring columns i2 by
-// one workgroup, in place of a transposition, a row pass and (FC_PIX_W) a transposition back.  The register
+// Column pass of the transposed layout [nx][ny]: the transforms along x of C = FCOL or one neighbouring columns
+// i2 by one workgroup, in place of a transposition, a row pass and (FC_PIX_W) a transposition back.  The register
 // engine of the ring stage (16 points per thread, nx / 16 threads a column) needs LDS for one component of
 // a point only, so four columns of 4096 points fit where the row kernel holds one; neighbouring lanes hold
 // neighbouring columns, and a row of the array is read and written 64 bytes at a time.
@@ -206,21 +210,21 @@ template <int LOGM> struct FColShape {
     // over the banks
     static constexpr int LS = R16<LOGM>::M + R16<LOGM>::M / 32 + (40 - (R16<LOGM>::M + R16<LOGM>::M / 32) % 32) % 32;
 };
-template <int LOGM, int MODE>
-__global__ __launch_bounds__(FCOL *FColShape<LOGM>::NT) void k_fcol(FRowArgs a)
+template <int LOGM, int MODE, int C>
+__global__ __launch_bounds__(C *FColShape<LOGM>::NT) void k_fcol(FRowArgs a)
 {
     using G = R16<LOGM>;
-    constexpr int NT = G::NT, WV = FCOL * NT <= 64 ? 1 : 2;
+    constexpr int NT = G::NT, WV = C * NT <= 64 ? 1 : 2;
     extern __shared__ double cbuf[];
     // neighbouring workgroups, which share the 128-byte lines, on one XCD
     const int nb = gridDim.x, b = nb % 8 ? (int)blockIdx.x : (int)((blockIdx.x & 7) * (nb / 8) + (blockIdx.x >> 3));
-    const int c = threadIdx.x % FCOL, t = threadIdx.x / FCOL, col = b * FCOL + c;
+    const int c = threadIdx.x % C, t = threadIdx.x / C, col = b * C + c;
     double *lds = cbuf + c * FColShape<LOGM>::LS;
     // The columns' rows of the real arrays go through the LDS, natural order on the memory side (element
-    // e = threadIdx.x + i * threads of the FCOL rows), positions brev(pos) on the side of the registers: at those
+    // e = threadIdx.x + i * threads of the C rows), positions brev(pos) on the side of the registers: at those
     // positions every lane of a load from memory would meet a line of its own.
-    constexpr int TH = FCOL * NT;
-    const int64_t mb = (int64_t)b * FCOL * G::M;
+    constexpr int TH = C * NT;
+    const int64_t mb = (int64_t)b * C * G::M;
     auto slot = [&](int i) {
         const int e = threadIdx.x + i * TH;
         return e / G::M * FColShape<LOGM>::LS + pd(e % G::M);
@@ -493,9 +497,11 @@ template <int MODE> static bool col_pass(FlatPlan &F, FRowArgs a)
     if (!col_ok(F.nx, F.ny)) return false;
     a.is = a.os = col_stride(F.nx, F.ny);
     auto go = [&](auto logm) {
-        constexpr int LOGM = decltype(logm)::value;
-        k_fcol<LOGM, MODE><<<F.ny / FCOL, FCOL * FColShape<LOGM>::NT, FCOL * FColShape<LOGM>::LS * sizeof(double),
-                             F.stream>>>(a);
+        constexpr int LOGM = decltype(logm)::value, NT = FColShape<LOGM>::NT, LS = FColShape<LOGM>::LS;
+        if (F.ny < FCOL_MIN_NY)
+            k_fcol<LOGM, MODE, 1><<<F.ny, NT, LS * sizeof(double), F.stream>>>(a);
+        else
+            k_fcol<LOGM, MODE, FCOL><<<F.ny / FCOL, FCOL * NT, FCOL * LS * sizeof(double), F.stream>>>(a);
         return true;
     };
     using std::integral_constant;
@@ -509,10 +515,10 @@ template <int MODE> static bool col_pass(FlatPlan &F, FRowArgs a)
 }
 template <int MODE> static hipError_t allow_lds_col()
 {
-    hipError_t e = hipFuncSetAttribute((const void *)k_fcol<12, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    hipError_t e = hipFuncSetAttribute((const void *)k_fcol<12, MODE, FCOL>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        FCOL * FColShape<12>::LS * (int)sizeof(double));
     if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)k_fcol<11, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        e = hipFuncSetAttribute((const void *)k_fcol<11, MODE, FCOL>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 FCOL * FColShape<11>::LS * (int)sizeof(double));
     return e;
 }

@@ -1,8 +1,8 @@
-"""The flat-sky column pass (four columns of 256 to 4096 points per workgroup) at every length it takes, with
-the fewest columns and more, and the lengths on either side that keep the transposed row pass, against
+"""The flat-sky column pass (one or, from 512 columns on, four columns of 256 to 4096 points per workgroup) at
+every length it takes, with the fewest columns and more, and the lengths on either side that keep the transposed row pass, against
 the flat oracle: synthesis, adjoint, operator and right-hand side.
 
-Tolerance 1e-12: FP64 transforms of at most 2^18 points, a few eps log2 n."""
+Tolerance 1e-12: FP64 transforms of at most 2^21 points, a few eps log2 n."""
 import numpy as np
 import pytest
 
@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("nx,ny", [(128, 16), (256, 4), (256, 32), (512, 8), (1024, 4), (1024, 64), (2048, 16),
-                                   (4096, 4), (4096, 32), (8192, 8)])
+                                   (4096, 4), (4096, 32), (8192, 8), (256, 256), (256, 512), (512, 512),
+                                   (1024, 512), (2048, 512), (4096, 512)])
 def test_columns_match_oracle(nx, ny):
     o = FlatOracle(nx, ny)
     p = _plan(nx, ny)
