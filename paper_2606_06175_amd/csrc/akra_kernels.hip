@@ -451,18 +451,15 @@ __device__ void unfold_short(cplx<T> *__restrict__ G, cplx<T> *buf, int N, int s
 }
 
 template <typename T, int MODE>
-__global__ __launch_bounds__(RF) void k_ring_full(cplx<T> *__restrict__ FG, int64_t fg_stride,
-                                                  const double *__restrict__ g1, const double *__restrict__ g2,
-                                                  double *__restrict__ o1, double *__restrict__ o2, int64_t map_stride,
-                                                  const double *__restrict__ Wt, const RingInfo *__restrict__ rings,
-                                                  const int *__restrict__ order, const cplx<T> *__restrict__ tw,
-                                                  int twn, int lmax, double omega, double *__restrict__ o3,
-                                                  const uint8_t *__restrict__ mask, const double *__restrict__ cdev)
+__device__ __forceinline__ void ring_full_body(cplx<T> *__restrict__ buf, int r, int rhs, cplx<T> *__restrict__ FG,
+                                               int64_t fg_stride, const double *__restrict__ g1,
+                                               const double *__restrict__ g2, double *__restrict__ o1,
+                                               double *__restrict__ o2, int64_t map_stride,
+                                               const double *__restrict__ Wt, const RingInfo *__restrict__ rings,
+                                               const cplx<T> *__restrict__ tw, int twn, int lmax, double omega,
+                                               double *__restrict__ o3, const uint8_t *__restrict__ mask,
+                                               const double *__restrict__ cdev)
 {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    cplx<T> *buf = reinterpret_cast<cplx<T> *>(smem_raw);
-    const int r = order[blockIdx.x];
-    const int rhs = blockIdx.y;
     const RingInfo ri = rings[r];
     const int N = ri.nphi, shift = ri.shift;
     const int logN = 31 - __builtin_clz(N);
@@ -573,19 +570,15 @@ __global__ __launch_bounds__(RF) void k_ring_full(cplx<T> *__restrict__ FG, int6
 constexpr int RBU = 4;  // elements per thread: N <= RF * RBU
 
 template <typename T, int MODE>
-__global__ __launch_bounds__(RF) void k_ring_bfull(cplx<T> *__restrict__ FG, int64_t fg_stride,
-                                                   const double *__restrict__ g1, const double *__restrict__ g2,
-                                                   double *__restrict__ o1, double *__restrict__ o2, int64_t map_stride,
-                                                   const double *__restrict__ Wt, const RingInfo *__restrict__ rings,
-                                                   const int *__restrict__ order, const cplx<T> *__restrict__ tw,
-                                                   int twn, int lmax, double omega, double *__restrict__ o3,
-                                                   const uint8_t *__restrict__ mask, const double *__restrict__ cdev,
-                                                   const cplx<T> *__restrict__ bhat_all)
+__device__ __forceinline__ void ring_bfull_body(cplx<T> *__restrict__ buf, int r, int rhs, cplx<T> *__restrict__ FG,
+                                                int64_t fg_stride, const double *__restrict__ g1,
+                                                const double *__restrict__ g2, double *__restrict__ o1,
+                                                double *__restrict__ o2, int64_t map_stride,
+                                                const double *__restrict__ Wt, const RingInfo *__restrict__ rings,
+                                                const cplx<T> *__restrict__ tw, int twn, int lmax, double omega,
+                                                double *__restrict__ o3, const uint8_t *__restrict__ mask,
+                                                const double *__restrict__ cdev, const cplx<T> *__restrict__ bhat_all)
 {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    cplx<T> *buf = reinterpret_cast<cplx<T> *>(smem_raw);
-    const int r = order[blockIdx.x];
-    const int rhs = blockIdx.y;
     const RingInfo ri = rings[r];
     const int N = ri.nphi, shift = ri.shift, M = ri.M;
     const int logM = 31 - __builtin_clz(M);
@@ -681,6 +674,26 @@ __global__ __launch_bounds__(RF) void k_ring_bfull(cplx<T> *__restrict__ FG, int
             const double2 e = ph.next();
             unfold_bin_ph<T>(F, tid + RF * u, N, rN, shift, lmax, cscale<T>(y, om), e);
         });
+}
+
+// The whole-ring LDS kernels in one launch: the first nbf workgroups of the grid take a Bluestein ring each
+// (the longer ones), the others a power-of-two ring.
+template <typename T, int MODE>
+__global__ __launch_bounds__(RF) void k_ring_lds(cplx<T> *__restrict__ FG, int64_t fg_stride, RingArgs a,
+                                                 int64_t map_stride, const RingInfo *__restrict__ rings,
+                                                 const int *__restrict__ order_bf, int nbf,
+                                                 const int *__restrict__ order_p2, const cplx<T> *__restrict__ tw,
+                                                 int twn, int lmax, double omega, const cplx<T> *__restrict__ bhat_all)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    cplx<T> *buf = reinterpret_cast<cplx<T> *>(smem_raw);
+    const int b = blockIdx.x;
+    if (b < nbf)
+        ring_bfull_body<T, MODE>(buf, order_bf[b], blockIdx.y, FG, fg_stride, a.g1, a.g2, a.o1, a.o2, map_stride, a.W,
+                                 rings, tw, twn, lmax, omega, a.o3, a.mask, a.cdev, bhat_all);
+    else
+        ring_full_body<T, MODE>(buf, order_p2[b - nbf], blockIdx.y, FG, fg_stride, a.g1, a.g2, a.o1, a.o2, map_stride,
+                                a.W, rings, tw, twn, lmax, omega, a.o3, a.mask, a.cdev);
 }
 
 // ================================================================================================
@@ -1126,20 +1139,15 @@ static void ring_launch_t(Plan &P, const RingSet &RS, const double *g1, const do
     const int64_t fg_stride = (int64_t)P.nrings * (P.lmax + 1) * 2;
     const void *tw = std::is_same<T, double>::value ? P.d_tw64 : P.d_tw32;
     const cplx<T> *bh = (const cplx<T> *)(std::is_same<T, double>::value ? P.d_bhat64 : P.d_bhat32);
-    if (RS.n[RK_P2]) {
-        // whole rings: N = 4 sub <= 4 nside <= 8192 = RF RFU (nside <= 2048 is enforced at plan creation)
-        const size_t nmax = std::max((size_t)RF, 4 * (size_t)P.maxM_p2);  // RF: the short-ring fold
-        size_t sm = sizeof(cplx<T>) * (nmax + nmax / 32);
-        k_ring_full<T, MODE><<<dim3(RS.n[RK_P2], nrhs), RF, sm, P.stream>>>(
-            (cplx<T> *)P.d_FG, fg_stride, g1, g2, o1, o2, P.npix, W, P.d_rings, RS.order[RK_P2], (const cplx<T> *)tw,
-            P.twn, P.lmax, P.omega, o3, mask, cdev);
-    }
-    if (RS.n[RK_BF]) {
-        const size_t nmax = std::max((size_t)RF, (size_t)P.maxM_bf);  // RF: the short-ring fold
-        size_t sm = sizeof(cplx<T>) * (nmax + nmax / 32);
-        k_ring_bfull<T, MODE><<<dim3(RS.n[RK_BF], nrhs), RF, sm, P.stream>>>(
-            (cplx<T> *)P.d_FG, fg_stride, g1, g2, o1, o2, P.npix, W, P.d_rings, RS.order[RK_BF], (const cplx<T> *)tw,
-            P.twn, P.lmax, P.omega, o3, mask, cdev, bh);
+    if (RS.n[RK_P2] + RS.n[RK_BF]) {
+        // power-of-two rings: N = 4 sub <= 4 nside <= 8192 = RF RFU (nside <= 2048 is enforced at plan creation)
+        size_t nmax = RF;  // the short-ring fold
+        if (RS.n[RK_P2]) nmax = std::max(nmax, 4 * (size_t)P.maxM_p2);
+        if (RS.n[RK_BF]) nmax = std::max(nmax, (size_t)P.maxM_bf);
+        const size_t sm = sizeof(cplx<T>) * (nmax + nmax / 32);
+        k_ring_lds<T, MODE><<<dim3(RS.n[RK_BF] + RS.n[RK_P2], nrhs), RF, sm, P.stream>>>(
+            (cplx<T> *)P.d_FG, fg_stride, RingArgs{g1, g2, o1, o2, W, o3, mask, cdev}, P.npix, P.d_rings,
+            RS.order[RK_BF], RS.n[RK_BF], RS.order[RK_P2], (const cplx<T> *)tw, P.twn, P.lmax, P.omega, bh);
     }
     if (RS.n[RK_BL]) {
         size_t sm = sizeof(cplx<T>) * (size_t)(P.maxM_bl + P.maxM_bl / 32);
