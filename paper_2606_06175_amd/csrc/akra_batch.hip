@@ -79,8 +79,10 @@ __global__ __launch_bounds__(256) void k_prologue_b(const double2 *__restrict__ 
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     if (rhs < nrhs && e < next) {
         const int l = (int)(lm[e] & 0xffff), m = (int)(lm[e] >> 16);
-        double q[4];
-        stencil_in(xE + rhs * rstride, xB + rhs * rstride, kern, sten, l, m, lmax, nalm, e - (int64_t)EXT_L * m, q);
+        double q[4], K;
+        double2 E, B;
+        stencil_in(xE + rhs * rstride, xB + rhs * rstride, kern, sten, l, m, lmax, nalm, e - (int64_t)EXT_L * m, q, K,
+                   E, B);
         const double s = sc[e];
         v = make_float4((float)(s * q[0]), (float)(s * q[1]), (float)(s * q[2]), (float)(s * q[3]));
     }

@@ -107,8 +107,12 @@ __global__ __launch_bounds__(256) void k_prologue(const double2 *__restrict__ xE
     const int l = (int)(lm[e] & 0xffff), m = (int)(lm[e] >> 16);
     const int64_t i = e - (int64_t)EXT_L * m, ns = nalm + ALM_PAD;
     const double2 *pE = xE + rhs * nalm, *pB = xB + rhs * nalm;
-    double q[4];
-    stencil_in(pE, pB, kern, sten, l, m, lmax, nalm, i, q);
+    const bool spin = rsp && l <= lmax;
+    Coef64S c = {};
+    if (spin) c = cs64[i];
+    double q[4], K;
+    double2 E, B;
+    stencil_in(pE, pB, kern, sten, l, m, lmax, nalm, i, q, K, E, B);
     double *r = rec + (rhs * rec_stride + e) * 5;
     // in the signs of the synthesis (see there)
     const int j = (l - m) & 3;
@@ -116,11 +120,9 @@ __global__ __launch_bounds__(256) void k_prologue(const double2 *__restrict__ xE
     r[0] = (j & 1) ? -sa[e] : sa[e];
 #pragma unroll
     for (int t = 0; t < 4; ++t) r[1 + t] = s * q[t];
-    if (rsp && l <= lmax) {
-        const double K = kern ? kern[l] : 1.0;
-        const double2 e2 = pE[i], b2 = pB[i];
-        const double2 E = make_double2(K * e2.x, m ? K * e2.y : 0.0), B = make_double2(K * b2.x, m ? K * b2.y : 0.0);
-        const Coef64S c = cs64[i];
+    if (spin) {
+        E = make_double2(K * E.x, m ? K * E.y : 0.0);
+        B = make_double2(K * B.x, m ? K * B.y : 0.0);
         SpinRec o;
         o.a = c.a;
         o.b = c.b;
@@ -190,39 +192,63 @@ __global__ __launch_bounds__(256) void k_epilogue(const S *__restrict__ part, co
         const int l = (int)(v & 0xffff), m = (int)(v >> 16);
         const int64_t i = e - (int64_t)EXT_L * m;
         const int *ws = wgstart + (int64_t)m * nrb;
-        double t[4] = {0, 0, 0, 0};
-        if (valid) {
-            for (int rb = nrbs; rb < nrb; ++rb) {
-                if (l < ws[rb]) continue;
-                const S *q = part + ((int64_t)rb * next + e) * 4;
+        const bool inner = valid && tid >= EXT_L && tid < 256 - EXT_L && l <= lmax;
+        // everything an entry needs is on its way before the first slab is waited for
+        const double s = valid ? sc[e] : 0.0;
+        double w[STENCIL] = {}, x[4] = {}, K = 1.0;
+        if (inner) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) t[c] += (double)q[c];
+            for (int row = 0; row < STENCIL; ++row) w[row] = sten[row * ns + i];
+            if (kern) K = kern[l];
+            if (xE) {
+                x[0] = xE[2 * i];
+                x[1] = xE[2 * i + 1];
+                x[2] = xB[2 * i];
+                x[3] = xB[2 * i + 1];
             }
-            const double s = sc[e];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) t[c] *= s;
         }
+        // sum of the slabs [r0, r1) at entry k, four in flight
+        auto slabs = [&](int r0, int r1, int64_t k, double (&t)[4]) {
+            for (int rb = r0; rb < r1; rb += 4) {
+                bool on[4];
+                S q[4][4] = {};
 #pragma unroll
-        for (int c = 0; c < 4; ++c) T[c][tid] = t[c];
+                for (int u = 0; u < 4; ++u) on[u] = rb + u < r1 && l >= ws[rb + u];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (on[u]) {
+                        const S *p = part + ((int64_t)(rb + u) * next + k) * 4;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) q[u][c] = p[c];
+                    }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) t[c] += (double)q[u][c];
+            }
+        };
+        double t[4] = {0, 0, 0, 0}, sp[4] = {0, 0, 0, 0};
+        if (valid) slabs(nrbs, nrb, e, t);
+        if (inner && l >= 2) slabs(0, nrbs, i, sp);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) T[c][tid] = s * t[c];
         __syncthreads();
-        if (valid && tid >= EXT_L && tid < 256 - EXT_L && l <= lmax) {
+        if (inner) {
             double eR = 0, eI = 0, bR = 0, bI = 0;
             if (l >= 2) {
                 auto even = [&](int d, int row) {
                     if (l + d < m) return;
-                    const double w = sten[row * ns + i];
-                    eR = fma(-w, T[0][tid + d], eR);
-                    eI = fma(-w, T[1][tid + d], eI);
-                    bR = fma(-w, T[2][tid + d], bR);
-                    bI = fma(-w, T[3][tid + d], bI);
+                    eR = fma(-w[row], T[0][tid + d], eR);
+                    eI = fma(-w[row], T[1][tid + d], eI);
+                    bR = fma(-w[row], T[2][tid + d], bR);
+                    bI = fma(-w[row], T[3][tid + d], bI);
                 };
                 auto odd = [&](int d, int row) {
                     if (l + d < m) return;
-                    const double x = sten[row * ns + i];
-                    eR = fma(x, T[3][tid + d], eR);
-                    eI = fma(-x, T[2][tid + d], eI);
-                    bR = fma(-x, T[1][tid + d], bR);
-                    bI = fma(x, T[0][tid + d], bI);
+                    eR = fma(w[row], T[3][tid + d], eR);
+                    eI = fma(-w[row], T[2][tid + d], eI);
+                    bR = fma(-w[row], T[1][tid + d], bR);
+                    bI = fma(w[row], T[0][tid + d], bI);
                 };
                 if (nrb > nrbs) {
                     even(-2, ST_WM2);
@@ -231,31 +257,21 @@ __global__ __launch_bounds__(256) void k_epilogue(const S *__restrict__ part, co
                     odd(1, ST_X1);
                     even(2, ST_W2);
                 }
-                double s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-                for (int rb = 0; rb < nrbs; ++rb) {
-                    if (l < ws[rb]) continue;
-                    const S *q = part + ((int64_t)rb * next + i) * 4;
-                    s0 += (double)q[0];
-                    s1 += (double)q[1];
-                    s2 += (double)q[2];
-                    s3 += (double)q[3];
-                }
                 if (nrbs) {
-                    eR -= 0.5 * (s0 + s2);
-                    eI -= 0.5 * (s1 + s3);
-                    bR -= 0.5 * (s1 - s3);
-                    bI += 0.5 * (s0 - s2);
+                    eR -= 0.5 * (sp[0] + sp[2]);
+                    eI -= 0.5 * (sp[1] + sp[3]);
+                    bR -= 0.5 * (sp[1] - sp[3]);
+                    bI += 0.5 * (sp[0] - sp[2]);
                 }
             }
             if (m == 0) eI = bI = 0.0;
-            const double K = kern ? kern[l] : 1.0;
             eR *= K; eI *= K; bR *= K; bI *= K;
             if (xE) {
-                eR += lam * xE[2 * i];
-                bR += lam * xB[2 * i];
+                eR += lam * x[0];
+                bR += lam * x[2];
                 if (m) {
-                    eI += lam * xE[2 * i + 1];
-                    bI += lam * xB[2 * i + 1];
+                    eI += lam * x[1];
+                    bI += lam * x[3];
                 }
             }
             // block systems: the output block of the unknowns held at zero is zero
@@ -265,9 +281,7 @@ __global__ __launch_bounds__(256) void k_epilogue(const S *__restrict__ part, co
             outE[2 * i + 1] = eI;
             outB[2 * i] = bR;
             outB[2 * i + 1] = bI;
-            if (xE)
-                dot += (m ? 2.0 : 1.0) *
-                       ((eR * xE[2 * i] + eI * xE[2 * i + 1]) + (bR * xB[2 * i] + bI * xB[2 * i + 1]));
+            if (xE) dot += (m ? 2.0 : 1.0) * ((eR * x[0] + eI * x[1]) + (bR * x[2] + bI * x[3]));
         }
         __syncthreads();
     }

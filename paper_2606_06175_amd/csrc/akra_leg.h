@@ -161,46 +161,51 @@ __device__ __forceinline__ int64_t ext_base(int m, int lmax) { return alm_base(m
 // the stored ones when l > lmax), of E, B = K_l (x_E, x_B) with Im(a_l0) dropped:
 //   q_l = w_2(l-2) E_{l-2} + w_0(l) E_l + w_-2(l+2) E_{l+2} + i (x_1(l-1) B_{l-1} + x_-1(l+1) B_{l+1}),
 //   u_l = w_2(l-2) B_{l-2} + w_0(l) B_l + w_-2(l+2) B_{l+2} - i (x_1(l-1) E_{l-1} + x_-1(l+1) E_{l+1})
-// (the stencil is zero at degrees below 2).
+// (the stencil is zero at degrees below 2, whose coefficients take no part whatever they hold).  All loads
+// go out together, none behind a condition: a neighbour outside its column reads the entry nearest to it and counts as
+// zero.  One neighbour after the other, the prologue waited for five latencies in turn (Nside 40: 5.0 us, so 3.9).
+// K, E, B: kernel and coefficients of the entry itself, as they are stored.
 __device__ __forceinline__ void stencil_in(const double2 *__restrict__ xE, const double2 *__restrict__ xB,
                                            const double *__restrict__ kern, const double *__restrict__ sten, int l,
-                                           int m, int lmax, int64_t nalm, int64_t i, double (&q)[4])
+                                           int m, int lmax, int64_t nalm, int64_t i, double (&q)[4], double &K,
+                                           double2 &E, double2 &B)
 {
+    constexpr int row[5] = {ST_W2, ST_X1, ST_W0, ST_XM1, ST_WM2};  // of the neighbours l - 2 .. l + 2
     const int64_t ns = nalm + ALM_PAD;
+    double w[5], k[5];
+    double2 e[5], b[5];
+#pragma unroll
+    for (int n = 0; n < 5; ++n) {
+        const int ln = l + n - 2, lc = ln < m ? m : ln > lmax ? lmax : ln;
+        const int64_t ic = i - l + lc;
+        w[n] = sten[row[n] * ns + ic];
+        k[n] = kern ? kern[lc] : 1.0;
+        e[n] = xE[ic];
+        b[n] = xB[ic];
+    }
+    K = k[2];
+    E = e[2];
+    B = b[2];
     q[0] = q[1] = q[2] = q[3] = 0.0;
-    auto at = [&](int d, int row, double &w, double2 &E, double2 &B) {
-        // (degrees below 2 take no part, whatever they hold)
-        if (l + d < m || l + d < 2 || l + d > lmax) return false;
-        w = sten[row * ns + i + d];
-        if (kern) w *= kern[l + d];
-        E = xE[i + d];
-        B = xB[i + d];
-        if (m == 0) E.y = B.y = 0.0;
-        return true;
-    };
-    auto even = [&](int d, int row) {
-        double w;
-        double2 E, B;
-        if (!at(d, row, w, E, B)) return;
-        q[0] = fma(w, E.x, q[0]);
-        q[1] = fma(w, E.y, q[1]);
-        q[2] = fma(w, B.x, q[2]);
-        q[3] = fma(w, B.y, q[3]);
-    };
-    auto odd = [&](int d, int row) {
-        double x;
-        double2 E, B;
-        if (!at(d, row, x, E, B)) return;
-        q[0] = fma(-x, B.y, q[0]);
-        q[1] = fma(x, B.x, q[1]);
-        q[2] = fma(x, E.y, q[2]);
-        q[3] = fma(-x, E.x, q[3]);
-    };
-    even(-2, ST_W2);
-    odd(-1, ST_X1);
-    even(0, ST_W0);
-    odd(1, ST_XM1);
-    even(2, ST_WM2);
+#pragma unroll
+    for (int n = 0; n < 5; ++n) {
+        const int ln = l + n - 2;
+        const bool on = ln >= m && ln >= 2 && ln <= lmax;
+        const double x = on ? w[n] * k[n] : 0.0;
+        const double eR = on ? e[n].x : 0.0, eI = on && m ? e[n].y : 0.0;
+        const double bR = on ? b[n].x : 0.0, bI = on && m ? b[n].y : 0.0;
+        if (n & 1) {
+            q[0] = fma(-x, bI, q[0]);
+            q[1] = fma(x, bR, q[1]);
+            q[2] = fma(x, eI, q[2]);
+            q[3] = fma(-x, eR, q[3]);
+        } else {
+            q[0] = fma(x, eR, q[0]);
+            q[1] = fma(x, eI, q[1]);
+            q[2] = fma(x, bR, q[2]);
+            q[3] = fma(x, bI, q[3]);
+        }
+    }
 }
 
 // XCD-aware placement: workgroups are dealt to the 8 XCDs round-robin, so all blocks of one m
@@ -962,6 +967,15 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(AdjWaves
     xcd_map((int)blockIdx.x, nbs + nbm, m, b);
     if (m > lmax) return;
     if (b < nbs) {
+        if constexpr (W == 1) {
+            // a workgroup with one spin group left runs no empty slot
+            if (b * spin_gpb(W) + 1 == nspin) {
+                adj_body<FORM_SPIN, S, 1, W, L, CLS>(red, FG, sa, cs64, ent, entk, entl, ng64, pair_z, part, wgstart,
+                                                     slab, lmax, npairs, nrings, glist, nspin, live, nrb, m, rbs + b,
+                                                     b * spin_gpb(W));
+                return;
+            }
+        }
         adj_body<FORM_SPIN, S, spin_gpb(W) / W, W, L, CLS>(red, FG, sa, cs64, ent, entk, entl, ng64, pair_z, part,
                                                                wgstart, slab, lmax, npairs, nrings, glist, nspin,
                                                                live, nrb, m, rbs + b, b * spin_gpb(W));
