@@ -263,6 +263,7 @@ struct Plan {
     // to the plan stream with events, so that one launch fills the other's tail
     hipStream_t side_stream = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    bool fork_classes = true;  // single-vector applies: the classes on two streams (see FORK_MIN_LMAX)
     bool in_fork = false;  // inside a fork_join: a nested one runs its halves in order
     hipGraphExec_t cg_graph = nullptr;
     double cg_graph_key[ITER_KEY_N] = {};
@@ -338,6 +339,13 @@ template <class A, class B> void fork_join(Plan &P, A &&side, B &&main)
     (void)hipStreamWaitEvent(P.stream, P.ev_join, 0);
     P.in_fork = false;
 }
+
+// The group classes of a single-vector apply run on two streams from this lmax on: a fork and its join cost an apply
+// 12 us (a recorded iteration 8), more than the shorter class hides below.  CG iteration, us, two streams / one, FP64
+// and FP32: Nside 48, lmax 48 72 / 67 and 71 / 67, Nside 64, lmax 64 75 / 70 and 83 / 70, Nside 96, lmax 96 89 / 77 and
+// 87 / 77, lmax 128 at Nside 64 89 / 89 and 93 / 90, at Nside 128 81 / 87 and 92 / 88, Nside 128, lmax 256 104 / 113
+// and 106 / 115.
+constexpr int FORK_MIN_LMAX = 128;
 
 // by-value kernel arguments: lambda of the right-hand sides of a batched group; the right-hand sides a PCG
 // update covers, with their preconditioners P

@@ -1031,7 +1031,7 @@ void launch_leg_synth(Plan &P, bool fp32, int nrhs, bool live)
             leg_synth_cls<GCLS_SOUTH>(P, fp32, nrhs, G.list[GCLS_SOUTH], G.npol[GCLS_SOUTH], G.nmain[GCLS_SOUTH]);
     };
     // the classes write F of disjoint rings: the two-sided groups on the side stream
-    if (n(GCLS_BOTH) && n(GCLS_NORTH) + n(GCLS_SOUTH)) fork_join(P, two, one);
+    if (P.fork_classes && n(GCLS_BOTH) && n(GCLS_NORTH) + n(GCLS_SOUTH)) fork_join(P, two, one);
     else {
         two();
         one();
@@ -1099,7 +1099,7 @@ void launch_leg_adj(Plan &P, bool fp32, int rhs, bool live)
         adj_cls<GCLS_NORTH>(P, fp32, rhs, G, lv, nspin, nrb);
         adj_cls<GCLS_SOUTH>(P, fp32, rhs, G, lv, nspin, nrb);
     };
-    if (n(GCLS_BOTH) && n(GCLS_NORTH) + n(GCLS_SOUTH)) fork_join(P, two, one);
+    if (P.fork_classes && n(GCLS_BOTH) && n(GCLS_NORTH) + n(GCLS_SOUTH)) fork_join(P, two, one);
     else {
         two();
         one();

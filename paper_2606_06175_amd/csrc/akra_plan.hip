@@ -642,6 +642,7 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     const double theta = prec == AKRA_FP32 && nrhs > 1 ? AKRA_POLE_THETA_B : AKRA_POLE_THETA;
     while (P->spin_groups < P->ng64 && std::acos(P->h_rings[64 * P->spin_groups].z) < theta) ++P->spin_groups;
     P->next = P->nalm + (int64_t)EXT_L * (lmax + 1);
+    P->fork_classes = lmax >= FORK_MIN_LMAX;
 
     // Legendre launch shapes
     P->syn_R = P->npairs >= 256 ? 2 : 1;
@@ -1043,7 +1044,7 @@ static akra_status apply_H_timed(Plan &P, bool fp32, const double *kern_dev, dou
     stage_mark(P, 0, false);
     const bool two = G.npol[GCLS_BOTH] + G.nmain[GCLS_BOTH] > 0,
                one = G.npol[GCLS_NORTH] + G.nmain[GCLS_NORTH] + G.npol[GCLS_SOUTH] + G.nmain[GCLS_SOUTH] > 0;
-    if (!P.timing && P.skip_rings && P.side_stream && two && one) {
+    if (!P.timing && P.skip_rings && P.side_stream && P.fork_classes && two && one) {
         // untimed: one chain per class of ring groups (stage times need the staged order below)
         launch_weighted_chains(P, fp32, P.d_W + (int64_t)rhs * P.npix);
         launch_epilogue(P, fp32, kern_dev, lam, xE, xB, yE, yB, dot_red);
