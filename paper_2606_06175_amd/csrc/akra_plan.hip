@@ -11,15 +11,21 @@
 
 #include "akra_internal.h"
 
-// The 64-pair groups that begin within AKRA_POLE_THETA radians of a pole run the spin form of the
-// Legendre kernels, the others the scalar form.  The scalar form divides its sums by sin^2(theta).  Its
+// The 64-pair groups that begin within AKRA_POLE_THETA radians of a pole, or AKRA_POLE_X / lmax, run the spin form of
+// the Legendre kernels, the others the scalar form.  The scalar form divides its sums by sin^2(theta).  Its
 // terms share the phase error of one recurrence, so that error (about sqrt(l) eps / theta, the same in
-// both forms) is not amplified, but their own rounding is.  Synthesis error of both forms against 64
-// bits more, relative to the ring's rms, spin / scalar: lmax 4096: 4.1e-14 / 4.2e-14 at 0.2 rad,
-// 6.9e-14 / 7.4e-14 at 0.1; lmax 64: 1.6e-15 / 2.1e-15 at 0.45, 3.6e-15 / 5.2e-15 at 0.2,
-// 5.2e-15 / 1.1e-14 at 0.1, 1.6e-14 / 7.3e-13 at 0.02.  From 0.15 rad on the two are as good as equal
-// at the sizes whose second group begins that near a pole (Nside 350 and up).
-constexpr double AKRA_POLE_THETA = 0.15;
+// both forms) is not amplified, but their own rounding is, and it shows where the recurrence has run over few
+// oscillations, lmax theta / pi.  Synthesis error of both forms against 64 bits more, relative to the ring's rms, in
+// 1e-15, spin / scalar:
+//   lmax   16, theta 0.2 1.0 / 4.2, 0.3 0.9 / 1.3, 0.6 0.5 / 0.7, 1.5 0.17 / 0.16
+//   lmax   64, theta 0.15 3.2 / 6.4, 0.2 3.2 / 5.2, 0.3 1.9 / 3.1, 0.45 1.6 / 1.7, 0.6 1.1 / 1.4, 0.8 0.7 / 0.8
+//   lmax  128, theta 0.1 9.5 / 13, 0.15 5.8 / 7.4, 0.2 4.5 / 6.1, 0.3 3.5 / 3.4
+//   lmax  256, theta 0.1 17 / 17, 0.15 9.9 / 11, 0.2 9.0 / 8.4
+//   lmax 1024, theta 0.05 66 / 78, 0.1 26 / 37, 0.15 20 / 26, 0.2 17 / 17, 0.3 10 / 12, 0.45 6.7 / 5.5
+//   lmax 4096, theta 0.1 69 / 74, 0.2 41 / 42
+// From lmax theta = 40 on the two are level (0.9 to 1.3, the scatter of the sample).  With lmax >= Nside the second
+// group always begins beyond 50 / lmax, so the bound matters for low degrees on many rings only.
+constexpr double AKRA_POLE_THETA = 0.15, AKRA_POLE_X = 40.0;
 // The batched kernels sum in FP32, whose rounding the division by sin^2(theta) does amplify: there the
 // spin form (in the FP32 difference form) covers the groups that begin within AKRA_POLE_THETA_B.
 constexpr double AKRA_POLE_THETA_B = 0.3;
@@ -639,7 +645,7 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     }
 
     P->ng64 = (P->npairs + 63) / 64;
-    const double theta = prec == AKRA_FP32 && nrhs > 1 ? AKRA_POLE_THETA_B : AKRA_POLE_THETA;
+    const double theta = std::max(prec == AKRA_FP32 && nrhs > 1 ? AKRA_POLE_THETA_B : AKRA_POLE_THETA, AKRA_POLE_X / lmax);
     while (P->spin_groups < P->ng64 && std::acos(P->h_rings[64 * P->spin_groups].z) < theta) ++P->spin_groups;
     P->next = P->nalm + (int64_t)EXT_L * (lmax + 1);
     P->fork_classes = lmax >= FORK_MIN_LMAX;
