@@ -278,7 +278,9 @@ template <int N> __device__ __forceinline__ void fma_row(double &acc, double r, 
 {
     asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(r), "v"(c), "n"(N));
 }
-// r's last write to its registers is two wait states back (a DPP operand's hazard after a vector write)
+// r's last write to its registers is two wait states back (a DPP operand's hazard after a vector write, which the
+// compiler does not see in inline asm).  Due at the start of every straight run of fma_row: a register copy or
+// reload may end the block before.
 __device__ __forceinline__ void settle(double (&r)[4])
 {
     asm volatile("s_nop 1" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
@@ -424,12 +426,13 @@ __device__ __forceinline__ void syn_body(const double *__restrict__ recs, int64_
     for (; l <= lend; l += 16) {
         if (l + 15 > lend && l + (lane & 15) > lend) r.a = r.q0 = r.q1 = r.u0 = r.u1 = 0.0;
         SRec n = load(l + 16);
-        settle(r);
         before(l);
+        settle(r);
         syn_steps8<0, R>(r, x, c, p, acc0, accB);
         after();
         if (l + 8 > lend) break;
         before(l + 8);
+        settle(r);
         syn_steps8<8, R>(r, x, c, p, acc0, accB);
         after();
         r = n;
