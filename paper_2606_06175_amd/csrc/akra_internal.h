@@ -215,8 +215,10 @@ struct Plan {
     // workspaces (sized for FP64; FP32 views reuse them)
     void *d_FG = nullptr;       // [nrhs][nrings][lmax+1][2] complex
     void *d_part = nullptr;     // [nrb][next][4] adjoint partial sums (spin blocks fill [nalm][4] of theirs)
-    double *d_rec = nullptr;    // [nrhs][next + ALM_PAD][5] synthesis records of the scalar form
-    void *d_rec_spin = nullptr; // [nrhs][nalm + ALM_PAD] synthesis records of the spin form (64 B)
+    // synthesis records, of every right-hand side of a launch (one in FP32 plans with several right-hand sides,
+    // whose transforms take d_brec)
+    double *d_rec = nullptr;    // [nrhs][next + ALM_PAD][5] scalar form
+    void *d_rec_spin = nullptr; // [nrhs][nalm + ALM_PAD] spin form
     float *d_brec = nullptr;    // FP32 plans with nrhs > 1: [next + ALM_PAD][8 rhs][4] batched records
     float *d_brec_spin = nullptr;  // [nalm + ALM_PAD][8 rhs][4] those of the spin form
     int nrb_b = 0;              // FP32 plans with nrhs > 1: ring blocks of the batched adjoint

@@ -850,7 +850,9 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     P->work_live[2] = P->work[2];
     P->work_live[4] = P->work_b;
     P->rec_stride = P->next + ALM_PAD;
-    const size_t rec_b = (size_t)nrhs * P->rec_stride * 5 * sizeof(double), recs_b = (size_t)nrhs * (P->nalm + ALM_PAD) * 64;
+    // FP32 plans with several right-hand sides run their single-vector stages one right-hand side at a time
+    const size_t nrec = prec == AKRA_FP32 && nrhs > 1 ? 1 : nrhs;
+    const size_t rec_b = nrec * P->rec_stride * 5 * sizeof(double), recs_b = nrec * (P->nalm + ALM_PAD) * 64;
     AK_TRY(alloc((void **)&P->d_rec, rec_b, *P));
     if (P->spin_groups > 0) AK_TRY(alloc(&P->d_rec_spin, recs_b, *P));
     if (prec == AKRA_FP32 && nrhs > 1) {
