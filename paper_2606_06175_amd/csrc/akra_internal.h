@@ -25,6 +25,8 @@ constexpr int ALM_PAD = 64;
 // the scalar functions of the transforms run to degree lmax + EXT_L (the stencil of sin^2 theta times a
 // spin-2 function reaches two degrees further)
 constexpr int EXT_L = 2;
+// doubles of a synthesis record of the spin form
+constexpr int SPIN_REC = 6;
 // right-hand sides per group of the batched kernels
 constexpr int NBR = 8;
 // unmasked-pixel compaction: threads per block, contiguous pixels per thread, pixels per tile
@@ -152,8 +154,9 @@ struct Plan {
     Coef64S *d_coef64s = nullptr;  // scaled form of the spin kernels
     Coef32D *d_coef32d = nullptr;
     int64_t next = 0;              // (l, m) entries with l up to lmax + EXT_L: ext_base(m) + l
-    double *d_sa = nullptr, *d_sc = nullptr;  // [next] a' and c_l of the scalar functions
-    double *d_sten = nullptr;      // [STENCIL][nalm + ALM_PAD] stencil of the spin-2 functions, zero at l < 2
+    // one allocation: a' and c_l of the scalar functions ([next + ALM_PAD] each) and the stencil of the spin-2
+    // functions, [STENCIL][nalm + ALM_PAD], zero at l < 2
+    double *d_sa = nullptr, *d_sc = nullptr, *d_sten = nullptr;
     uint32_t *d_lm = nullptr;      // [next] m << 16 | l
     double *d_seed2 = nullptr, *d_seedm2 = nullptr;  // [m][pair] seeds: spin groups at l = max(m,2) (both
                                                      // spins), scalar groups at l = m (plan build only)
@@ -167,7 +170,7 @@ struct Plan {
     int64_t work[3] = {0, 0, 0};  // (l, m, pair) triples: all, evaluated by synthesis, by adjoint
     int64_t work_b = 0;           // triples per right-hand side of the batched kernels (each group from its entry)
     void *d_tw64 = nullptr, *d_tw32 = nullptr;  // e^{-2 pi i k / twn}, k < twn/2
-    void *d_bhat64 = nullptr, *d_bhat32 = nullptr;  // Bluestein chirp spectra per distinct sub length
+    void *d_bhat64 = nullptr, *d_bhat32 = nullptr;  // Bluestein chirp spectra per distinct sub length (FP32 plans: both)
     int twn = 1;
     int *d_lof = nullptr;  // l of every alm index
     int *d_order_p2 = nullptr, *d_order_bl = nullptr, *d_order_bf = nullptr;
@@ -218,7 +221,7 @@ struct Plan {
     // synthesis records, of every right-hand side of a launch (one in FP32 plans with several right-hand sides,
     // whose transforms take d_brec)
     double *d_rec = nullptr;    // [nrhs][next + ALM_PAD][5] scalar form
-    void *d_rec_spin = nullptr; // [nrhs][nalm + ALM_PAD] spin form
+    void *d_rec_spin = nullptr; // [nrhs][nalm + ALM_PAD] spin form, SPIN_REC doubles
     float *d_brec = nullptr;    // FP32 plans with nrhs > 1: [next + ALM_PAD][8 rhs][4] batched records
     float *d_brec_spin = nullptr;  // [nalm + ALM_PAD][8 rhs][4] those of the spin form
     int nrb_b = 0;              // FP32 plans with nrhs > 1: ring blocks of the batched adjoint

@@ -126,7 +126,6 @@ __global__ __launch_bounds__(256) void k_prologue(const double2 *__restrict__ xE
         SpinRec o;
         o.a = c.a;
         o.b = c.b;
-        o.g = o.pad = 0.0;
         o.u0 = c.c * (E.x - B.y);
         o.u1 = c.c * (E.y + B.x);
         o.u2 = c.c * (E.x + B.y);
@@ -1173,7 +1172,7 @@ static void ring_launch_t(Plan &P, const RingSet &RS, const double *g1, const do
 }
 
 // Spectra of the Bluestein chirps, one per distinct sub-transform length L (plan creation):
-//   bhat = FFT_M(b) / M,  b_n = e^{+i pi n^2 / L} for n in (-L, L) (wrapped mod M), in FP64 and FP32.
+//   bhat = FFT_M(b) / M,  b_n = e^{+i pi n^2 / L} for n in (-L, L) (wrapped mod M), in FP64 and, with b32, FP32.
 __global__ __launch_bounds__(RT) void k_bhat(const int *__restrict__ Ls, const int *__restrict__ Ms,
                                              const int64_t *__restrict__ ofs, const double2 *__restrict__ tw,
                                              int twn, double2 *__restrict__ b64, float2 *__restrict__ b32)
@@ -1195,14 +1194,14 @@ __global__ __launch_bounds__(RT) void k_bhat(const int *__restrict__ Ls, const i
     for (int n = threadIdx.x; n < M; n += RT) {
         const double2 v = cscale<double>(buf[pd(n)], inv);
         b64[o + n] = v;
-        b32[o + n] = make_float2((float)v.x, (float)v.y);
+        if (b32) b32[o + n] = make_float2((float)v.x, (float)v.y);
     }
 }
 
 void launch_bhat_reorder(Plan &P, int logm, const int64_t *src_ofs, const int64_t *dst_ofs, int n)
 {
     launch_bhat_reorder_f64(P, logm, src_ofs, dst_ofs, n);
-    launch_bhat_reorder_f32(P, logm, src_ofs, dst_ofs, n);
+    if (P.prec == AKRA_FP32) launch_bhat_reorder_f32(P, logm, src_ofs, dst_ofs, n);
 }
 
 void launch_bhat(Plan &P, const int *Ls, const int *Ms, const int64_t *ofs, int n, int maxM)

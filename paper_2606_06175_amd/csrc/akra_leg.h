@@ -469,12 +469,10 @@ __device__ __forceinline__ void syn_body(const double *__restrict__ recs, int64_
 // and the south ring, by 2lambda_lm(pi - theta) = (-1)^(l+m) -2lambda_lm(theta), S-(u0), S-(u1), S+(u2),
 // S+(u3) with the sign of l + m.
 // ================================================================================================
-struct alignas(64) SpinRec {
-    double a, b, g, pad, u0, u1, u2, u3;  // a', b' of the scaled form; c_l times the u combinations
+struct SpinRec {
+    double a, b, u0, u1, u2, u3;  // a', b' of the scaled form; c_l times the u combinations
 };
-struct SpinIn {
-    double a, b, u0, u1, u2, u3;
-};
+static_assert(sizeof(SpinRec) == SPIN_REC * sizeof(double), "allocation of the records");
 
 template <typename S, int CLS>
 __device__ __forceinline__ void spin_body(const SpinRec *__restrict__ recs, int64_t rec_stride,
@@ -505,7 +503,7 @@ __device__ __forceinline__ void spin_body(const SpinRec *__restrict__ recs, int6
     for (int q = 0; q < 8; ++q) a[q] = b[q] = 0.0;
     const_as<SpinRec> *rp = uniform_ptr(recs + rhs * rec_stride + base);
     auto ld = [&](int i) {
-        SpinIn r;
+        SpinRec r;
         r.a = rp[i].a;
         r.b = rp[i].b;
         r.u0 = rp[i].u0;
@@ -514,7 +512,7 @@ __device__ __forceinline__ void spin_body(const SpinRec *__restrict__ recs, int6
         r.u3 = rp[i].u3;
         return r;
     };
-    auto step = [&](const SpinIn &in, double (&s)[8]) {
+    auto step = [&](const SpinRec &in, double (&s)[8]) {
         s[0] = fma(c2, in.u0, s[0]);
         s[1] = fma(c2, in.u1, s[1]);
         s[2] = fma(cm, in.u2, s[2]);
@@ -531,11 +529,11 @@ __device__ __forceinline__ void spin_body(const SpinRec *__restrict__ recs, int6
     int l = __builtin_amdgcn_readfirstlane(ls <= lmax ? ls : lmax + 1);
     // four degrees per trip, their records loaded a trip ahead: the few waves of these groups have
     // little beside them to hide a load's latency (the record buffer is padded)
-    SpinIn r[4];
+    SpinRec r[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) r[t] = ld(l + t);
     for (; l + 3 <= lmax; l += 4) {
-        SpinIn n[4];
+        SpinRec n[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) n[t] = ld(l + 4 + t);
 #pragma unroll

@@ -117,14 +117,19 @@ static void build_rings(Plan &P)
 // Entries past the last column (ALM_PAD) keep the kernels' look-ahead loads in bounds.
 // The scaled form (Coef64S) divides out c_l with c_{l0} = c_{l0+1} = 1, c_{l+1} = g_l c_{l-1}: entries
 // below l0 and the padding carry c = 1, the entry at lmax its c with a' = b' = 0.
-static void build_coef(int lmax, std::vector<Coef64> &c64, std::vector<Coef32D> &c32d,
-                       std::vector<Coef64S> &c64s)
-{
-    const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 2) / 2;
-    c64.assign(nalm + ALM_PAD, Coef64{0, 0, 0, 0});
-    c32d.assign(nalm + ALM_PAD, Coef32D{0, 0, 0, 0});
-    c64s.assign(nalm + ALM_PAD, Coef64S{0, 0, 1, 1});
-    parallel_for(lmax + 1, [&](int m) {
+struct SpinTables {
+    std::vector<Coef64> c64;
+    std::vector<Coef64S> c64s;
+    std::vector<Coef32D> c32d;  // the batched near-polar groups' (want32)
+    SpinTables(int lmax, bool want32)
+    {
+        const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 2) / 2;
+        c64.assign(nalm + ALM_PAD, Coef64{0, 0, 0, 0});
+        c64s.assign(nalm + ALM_PAD, Coef64S{0, 0, 1, 1});
+        if (want32) c32d.assign(nalm + ALM_PAD, Coef32D{0, 0, 0, 0});
+    }
+    void column(int lmax, int m)
+    {
         const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
         const int l0 = std::max(m, 2);
         typedef long double ld;
@@ -138,49 +143,61 @@ static void build_coef(int lmax, std::vector<Coef64> &c64, std::vector<Coef32D> 
             const ld b = 2.0L * m * q / (L * r1);
             const ld g = (L + 1) * r0 * sqrtl((2 * L + 3) / (2 * L - 1)) / (L * r1);
             c64[base + l] = Coef64{(double)a, (double)b, (double)g, 0.0};
-            c32d[base + l] = Coef32D{(float)a, (float)(a + b - g - 1), (float)(a - b - g - 1), (float)g};
+            if (!c32d.empty()) c32d[base + l] = Coef32D{(float)a, (float)(a + b - g - 1), (float)(a - b - g - 1), (float)g};
             if (l > l0) cs[l + 1] = g * cs[l - 1];
             const ld f = cs[l] / cs[l + 1];
             c64s[base + l] = Coef64S{(double)(a * f), (double)(b * f), (double)cs[l], (double)(1.0L / cs[l])};
         }
         c64s[base + lmax] = Coef64S{0.0, 0.0, (double)cs[lmax], (double)(1.0L / cs[lmax])};
-    });
-}
+    }
+};
 
 // Tables of the scalar functions (a', c_l over l = m .. lmax + EXT_L, and m << 16 | l of every entry) and
 // the stencil of the spin-2 functions in them (see akra_internal.h).
-static void build_scalar(int lmax, int64_t next, std::vector<double> &sa, std::vector<double> &sc,
-                         std::vector<double> &sten, std::vector<uint32_t> &lm)
-{
-    const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 2) / 2, ns = nalm + ALM_PAD;
-    sa.assign(next + ALM_PAD, 0.0);
-    sc.assign(next + ALM_PAD, 1.0);
-    sten.assign(STENCIL * ns, 0.0);
-    lm.assign(next, 0);
-    parallel_for(lmax + 1, [&](int m) {
+struct ScalarTables {
+    std::vector<double> tab;  // a' [next + ALM_PAD], c_l [next + ALM_PAD], stencil [STENCIL][nalm + ALM_PAD]
+    std::vector<uint32_t> lm;
+    std::vector<long double> nl;  // N of degree l
+    int64_t next, ns;
+    double *sa() { return tab.data(); }
+    double *sc() { return tab.data() + (next + ALM_PAD); }
+    double *sten() { return tab.data() + 2 * (next + ALM_PAD); }
+    ScalarTables(int lmax, int64_t next_) : next(next_)
+    {
+        ns = (int64_t)(lmax + 1) * (lmax + 2) / 2 + ALM_PAD;
+        tab.assign(2 * (next + ALM_PAD) + STENCIL * ns, 0.0);
+        std::fill(sc(), sten(), 1.0);
+        lm.assign(next, 0);
+        nl.assign(lmax + 1, 0.0L);
+        for (int l = 2; l <= lmax; ++l) nl[l] = 1.0L / sqrtl((long double)(l - 1) * l * (l + 1) * (l + 2));
+    }
+    void column(int lmax, int m)
+    {
         typedef long double ld;
         const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2, eb = base + (int64_t)EXT_L * m;
-        auto A = [&](int l) { return l <= m ? 0.0L : sqrtl(((ld)l * l - (ld)m * m) / (4.0L * l * l - 1.0L)); };
+        std::vector<ld> A(lmax + EXT_L + 2, 0.0L);  // A_l, zero up to l = m
+        for (int l = m + 1; l <= lmax + EXT_L + 1; ++l) A[l] = sqrtl(((ld)l * l - (ld)m * m) / (4.0L * l * l - 1.0L));
+        double *a = sa(), *c = sc(), *st = sten();
         ld c0 = 1.0L, cm = 1.0L;  // c_l, c_{l-1}
         for (int l = m; l <= lmax + EXT_L; ++l) {
-            const ld c1 = l == m ? 1.0L : A(l) / A(l + 1) * cm;
-            sa[eb + l] = (double)(c0 / (A(l + 1) * c1));
-            sc[eb + l] = (double)c0;
+            const ld c1 = l == m ? 1.0L : A[l] / A[l + 1] * cm;
+            a[eb + l] = (double)(c0 / (A[l + 1] * c1));
+            c[eb + l] = (double)c0;
             lm[eb + l] = (uint32_t)m << 16 | (uint32_t)l;
             cm = c0;
             c0 = c1;
         }
         for (int l = std::max(m, 2); l <= lmax; ++l) {
-            const ld L = l, M = m, N = 1.0L / sqrtl((L - 1) * L * (L + 1) * (L + 2));
-            const ld a0 = A(l), a1 = A(l + 1);
-            sten[ST_W2 * ns + base + l] = (double)(N * L * (L - 1) * a1 * A(l + 2));
-            sten[ST_W0 * ns + base + l] = (double)(N * (M * M - L * (L + 4) * a1 * a1 - (L + 1) * (L - 3) * a0 * a0));
-            sten[ST_WM2 * ns + base + l] = (double)(N * (L + 1) * (L + 2) * a0 * A(l - 1));
-            sten[ST_X1 * ns + base + l] = (double)(-2 * M * N * (L - 1) * a1);
-            sten[ST_XM1 * ns + base + l] = (double)(2 * M * N * (L + 2) * a0);
+            const ld L = l, M = m, N = nl[l];
+            const ld a0 = A[l], a1 = A[l + 1];
+            st[ST_W2 * ns + base + l] = (double)(N * L * (L - 1) * a1 * A[l + 2]);
+            st[ST_W0 * ns + base + l] = (double)(N * (M * M - L * (L + 4) * a1 * a1 - (L + 1) * (L - 3) * a0 * a0));
+            st[ST_WM2 * ns + base + l] = (double)(N * (L + 1) * (L + 2) * a0 * A[l - 1]);
+            st[ST_X1 * ns + base + l] = (double)(-2 * M * N * (L - 1) * a1);
+            st[ST_XM1 * ns + base + l] = (double)(2 * M * N * (L + 2) * a0);
         }
-    });
-}
+    }
+};
 
 // ---------------------------------------------------------------------------------------------
 // Seeds for the north ring of every pair, by a recurrence in m.  Spin groups: lambda_{l0,m}, l0 = max(m,2):
@@ -472,7 +489,7 @@ static akra_status build_live_lists(Plan &P)
 
 static void free_plan(Plan *P)
 {
-    void *ptrs[] = {P->d_rings, P->d_pair_z, P->d_coef64, P->d_coef64s, P->d_sa, P->d_sc, P->d_sten, P->d_lm, P->d_rec_spin,
+    void *ptrs[] = {P->d_rings, P->d_pair_z, P->d_coef64, P->d_coef64s, P->d_sa, P->d_lm, P->d_rec_spin,
                     P->d_seed2, P->d_seedm2, P->d_seedk,
                     P->d_ent, P->d_entk, P->d_entl, P->d_wgstart, P->d_wgstart_b, P->d_coef32d, P->d_brec, P->d_brec_spin,
                     P->d_tw64, P->d_tw32, P->d_bhat64, P->d_bhat32, P->d_bhatr64, P->d_bhatr32, P->d_lof, P->d_order_p2, P->d_order_bl, P->d_order_bf, P->d_FG, P->d_part, P->d_rec, P->d_W, P->d_kern, P->d_kuser, P->d_red, P->d_red_cg, P->d_scal, P->d_flag, P->d_x, P->d_r,
@@ -674,23 +691,20 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
 
     // tables
     {
-        std::vector<Coef64> c64;
-        std::vector<Coef32D> c32d;
-        std::vector<Coef64S> c64s;
-        build_coef(lmax, c64, c32d, c64s);
-        AK_TRY(upload((void **)&P->d_coef64, c64.data(), c64.size() * sizeof(Coef64), *P));
-        AK_TRY(upload((void **)&P->d_coef64s, c64s.data(), c64s.size() * sizeof(Coef64S), *P));
-        if (prec == AKRA_FP32 && nrhs > 1)  // the batched near-polar groups
-            AK_TRY(upload((void **)&P->d_coef32d, c32d.data(), c32d.size() * sizeof(Coef32D), *P));
-    }
-    {
-        std::vector<double> sa, sc, sten;
-        std::vector<uint32_t> lm;
-        build_scalar(lmax, P->next, sa, sc, sten, lm);
-        AK_TRY(upload((void **)&P->d_sa, sa.data(), sa.size() * sizeof(double), *P));
-        AK_TRY(upload((void **)&P->d_sc, sc.data(), sc.size() * sizeof(double), *P));
-        AK_TRY(upload((void **)&P->d_sten, sten.data(), sten.size() * sizeof(double), *P));
-        AK_TRY(upload((void **)&P->d_lm, lm.data(), lm.size() * sizeof(uint32_t), *P));
+        const bool near = prec == AKRA_FP32 && nrhs > 1;  // the batched near-polar groups
+        SpinTables spin(lmax, near);
+        ScalarTables scal(lmax, P->next);
+        parallel_for(lmax + 1, [&](int m) {
+            spin.column(lmax, m);
+            scal.column(lmax, m);
+        });
+        AK_TRY(upload((void **)&P->d_coef64, spin.c64.data(), spin.c64.size() * sizeof(Coef64), *P));
+        AK_TRY(upload((void **)&P->d_coef64s, spin.c64s.data(), spin.c64s.size() * sizeof(Coef64S), *P));
+        if (near) AK_TRY(upload((void **)&P->d_coef32d, spin.c32d.data(), spin.c32d.size() * sizeof(Coef32D), *P));
+        AK_TRY(upload((void **)&P->d_sa, scal.tab.data(), scal.tab.size() * sizeof(double), *P));
+        P->d_sc = P->d_sa + (scal.sc() - scal.sa());
+        P->d_sten = P->d_sa + (scal.sten() - scal.sa());
+        AK_TRY(upload((void **)&P->d_lm, scal.lm.data(), scal.lm.size() * sizeof(uint32_t), *P));
     }
     {
         std::vector<double> s2, sm;
@@ -772,7 +786,7 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         int *dL = nullptr, *dM = nullptr;
         int64_t *dO = nullptr;
         AK_TRY(alloc(&P->d_bhat64, (size_t)btot * sizeof(double2), *P));
-        AK_TRY(alloc(&P->d_bhat32, (size_t)btot * sizeof(float2), *P));
+        if (prec == AKRA_FP32) AK_TRY(alloc(&P->d_bhat32, (size_t)btot * sizeof(float2), *P));
         const size_t nb = bL.size();
         bool ok = hipMalloc((void **)&dL, nb * sizeof(int)) == hipSuccess &&
                   hipMalloc((void **)&dM, nb * sizeof(int)) == hipSuccess &&
@@ -794,7 +808,7 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     }
     if (rtot > 0) {
         AK_TRY(alloc(&P->d_bhatr64, (size_t)rtot * sizeof(double2), *P));
-        AK_TRY(alloc(&P->d_bhatr32, (size_t)rtot * sizeof(float2), *P));
+        if (prec == AKRA_FP32) AK_TRY(alloc(&P->d_bhatr32, (size_t)rtot * sizeof(float2), *P));
         // sources, then destinations, of all lengths in one buffer
         std::vector<int64_t> sd;
         for (auto *v : {rsrc, rdst})
@@ -852,18 +866,12 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     P->rec_stride = P->next + ALM_PAD;
     // FP32 plans with several right-hand sides run their single-vector stages one right-hand side at a time
     const size_t nrec = prec == AKRA_FP32 && nrhs > 1 ? 1 : nrhs;
-    const size_t rec_b = nrec * P->rec_stride * 5 * sizeof(double), recs_b = nrec * (P->nalm + ALM_PAD) * 64;
-    AK_TRY(alloc((void **)&P->d_rec, rec_b, *P));
-    if (P->spin_groups > 0) AK_TRY(alloc(&P->d_rec_spin, recs_b, *P));
+    AK_TRY(alloc((void **)&P->d_rec, nrec * P->rec_stride * 5 * sizeof(double), *P));
+    if (P->spin_groups > 0) AK_TRY(alloc(&P->d_rec_spin, nrec * (P->nalm + ALM_PAD) * SPIN_REC * sizeof(double), *P));
     if (prec == AKRA_FP32 && nrhs > 1) {
         AK_TRY(alloc((void **)&P->d_brec, (size_t)P->rec_stride * NBR * 4 * sizeof(float), *P));
         if (P->spin_groups > 0)
             AK_TRY(alloc((void **)&P->d_brec_spin, (size_t)(P->nalm + ALM_PAD) * NBR * 4 * sizeof(float), *P));
-    }
-    if (hipMemset(P->d_rec, 0, rec_b) != hipSuccess || (P->d_rec_spin && hipMemset(P->d_rec_spin, 0, recs_b) != hipSuccess)) {
-        free_plan(P);
-        set_error("hipMemset failed");
-        return AKRA_ERR_HIP;
     }
     AK_TRY(alloc((void **)&P->d_W, (size_t)nrhs * P->npix * sizeof(double), *P));
     AK_TRY(alloc((void **)&P->d_red, (size_t)512 * 4 * nrhs * sizeof(double), *P));

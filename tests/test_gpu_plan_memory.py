@@ -20,3 +20,13 @@ def test_right_hand_side_of_a_batch(nside, lmax):
     need = 32 * nrings * (lmax + 1) + 8 * npix + 6 * 32 * nalm
     print("per right-hand side %.0f bytes, buffers %.0f" % (per, need), flush=True)
     assert per <= need + 40000
+
+
+@pytest.mark.parametrize("nside,lmax", [(65, 130), (200, 300)])
+def test_fp64_plans_hold_no_fp32_spectra(nside, lmax):
+    """Chirp spectra of the Bluestein rings in FP32 (a complex float per point of each distinct convolution) are an
+    FP32 plan's; the synthesis records take 40 and 48 bytes, the tables of the recurrences 60 + 64 per (l, m)."""
+    b64, b32 = _bytes(nside, lmax, "fp64", 1), _bytes(nside, lmax, "fp32", 1)
+    print("fp64 %d fp32 %d" % (b64, b32), flush=True)
+    lengths = [n for n in {4 * min(i, nside) for i in range(1, nside + 1)} if n & (n - 1)]
+    assert b32 - b64 >= sum(8 * (2 * n - 1) for n in lengths)
