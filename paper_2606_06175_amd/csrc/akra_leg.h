@@ -619,8 +619,7 @@ __global__ __launch_bounds__(256) void k_leg_synth(const double *__restrict__ re
 // degree was that of five to six ring pairs' FMAs and did not hide behind them.  Adjoint and epilogue
 // over all rings: Nside 2048, lmax 4096, 4 pairs per lane 10.7 -> 9.2 ms, 8 pairs 8.5 -> 7.9 ms (spin
 // form before: 13.8 ms); Nside 512, lmax 1024, 4 pairs 0.40 -> 0.25 ms.  What bounds it now is vector issue:
-// six instructions per pair and eleven for the reduction per degree, at 0.72 of the FMA rate; two or
-// three waves per SIMD make no difference.
+// six instructions per pair and eleven for the reduction per degree, at 0.72 of the FMA rate.
 // ga, gb: the values a slot contracts with.  Scalar form: a two-sided class holds north + south for
 // even l + m and north - south for odd, a one-sided class its ring's in ga.  Spin form: ga = (G_N,
 // conj H_N), gb = the south ring's.
@@ -659,10 +658,13 @@ __device__ __forceinline__ void adj_step(double ca, double cb, const double (&x)
 }
 
 // Occupancy the adjoint is compiled for (waves per SIMD).  A slot of the scalar form holds x, mu_l,
-// mu_{l-1} and four (one-sided) or eight values of G.
+// mu_{l-1} and four (one-sided) or eight values of G.  Six two-sided slots do not fit in the 168 registers of
+// three waves (202 spilled, 17 reloads per eight degrees; two waves: 7 spilled): all rings, two / three waves, FP64 and
+// FP32, ms, lmax 4096 7.80 / 8.27 and 7.57 / 7.90, lmax 2048 1.00 / 1.16 and 0.96 / 1.06.  Five two-sided slots (76
+// spilled) and eight one-sided (142) are as good or better with three: lmax 4096 8.12 / 7.75 and 7.29 / 6.96.
 template <int R, int CLS> struct AdjWaves {
     static constexpr bool two = CLS == GCLS_BOTH;
-    static constexpr int value = two ? (R <= 2 ? 4 : R <= 6 ? 3 : 2) : (R <= 4 ? 4 : R <= 8 ? 3 : 2);
+    static constexpr int value = two ? (R <= 2 ? 4 : R <= 5 ? 3 : 2) : (R <= 4 ? 4 : R <= 8 ? 3 : 2);
 };
 // LDS hand-over between the lanes of a workgroup.  A single-wave workgroup needs no s_barrier: the
 // LDS unit executes one wave's instructions in order, so a fence that keeps the compiler from moving
