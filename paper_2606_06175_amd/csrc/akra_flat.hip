@@ -37,10 +37,12 @@ constexpr int FL_MAXN = 8192;  // longest row a workgroup transforms in LDS (FP6
 constexpr int FL_RED = 1024;   // partial sums of the dot products
 
 constexpr int FCOL = 4;  // columns of a workgroup of the column pass
-// From FCOL_MIN_NY columns on four to a workgroup; fewer leave compute units idle, and one column each fills more
-// of them (CG step, us, one / four / transposed: 4096 x 16 39 / 57 / 46, 4096 x 256 78 / 92 / 92, 1024 x 64 29 / 32 / 36,
-// 4096 x 512 120 / 127 / 144, 4096 x 1024 229 / 224 / 268)
-constexpr int FCOL_MIN_NY = 512;
+// From fcol_min_ny columns on four to a workgroup; fewer leave compute units idle, and one column each fills more
+// of them.  A workgroup has nx / 16 or four times as many threads, so longer columns need more of them.  CG step, us,
+// one / four (transposed): 512 columns of 256 35.5 / 34.1 (41), of 512 43.6 / 43.5 (52), of 1024 49.5 / 50.2 (63), of 4096
+// 116 / 124 (139); 1024 of 256 36.6 / 37.3 (46), of 512 50.9 / 47.8 (61), of 1024 71 / 69 (89), of 4096 228 / 223 (267);
+// 256 of 1024 35.7 / 38.5 (45), of 4096 75 / 91 (90); 64 of 4096 48 / 67 (60).
+static int fcol_min_ny(int nx) { return nx < 1024 ? 512 : 1024; }
 static bool col_ok(int nx, int ny) { return nx >= 256 && nx <= 4096 && ny % FCOL == 0; }
 // row stride of the buffers between row and column passes: 256 bytes over ny, as the rows of one column, a power
 // of two apart, meet few memory channels (the column pass at 4096 x 4096 276 us against 317)
@@ -498,7 +500,7 @@ template <int MODE> static bool col_pass(FlatPlan &F, FRowArgs a)
     a.is = a.os = col_stride(F.nx, F.ny);
     auto go = [&](auto logm) {
         constexpr int LOGM = decltype(logm)::value, NT = FColShape<LOGM>::NT, LS = FColShape<LOGM>::LS;
-        if (F.ny < FCOL_MIN_NY)
+        if (F.ny < fcol_min_ny(F.nx))
             k_fcol<LOGM, MODE, 1><<<F.ny, NT, LS * sizeof(double), F.stream>>>(a);
         else
             k_fcol<LOGM, MODE, FCOL><<<F.ny / FCOL, FCOL * NT, FCOL * LS * sizeof(double), F.stream>>>(a);
