@@ -27,7 +27,7 @@ METRIC = "H·v applies/s + CG time-to-1e-8 at Nside 2048 ℓmax 4096, mixed/batc
 PEAK_FP64 = 78.6e12      # MI355X FP64 vector FMA, FLOP/s
 PEAK_FP32 = 157.3e12     # MI355X FP32 vector (packed) FMA, FLOP/s
 # per (l, m, ring pair) and direction, for both rings of the pair or one: a scalar recurrence step (a
-# multiply and an FMA) and 4 contraction FMAs.  The groups within 0.15 rad of a pole run two spin-weighted
+# multiply and an FMA) and 4 contraction FMAs.  The groups within 0.15 rad (or 40 / lmax) of a pole run two spin-weighted
 # recurrences and 8 (4) FMAs; they are counted at the same 11, which understates the rates a little.
 FLOP_PER_TRIPLE = 11
 

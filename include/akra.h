@@ -364,8 +364,9 @@ akra_status akra_set_ring_whole_maxm(int maxm);
 /*
  * Register engine of the ring stage for plans created afterwards (process-wide, not thread-safe
  * against concurrent akra_plan_create).  on != 0 (the default): rings whose transform length is 4096
- * or 8192 (whole power-of-two rings and whole-ring Bluestein convolutions) run the kernels that hold
- * a transform in registers and exchange through LDS; on = 0: every ring runs the LDS kernels.  The
+ * or 8192 (whole power-of-two rings, whole-ring Bluestein convolutions and split rings), and in plans of
+ * at least 640 rings (times the right-hand sides of a batch) those of 256 to 2048 points, run the kernels
+ * that hold a transform in registers and exchange through LDS; on = 0: every ring runs the LDS kernels.  The
  * results agree to rounding; the switch exists for tests and timing comparisons.  Returns AKRA_OK.
  */
 akra_status akra_set_ring_register_engine(int on);
@@ -506,8 +507,9 @@ akra_status akra_noise_spectra(akra_plan plan, int nset, const double *g1, const
 akra_status akra_ang2pix(akra_plan plan, const double *z, const double *phi, int64_t n, int32_t *pix);
 
 /* Device bytes of the workspace akra_pixelize needs for n_gal galaxies (0 <= n_gal < 2^31), written
- * to *bytes (HOST): a 32-byte record {w, w e1, w e2, w^2} per galaxy, pixel keys, their sorted copy
- * and galaxy order, per-pixel runs and the radix-sort storage.  Errors: AKRA_ERR_ARG. */
+ * to *bytes (HOST): a 32-byte record and the pixel of each galaxy and counts per pixel range; beyond 2^24
+ * pixels records, pixel keys, their sorted copy and galaxy order, per-pixel runs and the radix-sort
+ * storage.  Errors: AKRA_ERR_ARG. */
 akra_status akra_pixelize_work_size(akra_plan plan, int64_t n_gal, int64_t *bytes);
 
 /*

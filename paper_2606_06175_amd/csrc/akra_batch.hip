@@ -245,8 +245,9 @@ __global__ __launch_bounds__(64 * SW) void k_leg_synth_b(const float *__restrict
 // (right-hand side of the group, block) is written, [rhs - rhs0][nrb][next][4], rows from the chunk
 // holding the block's first entry degree (recorded in wgstart) to lmax + 2.
 // AW is a launch shape of the autotuner (2, 4 or 8): fewer waves in step with each other against more slabs for
-// the epilogue; with the epilogue 2 is the better or equal one throughout (all rings, ms: Nside 256, 16
-// right-hand sides 0.48 against 0.52 for 4; 512, 4: 0.52, 0.58; 1024, 16: 8.9, 9.0).  Bound by the chunk's serial
+// the epilogue.  Adjoint and epilogue of an iteration with four waves against two, footprint: Nside 256, 16 right-hand
+// sides 36 us longer, Nside 512, four 23 us and 16 18 us longer, Nside 1024, eight 180 us and 16 390 us shorter (slabs
+// dominate), which is what the autotuner finds.  Bound by the chunk's serial
 // path (rows, operands, products, the sum of the waves): 0.38 of the FP32 matrix rate at Nside 512, 0.55 at 1024.
 // Footprint, AW = 4: Nside 256, 16 right-hand sides 170 -> 102 us a group of eight with G loaded in
 // batches and a' by vector loads (scalar loads without look-ahead before), Nside 512, four 373 -> 283 us.
@@ -659,7 +660,7 @@ __global__ __launch_bounds__(64 * SW) __attribute__((amdgpu_waves_per_eu(2))) vo
 //   out_0,1 = D+[c] + s D-[c+2],   out_2,3 = D-[c-2] + s D+[c].
 // G is loaded once per wave into registers (it does not depend on l).  The waves of the block are
 // summed in LDS and one slab per (right-hand side of the group, block) is written,
-// [rhs - NBR q][nrb][nalm][4], rows from the chunk holding the block's first entry degree (recorded in
+// [rhs - NBR q][nrb][next][4] (nalm rows used), rows from the chunk holding the block's first entry degree (recorded in
 // wgstart) to lmax.
 // ================================================================================================
 // AW waves (64-pair groups) per workgroup is a launch shape of the autotuner (2, 4 or 8)
@@ -672,7 +673,7 @@ __global__ __launch_bounds__(64 * AW) __attribute__((amdgpu_waves_per_eu(2))) vo
                                                         const Ent64 *__restrict__ ent, const int *__restrict__ entk,
                                                         const int *__restrict__ entl, int ng64,
                                                         const double *__restrict__ pair_z, float *__restrict__ part,
-                                                        int *__restrict__ wgstart, int64_t nalm, int lmax, int npairs,
+                                                        int *__restrict__ wgstart, int lmax, int npairs,
                                                         int nrings, int nrhs, int q, const int *__restrict__ glist,
                                                         int ngl, const uint8_t *__restrict__ live, int rb0,
                                                         int nrbl, int nrb, int64_t slab)
@@ -858,8 +859,6 @@ __global__ __launch_bounds__(64 * AW) __attribute__((amdgpu_waves_per_eu(2))) vo
     }
 }
 
-
-
 // near-polar and other groups (n1, n2 of them) touch disjoint rings and slabs: the near-polar launch, few
 // waves with long recurrences, runs beside the other
 template <class A, class B> static void beside(Plan &P, int n1, int n2, A &&pol, B &&rest)
@@ -898,7 +897,7 @@ static void adj_b_launch(Plan &P, int q, int64_t fg_stride, const int *list, int
     auto pol = [&]() {
         k_spin_adj_b<AW><<<(unsigned)(8 * nbp * slots), 64 * AW, 0, P.stream>>>(
             (const float2 *)P.d_FG, fg_stride, P.d_coef32d, P.d_ent, P.d_entk, P.d_entl, P.ng64, P.d_pair_z,
-            (float *)P.d_part, P.d_wgstart_b, P.nalm, P.lmax, P.npairs, P.nrings, P.nrhs, q, list, npol, live, 0, nbp,
+            (float *)P.d_part, P.d_wgstart_b, P.lmax, P.npairs, P.nrings, P.nrhs, q, list, npol, live, 0, nbp,
             nrb, P.next);
     };
     auto main = [&](auto kern) {

@@ -18,7 +18,8 @@ namespace akra {
 // Scaled-exponent representation of the Wigner-d recurrence values.
 // A value is mant * 2^(UNIT * k) with an integer k <= 0.  While k < 0 the value is below
 // 2^-(UNIT/2) and contributes nothing; the mantissa is rescaled by 2^-UNIT whenever it exceeds
-// 2^(UNIT/2), and k then grows by one.  Once k == 0 the mantissa is the value itself.
+// 2^(UNIT/2), and k then grows by one.  Once k == 0 the mantissa is the value itself.  UNIT is 512, in the
+// batched kernels' FP32 recurrences 64.
 // ------------------------------------------------------------------------------------------------
 // padding (in entries) after the coefficient table and the kernel-scaled alm buffers
 constexpr int ALM_PAD = 64;
@@ -37,14 +38,6 @@ struct SpecArgs {
     const double2 *x[SPEC_NP];  // coefficient sets X of the pairs (m >= 0 storage)
     const double2 *y[SPEC_NP];  // coefficient sets Y
     double *cl[SPEC_NP];        // [lmax+1] outputs
-};
-
-template <typename T> struct Scale;
-template <> struct Scale<double> {
-    static constexpr int UNIT = 512;
-};
-template <> struct Scale<float> {
-    static constexpr int UNIT = 64;
 };
 
 // Per-(l, m) recurrence coefficients of the normalised spin-weighted functions
@@ -100,8 +93,9 @@ struct RingInfo {
     int nphi;      // pixels on the ring, N = 4 * sub
     int sub;       // N / 4: length of the four interleaved sub-transforms
     int shift;     // phi0 = pi * shift / N
-    int M;         // Bluestein FFT length (0: sub is a power of two): of the whole ring when the
-                   // ring is transformed whole, else of the sub-transform
+    int M;         // Bluestein FFT length, 0 where the ring is transformed directly (N a power of two, unless the
+                   // register engine takes it and N < 256): of the whole ring when the ring is
+                   // transformed whole, else of the sub-transform
     int64_t bofs;  // Bluestein rings: offset of the chirp spectrum of the transformed length
     int64_t rofs;  // Bluestein rings of the register engine: offset of that spectrum in register order
 };
@@ -133,7 +127,7 @@ enum { RG_DIRECT = 0, RG_BLUE = 6, RG_SPLIT = 12, RG_N = 14 };
 // spin and two further scalar parts rounds up by at most one block)
 constexpr int LIVE_NRB_EXTRA = 4;
 // values keying a recorded PCG iteration (see iter_key)
-constexpr int ITER_KEY_N = 18;
+constexpr int ITER_KEY_N = 16;
 struct RingSet {
     const int *order[RING_KINDS] = {};
     int n[RING_KINDS] = {};
@@ -204,7 +198,7 @@ struct Plan {
                                              // batched kernels per right-hand side
 
     // Legendre launch shapes
-    int syn_R = 1, syn_V = 1, syn_groups = 1;  // syn_V: kept and reported, selects nothing
+    int syn_R = 1, syn_V = 1;  // syn_V: kept and reported, selects nothing
     int adj_R = 1, adj_W = 1, adj_L = 8, adj_nrb = 1;
     // the shapes of groups weighted on one side only (GCLS_NORTH, GCLS_SOUTH), tuned apart: they
     // read half the values of F or G
@@ -442,7 +436,6 @@ void launch_cg_xr_alpha(Plan &P, double *x, double *r, const double *p, const do
                         int64_t n_complex, const CgList &L);
 void launch_cg_p_beta(Plan &P, double *p, const double *r, double *scal, int64_t n_complex, const CgList &L);
 void launch_axpby(Plan &P, double *y, double a, const double *x, double b, int64_t n_complex);
-void launch_scalar_div(Plan &P, double *out, const double *num, const double *den);
 // shape-noise realisations and spectra (akra_spectra.hip)
 // ascending indices of the unmasked pixels into idx (capacity npix), their count into d_cmp_nobs
 void launch_unmasked_index(Plan &P, const uint8_t *mask, int32_t *idx);
@@ -455,7 +448,8 @@ void launch_spectra(Plan &P, const SpecArgs &a, int n);
 // mean and sample standard deviation over n realisations of len values (either output nullable)
 void launch_cl_moments(Plan &P, const double *cl, int n, int64_t len, double *mean, double *sd);
 // catalogue pixelisation (akra_pixel.hip)
-// device bytes of the pixelisation workspace for n_gal galaxies (sort keys, runs, sort storage)
+// device bytes of the pixelisation workspace for n_gal galaxies: records, pixels and bucket counts, or beyond
+// BUCKET_NPIX pixels records, sort keys, runs and sort storage
 hipError_t pixelize_work_bytes(Plan &P, int64_t n_gal, int64_t *bytes);
 // where the pixel keys and the galaxy records live inside that workspace
 uint32_t *pixelize_keys(Plan &P, int64_t n, void *work, double4 **rec);

@@ -977,8 +977,6 @@ __global__ void k_axpby(double *__restrict__ y, double a, const double *__restri
         y[i] = a * x[i] + b * y[i];
 }
 
-__global__ void k_scalar_div(double *out, const double *num, const double *den) { *out = *num / *den; }
-
 // ================================================================================================
 // launchers
 // ================================================================================================
@@ -1332,11 +1330,6 @@ void launch_cg_p(Plan &P, double *p, const double *r, const double *beta_dev, do
 void launch_axpby(Plan &P, double *y, double a, const double *x, double b, int64_t n_complex)
 {
     k_axpby<<<1024, 256, 0, P.stream>>>(y, a, x, b, 2 * n_complex);
-}
-
-void launch_scalar_div(Plan &P, double *out, const double *num, const double *den)
-{
-    k_scalar_div<<<1, 1, 0, P.stream>>>(out, num, den);
 }
 
 }  // namespace akra

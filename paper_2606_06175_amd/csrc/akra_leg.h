@@ -6,16 +6,16 @@
 // Two forms.  With W = (2lambda + -2lambda) / 2 and X = (2lambda - -2lambda) / 2, and the scalar functions
 // l_lm = sqrt((2l+1)/4pi) d^l_{m0}(theta),
 //   sin^2(theta) W_lm = w_2 l_{l+2} + w_0 l_l + w_-2 l_{l-2},   sin^2(theta) X_lm = x_1 l_{l+1} + x_-1 l_{l-1}
-// with coefficients that depend on (l, m) only (see Stencil).  So sin^2(theta) gamma_1 and
+// with coefficients that depend on (l, m) only (see akra_internal.h).  So sin^2(theta) gamma_1 and
 // sin^2(theta) gamma_2 are synthesised from scalar functions of degrees m .. lmax + 2, whose
 // coefficients the prologue forms by a five-point stencil in l, and the adjoint is the transpose.
 //   FORM_SCALAR, rings away from the poles: one recurrence of two instructions per degree (no b term)
 //   and four multiply-adds serve both rings of a pair, against two recurrences of two FMAs each and
 //   eight (one ring: four) multiply-adds in the spin form.
-//   FORM_SPIN, the 64-pair groups that begin within AKRA_POLE_THETA of a pole: there the terms of the
-//   scalar sums cancel to sin^2(theta) of their size, and the spin-weighted functions themselves are run.
-// Both are bounded by FP64 vector issue: the operands of a step are one scalar-loaded record and
-// registers.  Every plan runs them in FP64: a plain FP32 FMA issues at the FP64 rate on this part
+//   FORM_SPIN, the 64-pair groups that begin within AKRA_POLE_THETA or AKRA_POLE_X / lmax of a pole: there the
+//   terms of the scalar sums cancel to sin^2(theta) of their size, and the spin-weighted functions themselves are run.
+// Both are bounded by FP64 vector issue: the operands of a step are registers and one record, which
+// the scalar synthesis reads from the lanes of a vector register and the others by scalar loads.  Every plan runs them in FP64: a plain FP32 FMA issues at the FP64 rate on this part
 // (akra_fma_rate: 72 and 76 TFLOP/s), and an FP32 recurrence needs its coordinate as two floats, so
 // FP32 arithmetic here costs more instructions for less precision.  FP32 plans store F, G and the
 // partial sums as floats.

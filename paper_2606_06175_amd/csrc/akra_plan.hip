@@ -205,7 +205,7 @@ struct ScalarTables {
 //   d^m_{m,-2} = t_m (s/c)^4;  for m < 2: d^2_{0,+-2} = sqrt6 c^2 s^2, d^2_{1,2} = 2 c^3 s, d^2_{1,-2} = -2 c s^3.
 // c = cos(theta/2), s = sin(theta/2).  Scalar groups: l_mm = sqrt((2m+1)/4pi) t_m, t_0 = 1,
 //   t_{m+1} = -t_m sqrt((2m+1)/(2m+2)) sin(theta).  Long double with explicit binary exponents; stored as
-// mant * 2^(512 k) (see Scale<double>).
+// mant * 2^(512 k).
 // ---------------------------------------------------------------------------------------------
 static void build_seeds(Plan &P, std::vector<double> &s2, std::vector<double> &sm, std::vector<int> &sk)
 {
@@ -669,7 +669,6 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
 
     // Legendre launch shapes
     P->syn_R = P->npairs >= 256 ? 2 : 1;
-    P->syn_groups = (P->npairs + 64 * P->syn_R - 1) / (64 * P->syn_R);
     // pairs per lane of the adjoint: as many as leave two waves per SIMD (2048 waves), at most six
     P->adj_R = (int)std::min<int64_t>(6, std::max<int64_t>(1, (int64_t)(P->ng64 - P->spin_groups) * (lmax + 1) / 2048));
     P->adj_nrb = adj_nrb_of(*P);
@@ -1191,9 +1190,9 @@ static akra_status cg_iterate(Plan &P, bool fp32)
 static void iter_key(const Plan &P, bool fp32, double *k)
 {
     const double v[ITER_KEY_N] = {(double)fp32, (double)P.cg_rhs, (double)P.proj, P.cg_lam, P.cg_pc,
-                                  (double)(uintptr_t)P.cg_kern, (double)P.syn_V, (double)P.syn_R, (double)P.adj_R,
+                                  (double)(uintptr_t)P.cg_kern, (double)P.syn_R, (double)P.adj_R,
                                   (double)P.adj_W, (double)P.adj_L, (double)P.adj_nrb, (double)P.live_gen,
-                                  (double)P.syn_V1, (double)P.syn_R1, (double)P.adj_R1, (double)P.adj_W1,
+                                  (double)P.syn_R1, (double)P.adj_R1, (double)P.adj_W1,
                                   (double)P.adj_L1};
     std::memcpy(k, v, sizeof v);
 }
@@ -1732,11 +1731,11 @@ static akra_status solve_batched(Plan &P, const double *g1, const double *g2, co
             // replay of the recorded iteration; recorded again when a by-value argument or the active
             // set has changed
             std::vector<double> key;
-            key.reserve(9 + 3 * (size_t)nr);
+            key.reserve(13 + 3 * (size_t)nr);
             key.push_back((double)(uintptr_t)kd);
             key.push_back((double)P.proj);
             key.push_back((double)nr);
-            for (int v : {P.syn_V, P.syn_R, P.adj_R, P.adj_W, P.adj_L, P.adj_nrb, P.live_gen, P.syn_V1, P.syn_R1,
+            for (int v : {P.syn_R, P.adj_R, P.adj_W, P.adj_L, P.adj_nrb, P.live_gen, P.syn_R1,
                           P.adj_R1, P.adj_W1, P.adj_L1})
                 key.push_back((double)v);
             for (int r = 0; r < nr; ++r) {
