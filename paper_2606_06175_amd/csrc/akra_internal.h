@@ -167,9 +167,7 @@ struct Plan {
     void *d_bhat64 = nullptr, *d_bhat32 = nullptr;  // Bluestein chirp spectra per distinct sub length (FP32 plans: both)
     int twn = 1;
     int *d_lof = nullptr;  // l of every alm index
-    int *d_order_p2 = nullptr, *d_order_bl = nullptr, *d_order_bf = nullptr;
-    int n_p2 = 0, n_bl = 0, n_bf = 0, maxM_p2 = 1, maxM_bl = 1, maxM_bf = 1;
-    int *d_order_r[RG_N] = {};  // rings of the register engine by list
+    int maxM_p2 = 1, maxM_bl = 1, maxM_bf = 1;
     void *d_bhatr64 = nullptr, *d_bhatr32 = nullptr;  // their chirp spectra in register order
     std::vector<RingInfo> h_rings;
 
@@ -181,7 +179,7 @@ struct Plan {
     RingSet rs_cls[2];
     GroupSet gs_all, gs_live;
     std::vector<int> h_order[RING_KINDS];  // host copies of the rings of every kind
-    int *d_gl_all = nullptr;      // [ng64] 0, 1, .., ng64 - 1
+    int *d_gl_all = nullptr;      // one buffer: [ng64] 0, 1, .., ng64 - 1, then the ring lists by kind (rs_all)
     int *d_live_lists = nullptr;  // [RING_KINDS][nrings] ring lists, then [GCLS_N + 1][ng64] group lists
     uint8_t *d_ring_live = nullptr;  // [nrings] 1: the ring carries weight in some right-hand side's W
     uint8_t *h_live = nullptr;       // pinned: the flags read back, then the lists staged for upload

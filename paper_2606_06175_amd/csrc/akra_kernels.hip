@@ -1141,7 +1141,7 @@ void launch_cg_p_beta(Plan &P, double *p, const double *r, double *scal, int64_t
 
 // The ring kinds of a RingSet: RK_P2 whole power-of-two rings (LDS FFT), RK_BF whole-ring Bluestein,
 // RK_BL rings split into two half-length Bluestein transforms, RK_REG + q the register engine's
-// lists (see Plan::d_order_r)
+// lists (see akra_internal.h)
 template <typename T, int MODE>
 static void ring_launch_t(Plan &P, const RingSet &RS, const double *g1, const double *g2, double *o1, double *o2,
                           const double *W, double *o3, const uint8_t *mask, const double *cdev, int nrhs,

@@ -492,12 +492,10 @@ static void free_plan(Plan *P)
     void *ptrs[] = {P->d_rings, P->d_pair_z, P->d_coef64, P->d_coef64s, P->d_sa, P->d_lm, P->d_rec_spin,
                     P->d_seed2, P->d_seedm2, P->d_seedk,
                     P->d_ent, P->d_entk, P->d_entl, P->d_wgstart, P->d_wgstart_b, P->d_coef32d, P->d_brec, P->d_brec_spin,
-                    P->d_tw64, P->d_tw32, P->d_bhat64, P->d_bhat32, P->d_bhatr64, P->d_bhatr32, P->d_lof, P->d_order_p2, P->d_order_bl, P->d_order_bf, P->d_FG, P->d_part, P->d_rec, P->d_W, P->d_kern, P->d_kuser, P->d_red, P->d_red_cg, P->d_scal, P->d_flag, P->d_x, P->d_r,
+                    P->d_tw64, P->d_tw32, P->d_bhat64, P->d_bhat32, P->d_bhatr64, P->d_bhatr32, P->d_lof, P->d_FG, P->d_part, P->d_rec, P->d_W, P->d_kern, P->d_kuser, P->d_red, P->d_red_cg, P->d_scal, P->d_flag, P->d_x, P->d_r,
                     P->d_p, P->d_w, P->d_b, P->d_xs, P->d_cmp, P->d_spec, P->d_gl_all, P->d_live_lists,
                     P->d_ring_live};
     for (void *q : ptrs)
-        if (q) (void)hipFree(q);
-    for (int *q : P->d_order_r)
         if (q) (void)hipFree(q);
     if (P->h_pin) (void)hipHostFree(P->h_pin);
     if (P->h_live) (void)hipHostFree(P->h_live);
@@ -610,9 +608,6 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     P->h_order[RK_BF] = bf;
     P->h_order[RK_BL] = bl;
     for (int q = 0; q < RG_N; ++q) P->h_order[RK_REG + q] = rl[q];
-    P->n_p2 = (int)p2.size();
-    P->n_bl = (int)bl.size();
-    P->n_bf = (int)bf.size();
     P->maxM_p2 = maxp2;
     P->maxM_bl = maxbl;
     P->maxM_bf = maxbf;
@@ -718,20 +713,17 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         for (int p = 0; p < P->npairs; ++p) pz[p] = P->h_rings[p].z;
         AK_TRY(upload((void **)&P->d_pair_z, pz.data(), pz.size() * sizeof(double), *P));
         AK_TRY(upload((void **)&P->d_rings, P->h_rings.data(), P->h_rings.size() * sizeof(RingInfo), *P));
-        AK_TRY(upload((void **)&P->d_order_p2, p2.data(), p2.size() * sizeof(int), *P));
-        AK_TRY(upload((void **)&P->d_order_bl, bl.data(), bl.size() * sizeof(int), *P));
-        AK_TRY(upload((void **)&P->d_order_bf, bf.data(), bf.size() * sizeof(int), *P));
-        for (int q = 0; q < RG_N; ++q)
-            if (!rl[q].empty()) AK_TRY(upload((void **)&P->d_order_r[q], rl[q].data(), rl[q].size() * sizeof(int), *P));
-        P->rs_all.order[RK_P2] = P->d_order_p2;
-        P->rs_all.order[RK_BF] = P->d_order_bf;
-        P->rs_all.order[RK_BL] = P->d_order_bl;
-        for (int q = 0; q < RG_N; ++q) P->rs_all.order[RK_REG + q] = P->d_order_r[q];
-        for (int k = 0; k < RING_KINDS; ++k) P->rs_all.n[k] = (int)P->h_order[k].size();
-        // every group in one list (the transforms without weights), polar groups first
+        // every group in one list (the transforms without weights), spin-form groups first; then the ring lists
         std::vector<int> ids(P->ng64);
         for (int g = 0; g < P->ng64; ++g) ids[g] = g;
+        for (const auto &v : P->h_order) ids.insert(ids.end(), v.begin(), v.end());
         AK_TRY(upload((void **)&P->d_gl_all, ids.data(), ids.size() * sizeof(int), *P));
+        const int *at = P->d_gl_all + P->ng64;
+        for (int k = 0; k < RING_KINDS; ++k) {
+            P->rs_all.order[k] = at;
+            P->rs_all.n[k] = (int)P->h_order[k].size();
+            at += P->rs_all.n[k];
+        }
         GroupSet &A = P->gs_all;
         A.list[GCLS_BOTH] = A.list_any = P->d_gl_all;
         A.npol[GCLS_BOTH] = A.npol_any = P->spin_groups;
