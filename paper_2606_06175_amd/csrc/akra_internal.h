@@ -207,6 +207,8 @@ struct Plan {
     // adjoint; nrb_b adjoint ring blocks of bat_AW groups (the buffers hold those of bat_AW = 2)
     int bat_SW = 4, bat_AW = 2, nrb_b_cap = 0;
 
+    std::vector<void *> work_alloc;  // the allocations behind the workspaces and solver vectors below
+
     // workspaces (sized for FP64; FP32 views reuse them)
     void *d_FG = nullptr;       // [nrhs][nrings][lmax+1][2] complex
     void *d_part = nullptr;     // [nrb][next][4] adjoint partial sums (spin blocks fill [nalm][4] of theirs)

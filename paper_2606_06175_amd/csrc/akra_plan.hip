@@ -342,6 +342,44 @@ static akra_status alloc(void **dst, size_t bytes, Plan &P)
     return AKRA_OK;
 }
 
+// A plan's workspaces come from one allocation while they are small: the driver maps every allocation above 2 MB by
+// itself, 0.1 to 0.3 ms each (Nside 80, lmax 109, 12 right-hand sides, plans made while others live, 7.1 ms with 22 allocations, 5.3 with one).  Above
+// WORK_SPLIT bytes each has its own, as one mapping is nothing beside filling them.
+constexpr size_t WORK_SPLIT = (size_t)256 << 20;
+struct Workspaces {
+    struct Item {
+        void **dst;
+        size_t bytes;
+    };
+    std::vector<Item> items;
+    void add(void **dst, size_t bytes) { items.push_back({dst, bytes}); }
+    akra_status take(Plan &P)
+    {
+        size_t total = 0;
+        auto padded = [](size_t b) { return (std::max<size_t>(b, 16) + 4095) / 4096 * 4096; };
+        for (const Item &i : items) total += padded(i.bytes);
+        if (total > WORK_SPLIT) {
+            for (const Item &i : items) {
+                void *q = nullptr;
+                akra_status st = alloc(&q, i.bytes, P);
+                if (st) return st;
+                P.work_alloc.push_back(q);
+                *i.dst = q;
+            }
+            return AKRA_OK;
+        }
+        char *c = nullptr;
+        AK_HIP(hipMalloc((void **)&c, total), "hipMalloc");
+        P.work_alloc.push_back(c);
+        for (const Item &i : items) {
+            *i.dst = c;
+            c += padded(i.bytes);
+            P.device_bytes += (int64_t)i.bytes;
+        }
+        return AKRA_OK;
+    }
+};
+
 static void default_kernel(int lmax, std::vector<double> &k)
 {
     // K_l = sigma_D D_l, sigma_D = -1, D_l = -sqrt((l-1)(l+2)/(l(l+1))) (eq. Dl_kernel), K_0 = K_1 = 0
@@ -489,14 +527,13 @@ static akra_status build_live_lists(Plan &P)
 
 static void free_plan(Plan *P)
 {
-    void *ptrs[] = {P->d_rings, P->d_pair_z, P->d_coef64, P->d_coef64s, P->d_sa, P->d_lm, P->d_rec_spin,
-                    P->d_seed2, P->d_seedm2, P->d_seedk,
-                    P->d_ent, P->d_entk, P->d_entl, P->d_wgstart, P->d_wgstart_b, P->d_coef32d, P->d_brec, P->d_brec_spin,
-                    P->d_tw64, P->d_tw32, P->d_bhat64, P->d_bhat32, P->d_bhatr64, P->d_bhatr32, P->d_lof, P->d_FG, P->d_part, P->d_rec, P->d_W, P->d_kern, P->d_kuser, P->d_red, P->d_red_cg, P->d_scal, P->d_flag, P->d_x, P->d_r,
-                    P->d_p, P->d_w, P->d_b, P->d_xs, P->d_cmp, P->d_spec, P->d_gl_all, P->d_live_lists,
-                    P->d_ring_live};
+    void *ptrs[] = {P->d_rings, P->d_pair_z, P->d_coef64, P->d_coef64s, P->d_sa, P->d_lm, P->d_seed2, P->d_seedm2,
+                    P->d_seedk, P->d_ent, P->d_entk, P->d_entl, P->d_coef32d, P->d_tw64, P->d_tw32, P->d_bhat64,
+                    P->d_bhat32, P->d_bhatr64, P->d_bhatr32, P->d_lof, P->d_kern, P->d_kuser, P->d_gl_all,
+                    P->d_live_lists, P->d_ring_live};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
+    for (void *q : P->work_alloc) (void)hipFree(q);
     if (P->h_pin) (void)hipHostFree(P->h_pin);
     if (P->h_live) (void)hipHostFree(P->h_live);
     for (auto &e : P->ev_pool) {
@@ -832,8 +869,9 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         AK_TRY(upload((void **)&P->d_kuser, ones.data(), ones.size() * sizeof(double), *P));
     }
     // workspaces
+    Workspaces ws;
     const size_t fg = (size_t)nrhs * P->nrings * (lmax + 1) * 2 * sizeof(double2);
-    AK_TRY(alloc(&P->d_FG, fg, *P));
+    ws.add((void **)&P->d_FG, fg);
     // the class lists of a weighted apply split the groups in up to three polar and three main parts,
     // each rounded up to whole blocks: at most LIVE_NRB_EXTRA blocks more than the unsplit layout
     P->part_rb_cap = (size_t)std::max(P->adj_nrb, (P->spin_groups + 1) / 2 + (P->npairs <= 1024 ? P->ng64 : (P->ng64 + 3) / 4)) +
@@ -844,10 +882,10 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         P->nrb_b = (P->spin_groups + P->bat_AW - 1) / P->bat_AW + (P->ng64 - P->spin_groups + P->bat_AW - 1) / P->bat_AW;
         P->nrb_b_cap = (P->spin_groups + 1) / 2 + (P->ng64 - P->spin_groups + 1) / 2;
         P->part_rb_cap = std::max(P->part_rb_cap, (size_t)4 * P->nrb_b_cap);
-        AK_TRY(alloc((void **)&P->d_wgstart_b, (size_t)P->nrb_b_cap * (lmax + 1) * sizeof(int), *P));
+        ws.add((void **)&P->d_wgstart_b, (size_t)P->nrb_b_cap * (lmax + 1) * sizeof(int));
     }
-    AK_TRY(alloc(&P->d_part, P->part_rb_cap * P->next * 4 * sizeof(double), *P));
-    AK_TRY(alloc((void **)&P->d_wgstart, P->part_rb_cap * (lmax + 1) * sizeof(int), *P));
+    ws.add((void **)&P->d_part, P->part_rb_cap * P->next * 4 * sizeof(double));
+    ws.add((void **)&P->d_wgstart, P->part_rb_cap * (lmax + 1) * sizeof(int));
     compute_work(*P);
     // before any weight set-up every ring counts, in two-ring groups
     P->n_live_rings = P->nrings;
@@ -857,43 +895,44 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     P->rec_stride = P->next + ALM_PAD;
     // FP32 plans with several right-hand sides run their single-vector stages one right-hand side at a time
     const size_t nrec = prec == AKRA_FP32 && nrhs > 1 ? 1 : nrhs;
-    AK_TRY(alloc((void **)&P->d_rec, nrec * P->rec_stride * 5 * sizeof(double), *P));
-    if (P->spin_groups > 0) AK_TRY(alloc(&P->d_rec_spin, nrec * (P->nalm + ALM_PAD) * SPIN_REC * sizeof(double), *P));
+    ws.add((void **)&P->d_rec, nrec * P->rec_stride * 5 * sizeof(double));
+    if (P->spin_groups > 0) ws.add((void **)&P->d_rec_spin, nrec * (P->nalm + ALM_PAD) * SPIN_REC * sizeof(double));
     if (prec == AKRA_FP32 && nrhs > 1) {
-        AK_TRY(alloc((void **)&P->d_brec, (size_t)P->rec_stride * NBR * 4 * sizeof(float), *P));
+        ws.add((void **)&P->d_brec, (size_t)P->rec_stride * NBR * 4 * sizeof(float));
         if (P->spin_groups > 0)
-            AK_TRY(alloc((void **)&P->d_brec_spin, (size_t)(P->nalm + ALM_PAD) * NBR * 4 * sizeof(float), *P));
+            ws.add((void **)&P->d_brec_spin, (size_t)(P->nalm + ALM_PAD) * NBR * 4 * sizeof(float));
     }
-    AK_TRY(alloc((void **)&P->d_W, (size_t)nrhs * P->npix * sizeof(double), *P));
-    AK_TRY(alloc((void **)&P->d_red, (size_t)512 * 4 * nrhs * sizeof(double), *P));
-    AK_TRY(alloc((void **)&P->d_red_cg, (size_t)2 * CG_RED_BLOCKS * nrhs * sizeof(double), *P));
-    AK_TRY(alloc((void **)&P->d_scal, (size_t)(64 + 16 * nrhs) * sizeof(double), *P));
-    AK_TRY(alloc((void **)&P->d_flag, 64 * sizeof(int), *P));
+    ws.add((void **)&P->d_W, (size_t)nrhs * P->npix * sizeof(double));
+    ws.add((void **)&P->d_red, (size_t)512 * 4 * nrhs * sizeof(double));
+    ws.add((void **)&P->d_red_cg, (size_t)2 * CG_RED_BLOCKS * nrhs * sizeof(double));
+    ws.add((void **)&P->d_scal, (size_t)(64 + 16 * nrhs) * sizeof(double));
+    ws.add((void **)&P->d_flag, 64 * sizeof(int));
     // unmasked-pixel list scratch: count and flag, then per-tile counts and offsets
     P->cmp_ntile = (P->npix + CMP_TILE - 1) / CMP_TILE;
+    const size_t cmp_nt = (size_t)P->cmp_ntile, cmp_cnt = (cmp_nt * sizeof(int) + 255) / 256 * 256;
+    ws.add((void **)&P->d_cmp, 256 + cmp_cnt + cmp_nt * sizeof(int64_t));
+    P->spec_nmc = (lmax + SPEC_MC) / SPEC_MC;
+    ws.add((void **)&P->d_spec, (size_t)SPEC_NP * P->spec_nmc * (lmax + 1) * sizeof(double));
+    const size_t vb = (size_t)nrhs * 2 * P->nalm * sizeof(double2);
+    ws.add((void **)&P->d_x, vb);
+    ws.add((void **)&P->d_r, vb);
+    ws.add((void **)&P->d_p, vb);
+    ws.add((void **)&P->d_w, vb);
+    ws.add((void **)&P->d_b, vb);
+    ws.add((void **)&P->d_xs, vb);
+    AK_TRY(ws.take(*P));
     {
-        const size_t nt = (size_t)P->cmp_ntile, cnt_b = (nt * sizeof(int) + 255) / 256 * 256;
-        AK_TRY(alloc(&P->d_cmp, 256 + cnt_b + nt * sizeof(int64_t), *P));
         char *b = (char *)P->d_cmp;
         P->d_cmp_nobs = (int64_t *)b;
         P->d_cmp_flag = (int *)(b + 64);
         P->d_cmp_cnt = (int *)(b + 256);
-        P->d_cmp_offs = (int64_t *)(b + 256 + cnt_b);
+        P->d_cmp_offs = (int64_t *)(b + 256 + cmp_cnt);
         if (hipMemset(P->d_cmp, 0, 256) != hipSuccess) {
             free_plan(P);
             set_error("hipMemset failed");
             return AKRA_ERR_HIP;
         }
     }
-    P->spec_nmc = (lmax + SPEC_MC) / SPEC_MC;
-    AK_TRY(alloc((void **)&P->d_spec, (size_t)SPEC_NP * P->spec_nmc * (lmax + 1) * sizeof(double), *P));
-    const size_t vb = (size_t)nrhs * 2 * P->nalm * sizeof(double2);
-    AK_TRY(alloc((void **)&P->d_x, vb, *P));
-    AK_TRY(alloc((void **)&P->d_r, vb, *P));
-    AK_TRY(alloc((void **)&P->d_p, vb, *P));
-    AK_TRY(alloc((void **)&P->d_w, vb, *P));
-    AK_TRY(alloc((void **)&P->d_b, vb, *P));
-    AK_TRY(alloc((void **)&P->d_xs, vb, *P));
     if (hipStreamCreateWithFlags(&P->side_stream, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&P->ev_fork, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&P->ev_join, hipEventDisableTiming) != hipSuccess) {
