@@ -120,9 +120,18 @@ struct GroupSet {
 // rings of one ring-stage launch set, by kernel kind: whole power-of-two rings in LDS (RK_P2), whole-ring
 // Bluestein (RK_BF), two half-length Bluestein transforms (RK_BL), and the register engine's lists
 // (RK_REG + q): q = RG_DIRECT + j whole rings of M = 2^(8 + j) points, RG_BLUE + j whole-ring Bluestein of
-// M points (j = 0 .. 5), RG_SPLIT + j two half-length Bluestein transforms of 4096 and 8192 points (j = 0, 1)
-enum { RK_P2 = 0, RK_BF = 1, RK_BL = 2, RK_REG = 3, RING_KINDS = 17 };
+// M points (j = 0 .. 5), RG_SPLIT + j two half-length Bluestein transforms of 4096 and 8192 points (j = 0, 1).
+// Plans whose launches lie on both sides of RING_ENGINE_MIN also list every ring for the LDS kernels
+// (RK_FEW_P2, RK_FEW_BF), which then take the launches of fewer.
+enum { RK_P2 = 0, RK_BF = 1, RK_BL = 2, RK_REG = 3, RK_FEW_P2 = 17, RK_FEW_BF = 18, RING_KINDS = 19 };
 enum { RG_DIRECT = 0, RG_BLUE = 6, RG_SPLIT = 12, RG_N = 14 };
+// From this many rings in a launch (times its right-hand sides) on the register engine takes transforms below 4096
+// points.  It runs 2 to 16 rings in a workgroup of 256 threads, which below that leaves most of the 256 compute
+// units idle, while the LDS kernel gives a ring 1024 threads and a compute unit of its own.  CG iteration, us, register
+// engine / LDS: one right-hand side, full sky, FP64, Nside 32 66.9 / 53.5, 64 85.3 / 64.9, 128 107.2 / 95.3, 160 (639
+// rings) 124.3 / 133.6, 200 152.1 / 168.3; three, footprint, Nside 48 108.7 / 100.7, 64 108.5 / 107.3, 96 78.7 / 90.8;
+// eight, Nside 16 93.6 / 87.4, 24 89.9 / 94.2.  Synthesis of 16 maps in FP64, Nside 32 46 / 59, 64 73 / 119, 100 111 / 236.
+constexpr int RING_ENGINE_MIN = 640;
 // ring blocks a class-split adjoint may write beyond the unsplit layout (each of up to two further
 // spin and two further scalar parts rounds up by at most one block)
 constexpr int LIVE_NRB_EXTRA = 4;

@@ -1150,15 +1150,18 @@ static void ring_launch_t(Plan &P, const RingSet &RS, const double *g1, const do
     const int64_t fg_stride = (int64_t)P.nrings * (P.lmax + 1) * 2;
     const void *tw = std::is_same<T, double>::value ? P.d_tw64 : P.d_tw32;
     const cplx<T> *bh = (const cplx<T> *)(std::is_same<T, double>::value ? P.d_bhat64 : P.d_bhat32);
-    if (RS.n[RK_P2] + RS.n[RK_BF]) {
+    // (a plan without the lists for fewer rings keeps the others in every launch)
+    const bool few = RS.n[RK_FEW_P2] + RS.n[RK_FEW_BF] > 0 && (int64_t)P.nrings * nrhs < RING_ENGINE_MIN;
+    const int kp = few ? RK_FEW_P2 : RK_P2, kb = few ? RK_FEW_BF : RK_BF;
+    if (RS.n[kp] + RS.n[kb]) {
         // power-of-two rings: N = 4 sub <= 4 nside <= 8192 = RF RFU (nside <= 2048 is enforced at plan creation)
         size_t nmax = RF;  // the short-ring fold
-        if (RS.n[RK_P2]) nmax = std::max(nmax, 4 * (size_t)P.maxM_p2);
-        if (RS.n[RK_BF]) nmax = std::max(nmax, (size_t)P.maxM_bf);
+        if (RS.n[kp]) nmax = std::max(nmax, 4 * (size_t)P.maxM_p2);
+        if (RS.n[kb]) nmax = std::max(nmax, (size_t)P.maxM_bf);
         const size_t sm = sizeof(cplx<T>) * (nmax + nmax / 32);
-        k_ring_lds<T, MODE><<<dim3(RS.n[RK_BF] + RS.n[RK_P2], nrhs), RF, sm, P.stream>>>(
+        k_ring_lds<T, MODE><<<dim3(RS.n[kb] + RS.n[kp], nrhs), RF, sm, P.stream>>>(
             (cplx<T> *)P.d_FG, fg_stride, RingArgs{g1, g2, o1, o2, W, o3, mask, cdev}, P.npix, P.d_rings,
-            RS.order[RK_BF], RS.n[RK_BF], RS.order[RK_P2], (const cplx<T> *)tw, P.twn, P.lmax, P.omega, bh);
+            RS.order[kb], RS.n[kb], RS.order[kp], (const cplx<T> *)tw, P.twn, P.lmax, P.omega, bh);
     }
     if (RS.n[RK_BL]) {
         size_t sm = sizeof(cplx<T>) * (size_t)(P.maxM_bl + P.maxM_bl / 32);
@@ -1166,6 +1169,7 @@ static void ring_launch_t(Plan &P, const RingSet &RS, const double *g1, const do
             (cplx<T> *)P.d_FG, fg_stride, g1, g2, o1, o2, P.npix, W, P.d_rings, RS.order[RK_BL], (const cplx<T> *)tw,
             P.twn, P.lmax, P.omega, o3, mask, cdev, bh);
     }
+    if (few) return;  // every whole ring is done; longer transforms than 2048 points have no such plan
     ring16_launch<T, MODE>(P, RS, RingArgs{g1, g2, o1, o2, W, o3, mask, cdev}, nrhs, split);
 }
 

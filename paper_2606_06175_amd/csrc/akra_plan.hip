@@ -29,13 +29,6 @@ constexpr double AKRA_POLE_THETA = 0.15, AKRA_POLE_X = 40.0;
 // The batched kernels sum in FP32, whose rounding the division by sin^2(theta) does amplify: there the
 // spin form (in the FP32 difference form) covers the groups that begin within AKRA_POLE_THETA_B.
 constexpr double AKRA_POLE_THETA_B = 0.3;
-// From this many rings on the register engine takes transforms below 4096 points.  It runs 2 to 16 rings in a
-// workgroup of 256 threads, which below that leaves most of the 256 compute units idle, while the LDS
-// kernel gives a ring 1024 threads and a compute unit of its own.  CG iteration, us, register engine / LDS: one
-// right-hand side, full sky, FP64, Nside 32 66.9 / 53.5, 64 85.3 / 64.9, 128 107.2 / 95.3, 160 (639 rings) 124.3 /
-// 133.6, 200 152.1 / 168.3; three, footprint, Nside 48 108.7 / 100.7, 64 108.5 / 107.3, 96 78.7 / 90.8; eight,
-// Nside 16 93.6 / 87.4, 24 89.9 / 94.2.
-constexpr int RING_ENGINE_MIN = 640;
 
 namespace akra {
 
@@ -581,14 +574,14 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     // Bluestein convolution fits in LDS (M <= BF_MAXM), and the rest as two sub-transforms of length
     // N / 2, each by Bluestein (M <= 8192 since N <= 4 nside <= 8192)
     // The register engine, unless it is switched off, takes the rings whose transform length M is 4096
-    // or 8192, and in plans of at least RING_ENGINE_MIN rings (times the right-hand sides that a launch takes)
+    // or 8192, and in launches of at least RING_ENGINE_MIN rings times right-hand sides
     // those of M = 256 to 2048 with at most about eight orders per bin (2 lmax + 1 <= 8 N:
     // its threads fold a bin alone; the LDS kernels fold shorter rings with the whole workgroup.  Taking
     // every ring, synthesis and adjoint of all rings at Nside 300, lmax 750 took 433 us, with this bound 375).
     // Power-of-two rings below 256 pixels go through Bluestein there.
-    const bool many = (int64_t)P->nrings * (prec == AKRA_FP32 ? nrhs : 1) >= RING_ENGINE_MIN;
+    const bool many = (int64_t)P->nrings * nrhs >= RING_ENGINE_MIN, both = many && P->nrings < RING_ENGINE_MIN;
     const int BF_MAXM = g_ring_whole_maxm;
-    std::vector<int> p2, bl, bf, rl[RG_N];
+    std::vector<int> p2, bl, bf, rl[RG_N], few_p2, few_bf;
     int maxp2 = 1, maxbl = 1, maxbf = 1, maxreg = 1;  // the LDS kernels' lists, and the register engine
     auto log2i = [](int m) { return 31 - __builtin_clz((unsigned)m); };
     for (int r = 0; r < P->nrings; ++r) {
@@ -598,6 +591,7 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         while (MF < 2 * N - 1) MF <<= 1;
         const bool few = g_ring_register && many && 2 * lmax + 1 <= 8 * N;
         if (!ri.M) {
+            if (both) few_p2.push_back(r);
             if (N <= 8192 && ((few && N >= 256) || (g_ring_register && N >= 4096))) {
                 rl[RG_DIRECT + log2i(N) - 8].push_back(r);
                 maxreg = std::max(maxreg, N);
@@ -607,8 +601,8 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
                 maxreg = std::max(maxreg, MF);
             } else {
                 p2.push_back(r);
-                maxp2 = std::max(maxp2, ri.sub);
             }
+            if (both || (!p2.empty() && p2.back() == r)) maxp2 = std::max(maxp2, ri.sub);
             continue;
         }
         int M1 = 1;
@@ -616,12 +610,13 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
         if (M1 <= BF_MAXM) {
             const bool reg = g_ring_register && MF <= BF_MAXM && MF <= 8192 && (few || M1 >= 4096);
             ri.M = reg ? MF : M1;  // the whole ring's convolution length
+            if (both) few_bf.push_back(r);
+            if (both || !reg) maxbf = std::max(maxbf, ri.M);
             if (reg) {
                 rl[RG_BLUE + log2i(MF) - 8].push_back(r);
                 maxreg = std::max(maxreg, MF);
             } else {
                 bf.push_back(r);
-                maxbf = std::max(maxbf, M1);
             }
         } else {
             int M2 = 1;
@@ -641,10 +636,14 @@ static akra_status create(int nside, int lmax, int nrhs, int prec, void *stream,
     std::stable_sort(bl.begin(), bl.end(), bysize);
     std::stable_sort(bf.begin(), bf.end(), bysize);
     for (auto &v : rl) std::stable_sort(v.begin(), v.end(), bysize);
+    std::stable_sort(few_p2.begin(), few_p2.end(), bysize);
+    std::stable_sort(few_bf.begin(), few_bf.end(), bysize);
     P->h_order[RK_P2] = p2;
     P->h_order[RK_BF] = bf;
     P->h_order[RK_BL] = bl;
     for (int q = 0; q < RG_N; ++q) P->h_order[RK_REG + q] = rl[q];
+    P->h_order[RK_FEW_P2] = few_p2;
+    P->h_order[RK_FEW_BF] = few_bf;
     P->maxM_p2 = maxp2;
     P->maxM_bl = maxbl;
     P->maxM_bf = maxbf;

@@ -33,16 +33,19 @@ def _operands(nside, lmax, nrhs, full):
     return alm, ninv, torch.from_numpy(mask.astype(np.uint8)).to(dev)
 
 
-# rings x right-hand sides on both sides of 640: 612, 663, 630, 693 (FP32 counts the right-hand sides), 635, 643
+# rings x right-hand sides on both sides of 640: 612, 663, 630, 693, 635, 643; and FP64 plans whose transforms lie above
+# (762, 765 and 765) and whose applies, one right-hand side at a time, below
 @pytest.mark.parametrize("nside,lmax,prec,nrhs", [(13, 20, "fp32", 12), (13, 20, "fp32", 13), (16, 60, "fp32", 10),
                                                   (16, 24, "fp32", 11), (159, 40, "fp64", 1), (161, 40, "fp64", 1),
-                                                  (161, 200, "fp32", 1)])
+                                                  (161, 200, "fp32", 1), (32, 64, "fp64", 6),
+                                                  (64, 128, "fp64", 3), (64, 250, "fp64", 3)])
 def test_both_sides(nside, lmax, prec, nrhs):
     alm, ninv, mask = _operands(nside, lmax, nrhs, False)
     out = []
     for engine in (True, False):
         p = _plan(nside, lmax, prec, nrhs, engine)
-        out.append([x.cpu().numpy() for x in (*p.synth2(*alm), *p.apply_H(ninv, mask, *alm, 0.02))])
+        maps = p.synth2(*alm)
+        out.append([x.cpu().numpy() for x in (*maps, *p.adjoint2(*maps), *p.apply_H(ninv, mask, *alm, 0.02))])
         p.close()
     for a, b in zip(*out):
         assert np.linalg.norm(a - b) <= (1e-12 if prec == "fp64" else 2e-6) * np.linalg.norm(b)
