@@ -278,13 +278,16 @@ template <int N> __device__ __forceinline__ void fma_row(double &acc, double r, 
 {
     asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(r), "v"(c), "n"(N));
 }
+// the same with the wait states (see settle) in front
+template <int N> __device__ __forceinline__ void fma_row_settled(double &acc, double r, double c)
+{
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+        : "+v"(acc)
+        : "v"(r), "v"(c), "n"(N));
+}
 // r's last write to its registers is two wait states back (a DPP operand's hazard after a vector write, which the
 // compiler does not see in inline asm).  Due at the start of every straight run of fma_row: a register copy or
 // reload may end the block before.
-__device__ __forceinline__ void settle(double (&r)[4])
-{
-    asm volatile("s_nop 1" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
-}
 __device__ __forceinline__ void settle(SRec &r)
 {
     asm volatile("s_nop 1" : "+v"(r.a), "+v"(r.q0), "+v"(r.q1), "+v"(r.u0), "+v"(r.u1));
