@@ -53,11 +53,11 @@ def live_ring_bytes(nside, lmax, w, fg_bytes):
 # the kernel sources and launch shapes they were taken with (the SHA-256 of the Legendre sources and
 # the plan's two- and one-sided shapes are checked at run time).
 TRAFFIC = {
-    # profiles/cases_kernels.md: two-sided k_leg_adj<double, 6, 1, 8, 0> FETCH 3.3631e5 KiB x 2.0 + WRITE
-    # 6.8352e5 KiB, one-sided k_leg_adj<double, 7, 1, 8, 2> FETCH 4.7525e5 KiB x 2.0 + WRITE 1.15272e6 KiB (means
+    # profiles/cases_kernels.md: two-sided k_leg_adj<double, 6, 1, 8, 0> FETCH 3.0307e5 KiB x 2.0 + WRITE
+    # 5.3247e5 KiB, one-sided k_leg_adj<double, 7, 1, 8, 2> FETCH 4.7566e5 KiB x 2.0 + WRITE 1.15269e6 KiB (means
     # of the two dispatches of each run)
-    "leg_adj": {"bytes": 3.542e9, "workload": (2048, 4096), "shapes": ((1, 2, 8, 1, 8), (1, 1, 8, 1, 8)),
-                "sources_sha256": "685f7189abf0d907a006e1ec5e190985f0d620e2a9d76c91e9ffb5f78fb92575"},
+    "leg_adj": {"bytes": 3.320e9, "workload": (2048, 4096), "shapes": ((1, 2, 8, 1, 8), (1, 1, 8, 1, 8)),
+                "sources_sha256": "14deea913b08714ad91c5aced363d635b80298426fc972b94d40de05efc4d685"},
 }
 LEG_SOURCES = ("akra_internal.h", "akra_leg.h", "akra_leg_both.hip", "akra_leg_north.hip", "akra_leg_south.hip",
                "akra_kernels.hip")

@@ -163,7 +163,7 @@ __device__ __forceinline__ int64_t ext_base(int m, int lmax) { return alm_base(m
 //   u_l = w_2(l-2) B_{l-2} + w_0(l) B_l + w_-2(l+2) B_{l+2} - i (x_1(l-1) E_{l-1} + x_-1(l+1) E_{l+1})
 // (the stencil is zero at degrees below 2, whose coefficients take no part whatever they hold).  All loads
 // go out together, none behind a condition: a neighbour outside its column reads the entry nearest to it and counts as
-// zero.  One neighbour after the other, the prologue waited for five latencies in turn (Nside 40: 5.0 us, so 3.9).
+// zero.  One neighbour after the other, the prologue waited for five latencies in turn (Nside 40: 5.3 us, so 4.0).
 // K, E, B: kernel and coefficients of the entry itself, as they are stored.
 __device__ __forceinline__ void stencil_in(const double2 *__restrict__ xE, const double2 *__restrict__ xB,
                                            const double *__restrict__ kern, const double *__restrict__ sten, int l,
