@@ -57,7 +57,7 @@ TRAFFIC = {
     # 5.3247e5 KiB, one-sided k_leg_adj<double, 7, 1, 8, 2> FETCH 4.7566e5 KiB x 2.0 + WRITE 1.15269e6 KiB (means
     # of the two dispatches of each run)
     "leg_adj": {"bytes": 3.320e9, "workload": (2048, 4096), "shapes": ((1, 2, 8, 1, 8), (1, 1, 8, 1, 8)),
-                "sources_sha256": "14deea913b08714ad91c5aced363d635b80298426fc972b94d40de05efc4d685"},
+                "sources_sha256": "589a88c1ae1d0916d64ae8717a95d447cf2f62b1b705a4d6cd7aae25b66144ef"},
 }
 LEG_SOURCES = ("akra_internal.h", "akra_leg.h", "akra_leg_both.hip", "akra_leg_north.hip", "akra_leg_south.hip",
                "akra_kernels.hip")

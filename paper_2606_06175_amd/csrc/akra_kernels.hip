@@ -578,7 +578,7 @@ __device__ __forceinline__ void ring_full_body(cplx<T> *__restrict__ buf, int r,
 // ================================================================================================
 // Ring stage for rings of any length N whose Bluestein convolution (length M >= 2N - 1, a power of
 // two) fits in LDS: one DFT of the whole ring per direction by Bluestein's chirp-z, with the chirp
-// spectrum of length N from the plan's table; fold and unfold in m order as in k_ring_full.
+// spectrum of length N from the plan's table; fold and unfold in m order as in ring_full_body.
 // MODE as above.
 // ================================================================================================
 constexpr int RBU = 4;  // elements per thread: N <= RF * RBU
